@@ -35,11 +35,52 @@ __host__ __device__ inline int pair_index(int p, int q) {
 }
 // index of the off-diagonal pair a > b among the n (n - 1) / 2 such pairs
 __host__ __device__ inline int offdiag_index(int a, int b) { return a * (a - 1) / 2 + b; }
-// Active spaces of up to kFoldMax orbitals: the sigma contraction sums the
-// diagonal pairs' part of sigma itself and G holds only the off-diagonal pair
-// rows; larger ones keep every pair row in G (their contraction kernels have
-// no register room for the epilogue).
-constexpr int kFoldMax = 10;
+
+// Active spaces of up to kStringMax orbitals take sigma from string operators
+// (k_sigma_same_spin, k_sigma_dgemm): the opposite-spin intermediate E of one
+// alpha string fits the LDS.  Larger ones contract all pairs of every
+// determinant into the array G (k_sigma_dgemm_pairrows, k_sigma_gather).
+// The shapes below fix the layout of their link tables and of E.
+constexpr int kStringMax = 10;
+constexpr int kStringPassRows = 28;  // off-diagonal pairs of 8 orbitals
+__host__ __device__ constexpr int string_binom(int n, int k) {
+  int r = 1;
+  for (int i = 1; i <= k; ++i) r = r * (n - k + i) / i;
+  return r;
+}
+// columns of an integral row: the pairs, rounded up to 4
+__host__ __device__ constexpr int string_kp(int n) { return (n * (n + 1) / 2 + 3) / 4 * 4; }
+// E in one pass of all rows, or from 9 orbitals on in two of 28 rows
+__host__ __device__ constexpr int string_passes(int n) { return n >= 9 ? 2 : 1; }
+__host__ __device__ constexpr int string_rows(int n) {
+  return n >= 9 ? kStringPassRows : string_kp(n);
+}
+// row stride of E in LDS: the most strings rounded up to an odd multiple of 16
+// doubles, which spreads the rows of one store over the banks
+__host__ __device__ constexpr int string_stride(int n) {
+  const int c = (string_binom(n, n / 2) + 15) / 16;
+  return 16 * (c % 2 ? c : c + 1);
+}
+// slots of an alpha string's links (off-diagonal ones and the diagonal one),
+// in whole k-steps of 4, at least two k-steps below the largest count
+__host__ __device__ constexpr int string_kslots(int n, int ne) {
+  const int most = (1 + (n / 2) * ((n + 1) / 2) + 3) / 4;
+  const int k = (1 + ne * (n - ne) + 3) / 4, least = most > 2 ? most - 2 : 1;
+  return 4 * (k > least ? k : least);
+}
+// pairs of 16-bit link entries of a beta string in pass p, the most of any
+// string: with k electrons in the lowest 8 orbitals a string has k (8 - k)
+// links among them
+__host__ __device__ constexpr int string_gpairs(int n, int ne, int p) {
+  const int all = ne * (n - ne) + ne;
+  if (string_passes(n) == 1) return p == 0 ? (all + 1) / 2 : 0;
+  int most = 0;
+  for (int k = ne > n - 8 ? ne - (n - 8) : 0; k <= ne && k <= 8; ++k) {
+    const int c = p == 0 ? k * (8 - k) : all - k * (8 - k);
+    most = c > most ? c : most;
+  }
+  return (most + 1) / 2;
+}
 
 // Load through the global address space (pointers read from device structs
 // are generic; this keeps the loads off the flat path).
@@ -87,8 +128,9 @@ struct Item {
   int32_t Na, Nb, La, Lb;
   int64_t ndet;           // Na*Nb
   int64_t off;            // offset of this item in every vector slot of the arenas
-  int64_t goff;           // offset of its G block [npair][ndet]
-  int64_t woff;           // offset of its W matrix [kpad][kpad] (row-major)
+  int64_t goff;           // offset of its G block [npair][ndet] (above kStringMax)
+  int64_t woff;           // offset of its W matrix [kpad][kpad] (row-major), or
+                          // of its k_sigma_operands (up to kStringMax orbitals)
   int32_t kpad;           // npair rounded up to a multiple of 16
   int32_t ham;            // index of its ItemHam record
   int32_t chunk0, nchunk; // partial-reduction chunks [chunk0, chunk0+nchunk)
@@ -99,6 +141,8 @@ struct Item {
   const uint32_t* linkBT; // [Lb][Nb] (link-major copy: coalesced per-lane reads)
   const uint64_t* strA;   // [Na] alpha string bitmasks
   const uint64_t* strB;   // [Nb] beta string bitmasks
+  const uint32_t* klink;  // up to kStringMax orbitals: alpha and beta link tables
+  const uint32_t* glink;  //   of k_sigma_dgemm (see k_string_links)
   const int32_t* pairA;   // [Na][npair] pair table (see pack_pair_entry)
   const int32_t* pairB;   // [npair][Nb] the same for beta strings, pair-major
   // point-group blocked CASCI (null: the plain [Na][Nb] layout).  Then strA,

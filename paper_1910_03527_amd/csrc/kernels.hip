@@ -88,15 +88,12 @@ __global__ void k_strings(int n, int ne, int64_t N, uint64_t* out) {
 // canonical order (diagonal entries first, then q in I ascending, p not in I
 // ascending).  The sign is (-1)^(number of occupied orbitals strictly between
 // p and q), the parity of a+_p a_q acting on the occupation-number vector.
-// abi4 lists (p, q, J, s).  The packed tables are the sigma gather's.  Up
-// to kFoldMax orbitals an off-diagonal entry carries G's row
-// offdiag_index(max(p, q), min(p, q)) (the diagonal entries, first in packed,
-// carry pair_index(o, o) and the gather skips them) and the link-major copy
-// packedT holds only the L - ne off-diagonal links; above, entries carry
-// pair_index and packedT holds all L links.  packedT orders each string's
-// links by ascending pair field (a string's links have distinct pairs): at
-// link step l the lanes of a wave then read nearby rows of G's row block,
-// which the L1 and L2 serve far better than the canonical order's spread.
+// abi4 lists (p, q, J, s).  The packed tables are the sigma gather's; the
+// link-major copy packedT orders each string's links by ascending pair field
+// (a string's off-diagonal links have distinct pairs, as have its diagonal
+// ones): at link step l the lanes of a wave then read nearby rows of G's row
+// block, which the L1 and L2 serve far better than the canonical order's
+// spread.
 __global__ void k_links(int n, int ne, int64_t N, uint32_t* packed, uint32_t* packedT,
                         int32_t* abi4) {
   constexpr int kSortMax = kMaxActive * (kMaxActive / 2 + 1);  // links of a CASCI string
@@ -104,15 +101,13 @@ __global__ void k_links(int n, int ne, int64_t N, uint32_t* packed, uint32_t* pa
   if (I >= N) return;
   const int L = ne * (n - ne + 1);
   const bool sortT = packedT && L <= kSortMax;
-  const bool fold = n <= kFoldMax;  // the gather's layout of G (see k_sigma_gather)
-  const int nd = fold ? ne : 0;     // leading diagonal links left out of packedT
   uint32_t vs[kSortMax];
   uint64_t m = string_unrank(I, n, ne);
   int idx = 0;
   auto put = [&](uint32_t v) {
     if (packed) packed[I * L + idx] = v;
     if (sortT) vs[idx] = v;
-    else if (packedT && idx >= nd) packedT[(idx - nd) * N + I] = v;
+    else if (packedT) packedT[idx * N + I] = v;
   };
   for (int o = 0; o < n; ++o)
     if (m >> o & 1) {
@@ -132,7 +127,7 @@ __global__ void k_links(int n, int ne, int64_t N, uint32_t* packed, uint32_t* pa
       uint64_t between = (((uint64_t)1 << hi) - 1) & ~((((uint64_t)1 << lo) << 1) - 1);
       int sign = (__builtin_popcountll(m & between) & 1) ? -1 : 1;
       int64_t J = string_addr(r);
-      put(pack_link((int)J, fold ? offdiag_index(hi, lo) : pair_index(hi, lo), sign));
+      put(pack_link((int)J, pair_index(hi, lo), sign));
       if (abi4) {
         int32_t* e = abi4 + (I * L + idx) * 4;
         e[0] = p; e[1] = q; e[2] = (int32_t)J; e[3] = sign;
@@ -140,10 +135,10 @@ __global__ void k_links(int n, int ne, int64_t N, uint32_t* packed, uint32_t* pa
       ++idx;
     }
   }
-  if (sortT)  // links nd..L-1 in ascending pair field (distinct within a string)
-    for (int a = nd; a < L; ++a) {
+  if (sortT)  // links in ascending pair field (distinct within a string)
+    for (int a = 0; a < L; ++a) {
       int rank = 0;
-      for (int b = nd; b < L; ++b) rank += link_pair(vs[b]) < link_pair(vs[a]);
+      for (int b = 0; b < L; ++b) rank += link_pair(vs[b]) < link_pair(vs[a]);
       packedT[rank * N + I] = vs[a];
     }
 }
@@ -260,6 +255,12 @@ __device__ void build_item_hamiltonian(const ActiveSet& s, int M, const double* 
   }
 }
 
+// whether sigma of this CASCI contracts all pairs (needs W): the others take
+// k_sigma_operands
+__device__ inline bool pair_matrix(const Item& I) {
+  return I.ndet > 1 && (I.sym || I.n > kStringMax);
+}
+
 // One block per item: decode the tuple of bucket (order, nocc) from its index
 // (lexicographic ranks of its occupied and virtual parts), form A = R u T and
 // F = O \ A, and build the item's folded Hamiltonian and W.
@@ -316,7 +317,7 @@ __global__ void k_mbe_setup(MbeSpaces sp, const BucketDev* __restrict__ buckets,
   __syncthreads();
   const Item& I = items[it];
   build_item_hamiltonian(s, sp.M, h1, eri, e_const, I.na + I.nb, &hams[I.ham],
-                         I.ndet > 1 ? warena + I.woff : nullptr, I.kpad);
+                         pair_matrix(I) ? warena + I.woff : nullptr, I.kpad);
 }
 
 // Direct CASCI set-up: the whole given space is active (no frozen orbitals).
@@ -334,7 +335,7 @@ __global__ void k_casci_setup(int n, const double* const* h1s, const double* con
   __syncthreads();
   const Item& I = items[it];
   build_item_hamiltonian(s, n, h1s[it], eris[it], ecores[it], I.na + I.nb, &hams[I.ham],
-                         I.ndet > 1 ? warena + I.woff : nullptr, I.kpad);
+                         pair_matrix(I) ? warena + I.woff : nullptr, I.kpad);
 }
 
 // --------------------------------------------------------------- diagonal
@@ -371,13 +372,15 @@ __global__ void k_hdiag(const Item* __restrict__ items, const Work* __restrict__
 }
 
 // ------------------------------------------------------------------ sigma
-// sigma = (H - E_core) c by the Knowles-Handy / Olsen factorisation:
+// sigma = (H - E_core) c.  Above kStringMax orbitals by the Knowles-Handy /
+// Olsen factorisation
 //   D+_ab[K] = <K| E_ab + E_ba |c>   (a > b),   D+_aa[K] = <K|E_aa|c>
 //   G = W D+                          (the only dense step: FP64 MFMA)
 //   sigma_I = sum over links E_xy I = s K of s G_pair(x,y)[K]
-// Step 1+2 run fused in k_sigma_dgemm (D+ tile in LDS), step 3 in
-// k_sigma_gather.  Both read the vector slot given by `slot` (>= 0: fixed
-// slot, items with slot >= their guess count skip; -1: the item's newest).
+// (steps 1+2 fused in k_sigma_dgemm_pairrows, D+ tile in LDS, step 3 in
+// k_sigma_gather); up to kStringMax orbitals from string operators (below).
+// All read the vector slot given by `slot` (>= 0: fixed slot, items with
+// slot >= their guess count skip; -1: the item's newest).
 typedef double double4_t __attribute__((ext_vector_type(4)));
 
 __device__ inline int vec_slot(const DavState& st, int slot) {
@@ -408,334 +411,563 @@ __device__ inline bool item_active(const DavState& st, int slot) {
   return slot < 0 || slot < st.nguess;
 }
 
-// Contraction G = W D+ on FP64 MFMA.  A tile is one alpha string Ka and TN
-// consecutive beta strings; a workgroup keeps one beta block (TN strings)
-// and walks down a range of alpha strings (tiles are numbered column-major:
-// tile = block * Na + Ka).  A thread builds the same (pair, column) slots of
-// D+ in every tile; their beta pair-table entries are loaded once per work
-// unit, into registers for 32-column tiles of up to 10 orbitals (where the
-// kernel still fits four waves per SIMD) and into LDS otherwise.  Per tile
-// the c row of Ka is staged in LDS.  The alpha half of a D+ entry is
-// wave-uniform: a scalar pair-table load and a coalesced row segment of c.
-// D+ [pair][TN] (B operand) is staged in LDS, the wave's W rows (A operand)
-// sit in registers.  G is stored [Ka][row][Kb], rows g_stride(Nb) long: up to
-// kFoldMax orbitals the off-diagonal pairs (row offdiag_index), above every
-// pair (row pair_index, k_sigma_dgemm_pairrows).
+// Matrix element <I|H - E_core|J> between two different determinants of the
+// active space (Slater-Condon rules; strings are bit masks over the active
+// orbitals, alpha string before beta string, each in ascending order).
+__device__ inline int between_parity(uint64_t s, int p, int q) {
+  const int lo = p < q ? p : q, hi = p < q ? q : p;
+  const uint64_t m = (((uint64_t)1 << hi) - 1) & ~((((uint64_t)1 << lo) << 1) - 1);
+  return __builtin_popcountll(s & m) & 1;
+}
+__device__ double sc_offdiag(const ItemHam& H, uint64_t ia, uint64_t ib, uint64_t ja,
+                             uint64_t jb) {
+  const uint64_t xa = ia ^ ja, xb = ib ^ jb;
+  const int da = __builtin_popcountll(xa) >> 1, db = __builtin_popcountll(xb) >> 1;
+  if (da + db > 2) return 0.0;
+  const double* __restrict__ eri = H.eri;
+  const int M = H.M;
+  auto g = [&](int p, int q, int r, int s) -> double {
+    return ldg(eri + (((int64_t)H.act[p] * M + H.act[q]) * M + H.act[r]) * M + H.act[s]);
+  };
+  if (da + db == 1) {
+    // one excitation q -> p in the string of spin sigma
+    const uint64_t is = da ? ia : ib, js = da ? ja : jb, jo = da ? jb : ja;
+    const int p = __builtin_ctzll(is & ~js), q = __builtin_ctzll(js & ~is);
+    double v = H.heff[p * kMaxActive + q];
+    for (uint64_t x = js; x; x &= x - 1) {
+      const int r = __builtin_ctzll(x);
+      v += g(p, q, r, r) - g(p, r, r, q);   // r = q contributes zero
+    }
+    for (uint64_t x = jo; x; x &= x - 1) {
+      const int r = __builtin_ctzll(x);
+      v += g(p, q, r, r);
+    }
+    return between_parity(js, p, q) ? -v : v;
+  }
+  if (da == 1 && db == 1) {
+    const int p = __builtin_ctzll(ia & ~ja), q = __builtin_ctzll(ja & ~ia);
+    const int r = __builtin_ctzll(ib & ~jb), s = __builtin_ctzll(jb & ~ib);
+    const double v = g(p, q, r, s);
+    return (between_parity(ja, p, q) ^ between_parity(jb, r, s)) ? -v : v;
+  }
+  // two excitations in one string: holes q1 < q2, particles p1 < p2;
+  // I = E_p1q1 E_p2q2 J (up to the sign), element (p1 q1|p2 q2) - (p1 q2|p2 q1)
+  const uint64_t is = da ? ia : ib, js = da ? ja : jb;
+  uint64_t pp = is & ~js, hh = js & ~is;
+  const int p1 = __builtin_ctzll(pp), p2 = 63 - __builtin_clzll(pp);
+  const int q1 = __builtin_ctzll(hh), q2 = 63 - __builtin_clzll(hh);
+  const uint64_t k = (js & ~((uint64_t)1 << q2)) | ((uint64_t)1 << p2);
+  const int par = between_parity(js, p2, q2) ^ between_parity(k, p1, q1);
+  const double v = g(p1, q1, p2, q2) - g(p1, q2, p2, q1);
+  return par ? -v : v;
+}
+
 constexpr int64_t binom_c(int n, int k) {
   int64_t r = 1;
   for (int i = 1; i <= k; ++i) r = r * (n - k + i) / i;
   return r;
 }
 
-// Up to kFoldMax orbitals the diagonal pairs kk need no row of G: E_kk only counts occupations, so
-// their part of sigma, sum_k n_k(I) G_kk[I] with n_k(I) = n_k(Ia) + n_k(Ib),
-// is summed in the contraction's epilogue and written to sigma, and the
-// gather adds the off-diagonal links to it.  The contraction's output rows
-// are the off-diagonal pairs a > b first (row offdiag_index(a, b), the row of
-// G, which the gather's link tables carry), then padding, then the n
-// diagonal pairs in the last n rows of the last 16-row block (row
-// nrows - n + k: pair kk).  That block's wave, which sums the diagonal part,
-// has few or no G rows to store, so the waves stay balanced.
-// pair_index of output row r (nrows rows, n orbitals; -1: padding)
-__device__ inline int out_row_pair(int r, int n, int nrows) {
-  if (r >= nrows - n) return pair_index(r - (nrows - n), r - (nrows - n));
-  if (r >= n * (n - 1) / 2) return -1;
-  int a = 1;
-  while ((a + 1) * a / 2 <= r) ++a;
-  return pair_index(a, r - a * (a - 1) / 2);
+// Active spaces of up to kStringMax orbitals: H - E_core splits into a part
+// in the alpha string, a part in the beta string and the opposite-spin part,
+//   sigma = Ha C + C Hb + sum_{pq,rs} (pq|rs) Ea_pq Eb_rs C     (C = [Na][Nb]),
+// with Ha, Hb the Slater-Condon matrices of one spin's strings.  The first two
+// are dense products (k_sigma_same_spin).  In the third the alpha operators of
+// one string Ia are its links only (1 + na (n - na) of the n (n + 1) / 2 pairs,
+// the occupied diagonal ones taken together), so
+//   E[rs][Jb] = sum_{links kl of Ia} s_kl (rs|kl) C[Ja][Jb]
+// is a dense product of half the depth of one over all pairs, its B operand
+// is rows of C as they stand in memory, and sigma[Ia][Ib] is a sum of E over
+// the links of Ib: E of one alpha string stays in LDS and nothing but C and
+// sigma passes through HBM (k_sigma_dgemm).
+//
+// FP64 products use v_mfma_f64_4x4x4_4b_f64: four independent 4x4x4 blocks.
+// Measured rates of independent chains: 70-74 TFLOP/s from one wave per SIMD
+// on, against 33 (one wave per SIMD) to 47 TFLOP/s (four) for the 16x16x4
+// form.  Lane l holds A[l%4][l/16] and B[l/16][l%4] of block (l/4)%4 and
+// receives D[l/16][l%4].  A 16-row A operand (lane l: row l%16) meets every
+// 4-column block of a 16-column B operand in four instructions, with A's
+// blocks rotated by r = 0..3: instruction r then holds row
+// 4 ((b - r) & 3) + l/16 of column l%16, b = (l/4)%4.
+template <int R>
+__device__ inline double rot_blocks(double x) {  // block b takes block (b - R) & 3
+  if constexpr (R == 0) {
+    return x;
+  } else {
+    const int lo = __builtin_amdgcn_mov_dpp(__double2loint(x), 0x120 + 4 * R, 0xf, 0xf, true);
+    const int hi = __builtin_amdgcn_mov_dpp(__double2hiint(x), 0x120 + 4 * R, 0xf, 0xf, true);
+    return __hiloint2double(hi, lo);
+  }
+}
+// Load at a byte offset of 32 bits from a uniform base (one address register).
+__device__ inline double ldg_at(const double* base, uint32_t bytes) {
+  return ldg((const double*)((const char*)base + bytes));
+}
+__device__ inline double mfma4(double a, double b, double c) {
+  return __builtin_amdgcn_mfma_f64_4x4x4f64(a, b, c, 0, 0, 0);
+}
+__device__ inline double flip_sign(double x, uint32_t bit31) {
+  return __hiloint2double(__double2hiint(x) ^ (int)(bit31 & 0x80000000u), __double2loint(x));
 }
 
-// With 32-column tiles of up to 10 orbitals the pair-table entries stay in
-// registers and the kernel is compiled for four waves per SIMD (128 registers
-// per lane, accumulators included), which those shapes reach without
-// spilling; larger shapes take the registers they need.  Active spaces of
-// 11 or more orbitals run larger workgroups, since their LDS holds one or two
-// workgroups per CU: 512 threads (two waves per SIMD) for 11-12 orbitals,
-// 1024 (four per SIMD) for 13-14, where waves split a tile's output blocks
-// by row block and column half.
-// Active spaces of 8 or 9 orbitals have three 16-row blocks of G (36 or 45
-// pairs padded to 48): their workgroups have three waves, one row block
-// each, so that every wave of the CU issues MFMAs.
-constexpr int dgemm_threads(int nact) {
-  return nact >= 13 ? 1024 : nact >= 11 ? 512 : (nact == 8 || nact == 9) ? 192 : 256;
-}
-constexpr bool dgemm_reg_entries(int nact, int tn, int nt) {
-  return (nt == 256 || nt == 192) && tn == 32 && nact <= 10;
+// Work unit of this block: runs of kXcdRun consecutive units go to one XCD
+// (blocks are dealt to the eight XCDs in turn), so that a CASCI's C, integral
+// rows and string Hamiltonians are fetched into few of the eight L2s.
+__device__ inline int xcd_unit(int block, int n) {
+  constexpr int kRun = 16, kXcds = 8;
+  const int whole = n / (kRun * kXcds) * (kRun * kXcds);
+  if (block >= whole) return block;
+  const int x = block % kXcds, k = block / kXcds;
+  return (k / kRun * kXcds + x) * kRun + k % kRun;
 }
 
-template <int NACT, int TN, int NT = dgemm_threads(NACT)>
-__global__ void __launch_bounds__(NT, dgemm_reg_entries(NACT, TN, NT) ? 4 : 1) k_sigma_dgemm(
-    const Item* __restrict__ items, const Work* __restrict__ work,
+// Integral rows of k_sigma_dgemm, per CASCI [no + Na + 1][kp] (no = n (n-1) / 2
+// off-diagonal pairs, kp = npair rounded up to 4): column c is (.|c) for
+// off-diagonal pair c < no (offdiag_index) and (.|kk) for c = no + k; row
+// kl < no is the integral row (kl|c), row no + Ia the sum over the occupied
+// orbitals of alpha string Ia of (kk|c), the last row zero.  Then Ha and, for
+// unequal electron counts, Hb, [np][np] with np = strings rounded up to 16 and
+// zero padding.
+__global__ void __launch_bounds__(256) k_sigma_operands(const Item* __restrict__ items,
+                                                        const ItemHam* __restrict__ hams,
+                                                        double* __restrict__ warena) {
+  const Item& I = items[blockIdx.x];
+  if (I.ndet <= 1 || I.sym || I.n > kStringMax) return;
+  const ItemHam& H = hams[I.ham];
+  const int n = I.n, no = n * (n - 1) / 2, kp = string_kp(n);
+  const double* __restrict__ eri = H.eri;
+  const int M = H.M;
+  auto g = [&](int p, int q, int r, int s) -> double {
+    return ldg(eri + (((int64_t)H.act[p] * M + H.act[q]) * M + H.act[r]) * M + H.act[s]);
+  };
+  const int64_t nv = (int64_t)(no + I.Na + 1) * kp;
+  const int pa = (I.Na + 15) & ~15, pb = (I.Nb + 15) & ~15;
+  const int64_t na2 = (int64_t)pa * pa, nb2 = I.na != I.nb ? (int64_t)pb * pb : 0;
+  double* __restrict__ out = warena + I.woff;
+  const int64_t step = (int64_t)gridDim.y * 256;
+  for (int64_t x = (int64_t)blockIdx.y * 256 + threadIdx.x; x < nv + na2 + nb2; x += step) {
+    double v = 0.0;
+    if (x < nv) {
+      const int row = (int)(x / kp), c = (int)(x % kp);
+      int a = 0, b = 0;
+      if (c < no) {
+        a = 1;
+        while ((a + 1) * a / 2 <= c) ++a;
+        b = c - a * (a - 1) / 2;
+      } else {
+        a = b = c - no;
+      }
+      if (a < n) {
+        if (row < no) {
+          int k = 1;
+          while ((k + 1) * k / 2 <= row) ++k;
+          v = g(k, row - k * (k - 1) / 2, a, b);
+        } else if (row < no + I.Na) {
+          for (uint64_t m = I.strA[row - no]; m; m &= m - 1) {
+            const int k = __builtin_ctzll(m);
+            v += g(k, k, a, b);
+          }
+        }
+      }
+    } else {
+      const bool beta = x >= nv + na2;
+      const int64_t y = x - nv - (beta ? na2 : 0);
+      const int np = beta ? pb : pa, N = beta ? I.Nb : I.Na;
+      const int i = (int)(y / np), j = (int)(y % np);
+      if (i < N && j < N) {
+        const uint64_t* str = beta ? I.strB : I.strA;
+        const uint64_t mi = str[i], mj = str[j];
+        if (i == j) {
+          for (uint64_t z = mi; z; z &= z - 1) {
+            const int p = __builtin_ctzll(z);
+            v += H.heff[p * kMaxActive + p];
+            for (uint64_t w = z & (z - 1); w; w &= w - 1) {
+              const int q = __builtin_ctzll(w);
+              v += H.J[p * kMaxActive + q] - H.K[p * kMaxActive + q];
+            }
+          }
+        } else {
+          v = sc_offdiag(H, mi, 0, mj, 0);
+        }
+      }
+    }
+    out[x] = v;
+  }
+}
+
+// Link tables of k_sigma_dgemm (either may be null), one thread per string of
+// ne electrons.
+// alpha [N][ks] (ks = string_kslots): slot k is the address Ja (bits 0..9), the
+// integral row (bits 10..20) and the sign (bit 31) of one off-diagonal link,
+// then the diagonal slot (own address, row no + I), then zero-row slots.
+// beta [entry pairs of pass 0, then of pass 1][N]: two 16-bit entries each,
+// bits 0..14 the position of E[rs][Jb] in LDS (row in the pass times
+// string_stride plus Jb), bit 15 the sign, links in ascending row order,
+// diagonal pairs last, filled up with the position of a zero.
+__global__ void k_string_links(int n, int ne, int64_t N, uint32_t* alpha, uint32_t* beta) {
+  const int64_t I = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (I >= N) return;
+  const uint64_t m = string_unrank(I, n, ne);
+  const int no = n * (n - 1) / 2, ks = string_kslots(n, ne);
+  const int S = string_stride(n), passes = string_passes(n), rp = string_rows(n);
+  uint32_t* __restrict__ al = alpha ? alpha + I * ks : nullptr;
+  int k = 0, pass = 0, cnt = 0, base = 0;
+  uint32_t held = 0;
+  auto put = [&](uint32_t e) {
+    if (!beta) return;
+    if (cnt & 1) beta[(int64_t)(base + cnt / 2) * N + I] = held | (e << 16);
+    else held = e;
+    ++cnt;
+  };
+  auto close = [&]() {  // fill the pass up to its entry count with zeros
+    const int full = 2 * string_gpairs(n, ne, pass);
+    while (beta && cnt < full) put((uint32_t)(rp * S));
+    base += full / 2;
+    cnt = 0;
+    ++pass;
+  };
+  for (int a = 1; a < n; ++a)
+    for (int b = 0; b < a; ++b) {
+      const int r = a * (a - 1) / 2 + b;
+      if (pass + 1 < passes && r == (pass + 1) * rp) close();
+      const bool ia = m >> a & 1, ib = m >> b & 1;
+      if (ia == ib) continue;
+      const uint64_t o = (m ^ ((uint64_t)1 << a)) ^ ((uint64_t)1 << b);
+      const uint64_t between = (((uint64_t)1 << a) - 1) & ~((((uint64_t)1 << b) << 1) - 1);
+      const uint32_t neg = __builtin_popcountll(m & between) & 1;
+      const uint32_t J = (uint32_t)string_addr(o);
+      if (al) al[k++] = J | ((uint32_t)r << 10) | (neg << 31);
+      put((uint32_t)((r - pass * rp) * S) + J | (neg << 15));
+    }
+  if (al) al[k++] = (uint32_t)I | ((uint32_t)(no + I) << 10);
+  while (al && k < ks) al[k++] = (uint32_t)I | ((uint32_t)(no + N) << 10);
+  for (int o = 0; o < n; ++o)
+    if (m >> o & 1) put((uint32_t)((no + o - pass * rp) * S) + (uint32_t)I);
+  close();
+}
+
+// sigma = Ha C + C Hb.  One wave per tile of 16 RB alpha x 16 CB beta strings,
+// the first sum over Ja, then the second over Jb, each in chunks of 16 (four
+// k-steps, the next chunk's operands loaded while one is multiplied).  Ha's
+// and Hb's symmetry and C's layout give every operand whole 128-byte lines:
+// in the second sum lane l takes four consecutive C[Ia][Jb] and the k order
+// is permuted to match.  Bound by the FP64 matrix pipe (2 (Na + Nb) flops per
+// determinant, operands from L2).
+typedef double double2u_t __attribute__((ext_vector_type(2), aligned(8)));
+template <int RB, int CB>
+__global__ void __launch_bounds__(256, 2) k_sigma_same_spin(
+    const Item* __restrict__ items, const Work* __restrict__ work, int nwork,
     const double* __restrict__ warena, const double* __restrict__ V, int64_t ntot,
-    double* __restrict__ Garena, double* __restrict__ Sarena, const DavState* __restrict__ st,
-    int slot) {
-  constexpr int NP = NACT * (NACT + 1) / 2;
-  constexpr int KPAD = (NP + 15) / 16 * 16;
-  constexpr int KS = (NP + 3) / 4;       // MFMA k-steps (4 pair rows per step)
-  constexpr int KR = KS * 4;             // D+ rows held in LDS (zero beyond NP)
-  constexpr int NRB = KPAD / 16;         // 16-row blocks of G
-  constexpr int NW = NT / 64;            // waves per workgroup
-  constexpr int NCB = TN / 16;           // 16-column blocks per tile
-  constexpr int NCG = (NW >= 16 && NCB % 2 == 0) ? 2 : 1;  // column groups of waves
-  constexpr int NRG = NW / NCG;          // row groups of waves
-  constexpr int NCBW = NCB / NCG;        // column blocks per wave
-  constexpr int RBW = (NRB + NRG - 1) / NRG;  // row blocks per wave
-  constexpr int NSUB = NT / TN;          // row groups of the D+ build
-  constexpr int NPER = (NP + NSUB - 1) / NSUB;
-  constexpr int LDT = TN + 1;            // padded LDS row (doubles)
-  constexpr int CMAX = (int)binom_c(NACT, NACT / 2);  // largest string count for NACT
-  constexpr int CPT = (CMAX + NT - 1) / NT;           // c-row doubles per thread
-  constexpr int TPT = (NP * TN + NT - 1) / NT;        // beta-table entries per thread
-  constexpr bool EREG = dgemm_reg_entries(NACT, TN, NT);  // the launch-bounds rule
-  constexpr int NO = NP - NACT;          // off-diagonal pairs: the rows of G
-  static_assert(NACT <= kFoldMax, "larger active spaces take k_sigma_dgemm_pairrows");
-  __shared__ double Ds[KR * LDT];
-  __shared__ int32_t Tb[EREG ? 1 : NP * TN];
-  __shared__ double Cr[CMAX];
-  __shared__ uint32_t occB[TN];          // occupations of the work unit's beta strings
-
-  const Work wk = work[blockIdx.x];
+    double* __restrict__ Sarena, const DavState* __restrict__ st, int slot) {
+  const int unit = __builtin_amdgcn_readfirstlane(
+      4 * xcd_unit((int)blockIdx.x, (int)gridDim.x) + (int)(threadIdx.x >> 6));
+  if (unit >= nwork) return;
+  const Work wk = work[unit];
   const Item& I = items[wk.item];
   const DavState& S = st[wk.item];
   if (!item_active(S, slot)) return;
   const int vs = vec_slot(S, slot);
-  const double* __restrict__ c = V + (int64_t)vs * ntot + I.off;
-  double* __restrict__ G = Garena + I.goff;
+  const int lane = threadIdx.x & 63, li = lane & 15, lk = lane >> 4;
   const int Na = I.Na, Nb = I.Nb;
-  const int32_t* __restrict__ pA = I.pairA;
-  const int32_t* __restrict__ pB = I.pairB;
+  const int pa = (Na + 15) & ~15, pb = (Nb + 15) & ~15;
+  const double* __restrict__ c = V + (int64_t)vs * ntot + I.off;
+  const double* __restrict__ Ha = warena + I.woff +
+                                  (int64_t)(I.n * (I.n - 1) / 2 + Na + 1) * string_kp(I.n);
+  const double* __restrict__ Hb = I.na != I.nb ? Ha + (int64_t)pa * pa : Ha;
+  const int r0 = wk.begin * 16 * RB, c0 = wk.end * 16 * CB;  // first alpha, beta string
+  int ia[RB], jb[CB];
+#pragma unroll
+  for (int r = 0; r < RB; ++r) ia[r] = min(r0 + 16 * r + li, Na - 1);
+#pragma unroll
+  for (int q = 0; q < CB; ++q) jb[q] = min(c0 + 16 * q + li, Nb - 1);
+  double acc[RB][CB][4];
+#pragma unroll
+  for (int r = 0; r < RB; ++r)
+#pragma unroll
+    for (int q = 0; q < CB; ++q)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) acc[r][q][v] = 0.0;
+  double A[2][RB][4], B[2][CB][4];
+  auto load1 = [&](int k0, double (&a)[RB][4], double (&b)[CB][4]) {
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const int ja = k0 + 4 * j + lk;          // < pa
+      const int jc = min(ja, Na - 1);          // Ha's rows beyond Na are zero
+#pragma unroll
+      for (int r = 0; r < RB; ++r) a[r][j] = ldg(Ha + ja * pa + ia[r]);
+#pragma unroll
+      for (int q = 0; q < CB; ++q) b[q][j] = ldg(c + jc * Nb + jb[q]);
+    }
+  };
+  auto load2 = [&](int k0, double (&a)[RB][4], double (&b)[CB][4]) {
+    const int j0 = k0 + 4 * lk;  // this lane's four Jb (< pb)
+#pragma unroll
+    for (int r = 0; r < RB; ++r) {
+      const double* __restrict__ row = c + ia[r] * Nb;
+      if (k0 + 16 <= Nb) {  // uniform
+        const double2u_t x = ldg((const double2u_t*)(row + j0)),
+                         y = ldg((const double2u_t*)(row + j0 + 2));
+        a[r][0] = x[0], a[r][1] = x[1], a[r][2] = y[0], a[r][3] = y[1];
+      } else {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) a[r][j] = ldg(row + min(j0 + j, Nb - 1));
+      }
+    }
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+#pragma unroll
+      for (int q = 0; q < CB; ++q) b[q][j] = ldg(Hb + (j0 + j) * pb + jb[q]);
+  };
+  auto multiply = [&](const double (&a)[RB][4], const double (&b)[CB][4]) {
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+#pragma unroll
+      for (int r = 0; r < RB; ++r) {
+        const double a1 = rot_blocks<1>(a[r][j]), a2 = rot_blocks<2>(a[r][j]),
+                     a3 = rot_blocks<3>(a[r][j]);
+#pragma unroll
+        for (int q = 0; q < CB; ++q) {
+          acc[r][q][0] = mfma4(a[r][j], b[q][j], acc[r][q][0]);
+          acc[r][q][1] = mfma4(a1, b[q][j], acc[r][q][1]);
+          acc[r][q][2] = mfma4(a2, b[q][j], acc[r][q][2]);
+          acc[r][q][3] = mfma4(a3, b[q][j], acc[r][q][3]);
+        }
+      }
+  };
+  const int n1 = pa / 16, n2 = pb / 16;
+  load1(0, A[0], B[0]);
+  for (int k = 0; k < n1 + n2; k += 2) {
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      if (k + h < n1 + n2) {
+        const int nx = k + h + 1;
+        if (nx < n1) load1(16 * nx, A[1 - h], B[1 - h]);
+        else if (nx < n1 + n2) load2(16 * (nx - n1), A[1 - h], B[1 - h]);
+        multiply(A[h], B[h]);
+      }
+    }
+  }
+  // instruction v of lane l is row 4 ((b - v) & 3) + l/16: put row block v
+  // into register v, so that a store covers whole 128-byte row pieces
+  double* __restrict__ out = Sarena + (int64_t)vs * ntot + I.off;
+  const bool b1 = lane & 4, b2 = lane & 8;
+#pragma unroll
+  for (int r = 0; r < RB; ++r)
+#pragma unroll
+    for (int q = 0; q < CB; ++q) {
+      const double* x = acc[r][q];
+      const double t0 = b1 ? x[1] : x[0], t1 = b1 ? x[0] : x[3], t2 = b1 ? x[3] : x[2],
+                   t3 = b1 ? x[2] : x[1];
+      const double y[4] = {b2 ? t2 : t0, b2 ? t3 : t1, b2 ? t0 : t2, b2 ? t1 : t3};
+      const int kb = c0 + 16 * q + li;
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        const int ka = r0 + 16 * r + 4 * v + lk;
+        if (ka < Na && kb < Nb) out[ka * Nb + kb] = y[v];
+      }
+    }
+}
 
-  const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
-  const int col = t % TN;
-  const int sub = (TN >= 64) ? __builtin_amdgcn_readfirstlane(t / TN) : t / TN;
+// Opposite-spin part, added to the same-spin part in sigma.  A workgroup of
+// WPS x SPW waves takes SPW alpha strings at a time, WPS waves each: the waves
+// of a string share its 16-column blocks of E, then thread Ib sums E over the
+// links of beta string Ib.  Links and their LDS positions stay in registers
+// for the whole work unit, the string's integral rows (A operand, rotated
+// copies of the 16-row block and replicated 4-row tails) for one pass.  From 9
+// orbitals on E is formed in two passes of 28 rows (the pairs of the lowest
+// 8 orbitals, then the rest and the diagonal pairs), so that two workgroups
+// of 10 orbitals share a CU and one's sums run under the other's products.
+// Every E element is one chain over the string's links in slot order and
+// every sum has a fixed order: sigma does not depend on WPS or SPW.
+template <int NACT>
+struct StringShape {
+  static constexpr int NP = NACT * (NACT + 1) / 2, NO = NP - NACT;
+  static constexpr int KP = string_kp(NACT), P = string_passes(NACT), RP = string_rows(NACT);
+  static constexpr int S = string_stride(NACT);
+  static constexpr int CMAX = (int)binom_c(NACT, NACT / 2);
+  static constexpr int KS = (1 + (NACT / 2) * ((NACT + 1) / 2) + 3) / 4;  // most k-steps
+  static constexpr int KS0 = KS > 2 ? KS - 2 : 1;  // the tables hold at least these
+  static constexpr int groups(int p) { return ((p + 1) * RP <= KP ? RP : KP - p * RP) / 4; }
+  static constexpr int gpairs(int p) {  // most entry pairs of a pass
+    int m = 0;
+    for (int ne = 0; ne <= NACT; ++ne) m = string_gpairs(NACT, ne, p) > m ? string_gpairs(NACT, ne, p) : m;
+    return m;
+  }
+};
 
-  const int blk = wk.begin / Na;          // every work unit stays inside one beta block
-  const int Kb0 = blk * TN;
-  const int Kb = Kb0 + col;
-  const double keep = Kb < Nb ? 1.0 : 0.0;  // ragged end of the row: zero columns
-  const int Kbc = Kb < Nb ? Kb : Nb - 1;
-  const double* __restrict__ ca = c + Kbc;  // alpha source of D+: ca[Ja * Nb]
-  for (int x = t; x < TN; x += NT) occB[x] = Kb0 + x < Nb ? (uint32_t)ldg(I.strB + Kb0 + x) : 0u;
-
-  // Row blocks rb = wrot + NRG r and column blocks cg NCBW .. of this wave.
-  // When the 16-row blocks of G do not come in multiples of NRG some waves
-  // have one block fewer; rotating the assignment by workgroup spreads those
-  // idle slots over the SIMDs.
-  const int cg = NCG == 1 ? 0 : wave / NRG;
-  const int wrot = ((NCG == 1 ? wave : wave % NRG) + (int)blockIdx.x) % NRG;
-  // W rows of this wave's row blocks, as MFMA A operands: lane l holds
-  // W[rb*16 + l%16][ks*4 + l/16] (B operand: lane l holds D+[ks*4 + l/16][l%16])
-  double wreg[RBW][KS];
+template <int NACT, int WPS, int SPW>
+__global__ void __launch_bounds__(64 * WPS * SPW, NACT >= 8 ? 2 : NACT == 7 ? 3 : 4) k_sigma_dgemm(
+    const Item* __restrict__ items, const Work* __restrict__ work,
+    const double* __restrict__ warena, const double* __restrict__ V, int64_t ntot,
+    double* __restrict__ Sarena, const DavState* __restrict__ st, int slot) {
+  using T = StringShape<NACT>;
+  constexpr int KS = T::KS, KS0 = T::KS0, S = T::S;
+  constexpr int TPS = 64 * WPS;                       // threads per string
+  constexpr int JPT = (T::CMAX + TPS - 1) / TPS;      // beta strings per thread
+  constexpr int ELDS = T::RP * S + 2;                 // E of a string, then a zero
+  __shared__ double Es[SPW * ELDS];
+  const Work wk = work[xcd_unit((int)blockIdx.x, (int)gridDim.x)];
+  const Item& I = items[wk.item];
+  const DavState& D = st[wk.item];
+  if (!item_active(D, slot)) return;
+  const int vs = vec_slot(D, slot);
+  const int Na = I.Na, Nb = I.Nb;
+  const double* __restrict__ c = V + (int64_t)vs * ntot + I.off;
   const double* __restrict__ W = warena + I.woff;
-#pragma unroll
-  for (int r = 0; r < RBW; ++r) {
-    const int rb = wrot + NRG * r;
-    const int wr = rb < NRB ? out_row_pair(rb * 16 + (lane & 15), NACT, KPAD) : -1;
-#pragma unroll
-    for (int ks = 0; ks < KS; ++ks)
-      wreg[r][ks] = wr >= 0 ? ldg(W + wr * KPAD + ks * 4 + (lane >> 4)) : 0.0;
-  }
-  // This thread's beta pair-table entries: slot i is pair sub + NSUB i of
-  // column col (x = t + NT i has x / TN = sub + NSUB i and x % TN = col),
-  // the slots it writes in every tile's D+.  Then the zero padding rows of D+.
-  static_assert(TPT == NPER, "one pair-table entry per D+ slot of a thread");
-  // With EREG the entries stay in registers, packed: the Cr position jb of
-  // slot i in byte i % 4 of jbp[i / 4], its sign and non-zero flag in bit i
-  // of sgb and nzb (at most 10 orbitals: jb < 256).
-  constexpr int NJP = (NPER + 3) / 4;
-  uint32_t jbp[NJP], sgb = 0, nzb = 0;
-#pragma unroll
-  for (int q = 0; q < NJP; ++q) jbp[q] = 0;
-#pragma unroll
-  for (int i = 0; i < NPER; ++i) {
-    const int ab = sub + NSUB * i;
-    const int32_t e = ab < NP ? ldg(pB + ab * Nb + Kbc) : 0;
-    if constexpr (EREG) {
-      jbp[i / 4] |= (uint32_t)(e ? (e >> 1) - 1 : 0) << (8 * (i % 4));
-      sgb |= (uint32_t)(e & 1) << i;
-      nzb |= (uint32_t)(e != 0) << i;
-    } else if (ab < NP) {
-      Tb[t + NT * i] = e;
-    }
-  }
-  for (int x = NP * LDT + t; x < KR * LDT; x += NT) Ds[x] = 0.0;
+  double* __restrict__ out = Sarena + (int64_t)vs * ntot + I.off;
 
-  // Software pipeline over the tiles of the work unit: the alpha pair-table
-  // entries of tile i+1 are loaded while tile i builds D+, and the c row and
-  // alpha-half values of tile i+1 while tile i runs its MFMAs.
-  int32_t ea[NPER];   // alpha pair-table entries (only while their values are loaded)
-  uint32_t sga = 0, nza = 0;  // their signs and non-zero flags, bit i
-  double ga[NPER];    // c values they address (alpha half of D+)
-  double cr[CPT];     // this thread's share of the c row Ka
-  // The alpha entries are wave-uniform per row (scalar loads): with TN = 32
-  // a wave covers the two rows 2*wave and 2*wave+1 of each row group.
-  const int wave_u = __builtin_amdgcn_readfirstlane(wave);
-  auto load_entries = [&](int ka, int32_t (&e)[NPER]) {
-    const int32_t* __restrict__ pa = pA + ka * NP;
-#pragma unroll
-    for (int i = 0; i < NPER; ++i) {
-      if constexpr (TN >= 64) {
-        const int ab = sub + NSUB * i;
-        e[i] = ab < NP ? ldc(pa + ab) : 0;
-      } else {
-        static_assert(TN == 32, "tile width 32, 64 or 128");
-        const int ab0 = 2 * wave_u + NSUB * i;
-        const int32_t e0 = ab0 < NP ? ldc(pa + ab0) : 0;
-        const int32_t e1 = ab0 + 1 < NP ? ldc(pa + ab0 + 1) : 0;
-        e[i] = lane < 32 ? e0 : e1;
-      }
+  const int lane = threadIdx.x & 63, li = lane & 15, lk = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  const int sw = wave / WPS, wi = wave % WPS;  // string of this wave, wave of the string
+  const int ts = (int)threadIdx.x - sw * TPS;
+  double* __restrict__ E = Es + sw * ELDS;
+  if (ts == 0) E[T::RP * S] = 0.0;  // where filled-up entries point
+  auto sync = [&]() {
+    if constexpr (WPS > 1) {
+      __syncthreads();
+    } else {  // the string belongs to this wave: LDS is in order within it
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+      __builtin_amdgcn_wave_barrier();
     }
   };
-  auto load_values = [&](int ka) {
-    if constexpr (EREG) {
-      sga = 0;
-      nza = 0;
-    }
+  // link entries of this thread's beta strings
+  constexpr int G0 = T::gpairs(0), G1 = T::P > 1 ? T::gpairs(1) : 0;
+  uint32_t gl0[JPT][G0], gl1[JPT][G1 > 0 ? G1 : 1];
+  const int n0 = string_gpairs(NACT, I.nb, 0), n1 = T::P > 1 ? string_gpairs(NACT, I.nb, 1) : 0;
 #pragma unroll
-    for (int i = 0; i < NPER; ++i) {
-      ga[i] = ea[i] ? ldg(ca + ((ea[i] >> 1) - 1) * Nb) : 0.0;
-      if constexpr (EREG) {
-        sga |= (uint32_t)(ea[i] & 1) << i;
-        nza |= (uint32_t)(ea[i] != 0) << i;
-      }
-    }
+  for (int j = 0; j < JPT; ++j) {
+    const int kb = min(ts + j * TPS, Nb - 1);
 #pragma unroll
-    for (int j = 0; j < CPT; ++j) {
-      const int x = t + NT * j;
-      cr[j] = x < Nb ? ldg(c + ka * Nb + x) : 0.0;
-    }
+    for (int q = 0; q < G0; ++q) gl0[j][q] = q < n0 ? ldg(I.glink + q * Nb + kb) : 0u;
+#pragma unroll
+    for (int q = 0; q < G1; ++q) gl1[j][q] = q < n1 ? ldg(I.glink + (n0 + q) * Nb + kb) : 0u;
+  }
+  const int kslots = string_kslots(NACT, I.na), nks = kslots / 4;
+  const int ncb = (Nb + 15) >> 4;
+  uint32_t e[KS];
+  auto load_links = [&](int ka) {
+#pragma unroll
+    for (int k = 0; k < KS; ++k)
+      if (k < KS0 || k < nks) e[k] = ldg(I.klink + ka * kslots + 4 * k + lk);
   };
-  load_entries(wk.begin - blk * Na, ea);
-  load_values(wk.begin - blk * Na);
+  load_links(min(wk.begin + sw, wk.end - 1));
 
-  for (int tile = wk.begin; tile < wk.end; ++tile) {
-    const int Ka = tile - blk * Na;              // uniform
-    const bool more = tile + 1 < wk.end;
+  for (int s0 = wk.begin; s0 < wk.end; s0 += SPW) {
+    const bool live = s0 + sw < wk.end;
+    const int Ka = live ? s0 + sw : wk.end - 1;
+    uint32_t boff[KS], aoff[KS], sg[KS];  // byte offsets of C row and integral row
 #pragma unroll
-    for (int j = 0; j < CPT; ++j)
-      if (t + NT * j < Nb) Cr[t + NT * j] = cr[j];
-    // the next tile's alpha entries: for the register-entry kernels after the
-    // D+ build (their registers are short), else ahead of it
-    int32_t en[EREG ? 1 : NPER];
-    if constexpr (!EREG) {
-      if (more) {
-        load_entries(Ka + 1, en);
-      } else {
-#pragma unroll
-        for (int i = 0; i < NPER; ++i) en[i] = 0;
+    for (int k = 0; k < KS; ++k)
+      if (k < KS0 || k < nks) {
+        boff[k] = (e[k] & 0x3FFu) * (uint32_t)(8 * Nb);
+        aoff[k] = ((e[k] >> 10) & 0x7FFu) * (uint32_t)(8 * T::KP);
+        sg[k] = e[k];
       }
-    }
-    __syncthreads();
+    if (s0 + SPW < wk.end) load_links(min(s0 + SPW + sw, wk.end - 1));
+    double sum0[JPT], sum1[JPT];
 #pragma unroll
-    for (int i = 0; i < NPER; ++i) {
-      const int ab = sub + NSUB * i;
-      if (ab < NP) {
-        int jb;
-        double fb;
-        if constexpr (EREG) {
-          jb = (jbp[i / 4] >> (8 * (i % 4))) & 0xFF;
-          fb = (nzb >> i & 1) ? ((sgb >> i & 1) ? -keep : keep) : 0.0;
-        } else {
-          const int32_t e = Tb[t + NT * i];
-          jb = e ? (e >> 1) - 1 : 0;
-          fb = e ? ((e & 1) ? -keep : keep) : 0.0;
-        }
-        double fa;
-        if constexpr (EREG) fa = (nza >> i & 1) ? ((sga >> i & 1) ? -keep : keep) : 0.0;
-        else fa = ea[i] ? ((ea[i] & 1) ? -keep : keep) : 0.0;
-        Ds[ab * LDT + col] = fa * ga[i] + fb * Cr[jb];
-      }
-    }
-    __syncthreads();
-    if (more) {
-      if constexpr (EREG) {
-        load_entries(Ka + 1, ea);
-      } else {
+    for (int j = 0; j < JPT; ++j) sum0[j] = sum1[j] = 0.0;
+
+    auto pass = [&](auto pc) {
+      constexpr int p = decltype(pc)::value;
+      constexpr int NG = T::groups(p), NB = NG / 4, NT = NG % 4;  // 16-row blocks, 4-row tails
+      double a[KS][NB > 0 ? 4 * NB : 1], at[KS][NT > 0 ? NT : 1], b[2][KS];
+      auto load_b = [&](int cb, double (&x)[KS]) {
+        const uint32_t col = 8 * (uint32_t)min(cb * 16 + li, Nb - 1);
 #pragma unroll
-        for (int i = 0; i < NPER; ++i) ea[i] = en[i];
-      }
-      load_values(Ka + 1);
-    }
+        for (int k = 0; k < KS; ++k)
+          if (k < KS0 || k < nks) x[k] = ldg_at(c, boff[k] + col);
+      };
+      if (wi < ncb) load_b(wi, b[0]);
 #pragma unroll
-    for (int r = 0; r < RBW; ++r) {
-      const int rb = wrot + NRG * r;
-      if (rb >= NRB) continue;
-      double4_t acc[NCBW];
+      for (int k = 0; k < KS; ++k)
+        if (k < KS0 || k < nks) {
+          const uint32_t w = aoff[k] + 8 * p * T::RP;
 #pragma unroll
-      for (int cb2 = 0; cb2 < NCBW; ++cb2) acc[cb2] = (double4_t){0.0, 0.0, 0.0, 0.0};
-      // B operands double-buffered in registers: the LDS reads of k-step
-      // ks+1 are issued before the MFMAs of k-step ks
-      double bq[2][NCBW];
-      const double* bbase = Ds + (lane >> 4) * LDT + cg * NCBW * 16 + (lane & 15);
-#pragma unroll
-      for (int cb2 = 0; cb2 < NCBW; ++cb2) bq[0][cb2] = bbase[cb2 * 16];
-#pragma unroll
-      for (int ks = 0; ks < KS; ++ks) {
-        if (ks + 1 < KS) {
-#pragma unroll
-          for (int cb2 = 0; cb2 < NCBW; ++cb2)
-            bq[(ks + 1) & 1][cb2] = bbase[(ks + 1) * 4 * LDT + cb2 * 16];
-        }
-#pragma unroll
-        for (int cb2 = 0; cb2 < NCBW; ++cb2)
-          acc[cb2] = __builtin_amdgcn_mfma_f64_16x16x4f64(wreg[r][ks], bq[ks & 1][cb2], acc[cb2],
-                                                          0, 0, 0);
-      }
-      // instruction order for the scheduler: the first B reads, then per
-      // k-step the next step's B reads (0x100: LDS read) ahead of this
-      // step's MFMAs (0x008)
-      __builtin_amdgcn_sched_group_barrier(0x100, NCBW, 0);
-#pragma unroll
-      for (int ks = 0; ks < KS; ++ks) {
-        if (ks + 1 < KS) __builtin_amdgcn_sched_group_barrier(0x100, NCBW, 0);
-        __builtin_amdgcn_sched_group_barrier(0x008, NCBW, 0);
-      }
-      const int Gs = g_stride(Nb);  // row stride of G
-      double* __restrict__ Grow = G + (int64_t)Ka * NO * Gs;
-#pragma unroll
-      for (int cb2 = 0; cb2 < NCBW; ++cb2) {
-        const int cl = (cg * NCBW + cb2) * 16 + (lane & 15);  // column in the tile
-        const int Kc = Kb0 + cl;
-        // gfx950 FP64 16x16x4 output layout: register v of lane l is row
-        // l/16 + 4v, column l%16 of the 16x16 block
-        if (rb == NRB - 1) {
-          // the last block's rows 16 - NACT + k: the diagonal pairs, summed
-          // into sigma with weights n_k(Ka) + n_k(Kb), lanes l/16 in a fixed order
-          const uint32_t sa = (uint32_t)ldc(I.strA + Ka), sb = occB[cl];
-          double pd = 0.0;
-#pragma unroll
-          for (int v = 0; v < 4; ++v) {
-            const int k = (lane >> 4) + 4 * v - (16 - NACT);
-            if (k >= 0) pd += (double)(((sa >> k) & 1) + ((sb >> k) & 1)) * acc[cb2][v];
+          for (int r = 0; r < NB; ++r) {
+            const double x = flip_sign(ldg_at(W, w + 8 * (16 * r + li)), sg[k]);
+            a[k][4 * r] = x;
+            a[k][4 * r + 1] = rot_blocks<1>(x);
+            a[k][4 * r + 2] = rot_blocks<2>(x);
+            a[k][4 * r + 3] = rot_blocks<3>(x);
           }
-          pd += __shfl_xor(pd, 16, 64);
-          pd += __shfl_xor(pd, 32, 64);
-          if ((lane >> 4) == 0 && Kc < Nb)
-            Sarena[(int64_t)vs * ntot + I.off + (int64_t)Ka * Nb + Kc] = pd;
-        }
-        if (Kc < Gs) {  // the row's padding too (zero: D+ is zero there), whole lines
 #pragma unroll
-          for (int v = 0; v < 4; ++v) {
-            const int row = rb * 16 + (lane >> 4) + 4 * v;
-            if (row < NO) Grow[row * Gs + Kc] = acc[cb2][v];
+          for (int t = 0; t < NT; ++t)
+            at[k][t] = flip_sign(ldg_at(W, w + 8 * (16 * NB + 4 * t + (lane & 3))), sg[k]);
+        }
+      const int blk = (lane >> 2) & 3;
+      auto block = [&](int cb, const double (&x)[KS]) {
+        double acc[NG];
+#pragma unroll
+        for (int g = 0; g < NG; ++g) acc[g] = 0.0;
+#pragma unroll
+        for (int k = 0; k < KS; ++k)
+          if (k < KS0 || k < nks) {
+#pragma unroll
+            for (int g = 0; g < 4 * NB; ++g) acc[g] = mfma4(a[k][g], x[k], acc[g]);
+#pragma unroll
+            for (int t = 0; t < NT; ++t) acc[4 * NB + t] = mfma4(at[k][t], x[k], acc[4 * NB + t]);
           }
+        double* __restrict__ Ec = E + cb * 16 + li;
+#pragma unroll
+        for (int g = 0; g < 4 * NB; ++g)
+          Ec[(16 * (g / 4) + 4 * ((blk - g) & 3) + lk) * S] = acc[g];
+#pragma unroll
+        for (int t = 0; t < NT; ++t) Ec[(16 * NB + 4 * t + lk) * S] = acc[4 * NB + t];
+      };
+      for (int cb = wi; cb < ncb; cb += 2 * WPS) {
+        if (cb + WPS < ncb) load_b(cb + WPS, b[1]);
+        block(cb, b[0]);
+        if (cb + WPS < ncb) {
+          if (cb + 2 * WPS < ncb) load_b(cb + 2 * WPS, b[0]);
+          block(cb + WPS, b[1]);
         }
       }
+      sync();
+#pragma unroll
+      for (int j = 0; j < JPT; ++j) {
+        constexpr int GN = p == 0 ? G0 : G1;
+        const int nq = p == 0 ? n0 : n1;
+#pragma unroll
+        for (int q = 0; q < GN; ++q)
+          if (q < nq) {
+            const uint32_t u = p == 0 ? gl0[j][q] : gl1[j][q];
+            sum0[j] += flip_sign(E[u & 0x7FFFu], u << 16);
+            sum1[j] += flip_sign(E[(u >> 16) & 0x7FFFu], u);
+          }
+      }
+      sync();
+    };
+    pass(std::integral_constant<int, 0>{});
+    if constexpr (T::P > 1) pass(std::integral_constant<int, 1>{});
+    if (live) {
+#pragma unroll
+      for (int j = 0; j < JPT; ++j) {
+        const int kb = ts + j * TPS;
+        if (kb < Nb) out[Ka * Nb + kb] += sum0[j] + sum1[j];
+      }
     }
-    // No barrier here: the next tile's Cr stores follow this tile's second
-    // barrier (every D+ read of Cr is done), and its D+ stores follow the
-    // next first barrier (every MFMA read of Ds is done).
   }
 }
 
-// The contraction for active spaces of more than kFoldMax orbitals: G holds
-// every pair row, [Ka][pair_index][Kb], diagonal pairs included, and the
-// gather adds all links.  Their workgroups (512 and 1024 threads) have no
-// register room for the diagonal epilogue of k_sigma_dgemm (measured: 3
-// instead of 4 waves per SIMD at 11-12 orbitals, spills at 14), so they keep
-// this layout.  Same tiles, D+ build and MFMA order as k_sigma_dgemm.
+// Above kStringMax orbitals: contraction G = W D+ over all pairs.  A tile is
+// one alpha string Ka and TN consecutive beta strings; a workgroup keeps one
+// beta block (TN strings) and walks down a range of alpha strings (tiles are
+// numbered column-major: tile = block * Na + Ka).  A thread builds the same
+// (pair, column) slots of D+ in every tile; their beta pair-table entries are
+// loaded once per work unit into LDS.  Per tile the c row of Ka is staged in
+// LDS.  The alpha half of a D+ entry is wave-uniform: a scalar pair-table load
+// and a coalesced row segment of c.  D+ [pair][TN] (B operand) is staged in
+// LDS, the wave's W rows (A operand) sit in registers.  G is stored
+// [Ka][pair_index][Kb], rows g_stride(Nb) long; the gather adds all links.
+// Workgroups of 512 threads (two waves per SIMD) for 11-12 orbitals, 1024
+// (four per SIMD) for 13-14, since their LDS holds one or two workgroups per
+// CU; with 1024 the waves split a tile's output blocks by row block and column
+// half.
+constexpr int dgemm_threads(int nact) { return nact >= 13 ? 1024 : 512; }
+
 template <int NACT, int TN, int NT = dgemm_threads(NACT)>
-__global__ void __launch_bounds__(NT, dgemm_reg_entries(NACT, TN, NT) ? 4 : 1) k_sigma_dgemm_pairrows(
+__global__ void __launch_bounds__(NT) k_sigma_dgemm_pairrows(
     const Item* __restrict__ items, const Work* __restrict__ work,
     const double* __restrict__ warena, const double* __restrict__ V, int64_t ntot,
     double* __restrict__ Garena, const DavState* __restrict__ st, int slot) {
@@ -756,9 +988,8 @@ __global__ void __launch_bounds__(NT, dgemm_reg_entries(NACT, TN, NT) ? 4 : 1) k
   constexpr int CMAX = (int)binom_c(NACT, NACT / 2);  // largest string count for NACT
   constexpr int CPT = (CMAX + NT - 1) / NT;           // c-row doubles per thread
   constexpr int TPT = (NP * TN + NT - 1) / NT;        // beta-table entries per thread
-  constexpr bool EREG = dgemm_reg_entries(NACT, TN, NT);  // the launch-bounds rule
   __shared__ double Ds[KR * LDT];
-  __shared__ int32_t Tb[EREG ? 1 : NP * TN];
+  __shared__ int32_t Tb[NP * TN];
   __shared__ double Cr[CMAX];
 
   const Work wk = work[blockIdx.x];
@@ -805,16 +1036,10 @@ __global__ void __launch_bounds__(NT, dgemm_reg_entries(NACT, TN, NT) ? 4 : 1) k
   // column col (x = t + NT i has x / TN = sub + NSUB i and x % TN = col),
   // the slots it writes in every tile's D+.  Then the zero padding rows of D+.
   static_assert(TPT == NPER, "one pair-table entry per D+ slot of a thread");
-  int32_t eb[NPER];
 #pragma unroll
   for (int i = 0; i < NPER; ++i) {
     const int ab = sub + NSUB * i;
-    eb[i] = ab < NP ? ldg(pB + ab * Nb + Kbc) : 0;
-  }
-  if constexpr (!EREG) {
-#pragma unroll
-    for (int i = 0; i < NPER; ++i)
-      if (sub + NSUB * i < NP) Tb[t + NT * i] = eb[i];
+    if (ab < NP) Tb[t + NT * i] = ldg(pB + ab * Nb + Kbc);
   }
   for (int x = NP * LDT + t; x < KR * LDT; x += NT) Ds[x] = 0.0;
 
@@ -873,9 +1098,7 @@ __global__ void __launch_bounds__(NT, dgemm_reg_entries(NACT, TN, NT) ? 4 : 1) k
     for (int i = 0; i < NPER; ++i) {
       const int ab = sub + NSUB * i;
       if (ab < NP) {
-        int32_t e;
-        if constexpr (EREG) e = eb[i];
-        else e = Tb[t + NT * i];
+        const int32_t e = Tb[t + NT * i];
         const int jb = e ? (e >> 1) - 1 : 0;
         const double fa = ea[i] ? ((ea[i] & 1) ? -keep : keep) : 0.0;
         const double fb = e ? ((e & 1) ? -keep : keep) : 0.0;
@@ -947,217 +1170,7 @@ __global__ void __launch_bounds__(NT, dgemm_reg_entries(NACT, TN, NT) ? 4 : 1) k
   }
 }
 
-// The same contraction on flattened tiles, for active spaces of at most 9
-// orbitals (short beta strings, where a tile of one alpha string leaves the
-// last beta block mostly empty): a tile is TN consecutive determinants
-// K = Ka Nb + Kb of one item and may cross alpha strings, so only an item's
-// last tile is ragged.  The whole beta pair table of the item is staged in LDS
-// once per work unit, and per tile the c rows it spans (a contiguous stretch of
-// c); the alpha pair entries and the alpha-half c values are per-lane loads,
-// fetched one tile ahead.  D+ and the MFMA contraction are formed from
-// the same operands in the same order as in k_sigma_dgemm, so G is identical.
-// Work units hold ranges of flat tile numbers of one item.
-template <int NACT, int TN>
-__global__ void __launch_bounds__(256) k_sigma_dgemm_flat(const Item* __restrict__ items,
-                                                          const Work* __restrict__ work,
-                                                          const double* __restrict__ warena,
-                                                          const double* __restrict__ V,
-                                                          int64_t ntot,
-                                                          double* __restrict__ Garena,
-                                                          double* __restrict__ Sarena,
-                                                          const DavState* __restrict__ st,
-                                                          int slot) {
-  static_assert(NACT <= 9, "flattened tiles stage the whole beta pair table");
-  constexpr int NP = NACT * (NACT + 1) / 2;
-  constexpr int KPAD = (NP + 15) / 16 * 16;
-  constexpr int KS = (NP + 3) / 4;
-  constexpr int KR = KS * 4;
-  constexpr int NRB = KPAD / 16;
-  constexpr int RBW = (NRB + 3) / 4;
-  constexpr int NCB = TN / 16;
-  constexpr int NSUB = 256 / TN;
-  constexpr int NPER = (NP + NSUB - 1) / NSUB;
-  constexpr int LDT = TN + 1;
-  constexpr int CMAX = (int)binom_c(NACT, NACT / 2);
-  constexpr int CRMAX = TN + 2 * CMAX;                 // c rows a tile can touch
-  constexpr int CPT = (CRMAX + 255) / 256;
-  constexpr int NO = NP - NACT;  // off-diagonal pairs: the rows of G
-  static_assert(NACT <= kFoldMax, "flattened tiles sum the diagonal part themselves");
-  __shared__ double Ds[KR * LDT];
-  __shared__ int32_t Tb[NP * CMAX];  // beta pair table [pair][Kb]
-  __shared__ double Cr[CRMAX];       // c rows Ka_lo .. Ka_hi of the tile
-
-  const Work wk = work[blockIdx.x];
-  const Item& I = items[wk.item];
-  const DavState& S = st[wk.item];
-  if (!item_active(S, slot)) return;
-  const int vs = vec_slot(S, slot);
-  const double* __restrict__ c = V + (int64_t)vs * ntot + I.off;
-  double* __restrict__ G = Garena + I.goff;
-  const int Nb = I.Nb;
-  const int nd = (int)I.ndet;
-  const int32_t* __restrict__ pA = I.pairA;
-  const int32_t* __restrict__ pB = I.pairB;
-
-  const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
-  const int col = t % TN;
-  const int sub = (TN >= 64) ? __builtin_amdgcn_readfirstlane(t / TN) : t / TN;
-  const int wrot = (wave + (int)blockIdx.x) & 3;
-  double wreg[RBW][KS];
-  const double* __restrict__ W = warena + I.woff;
-#pragma unroll
-  for (int r = 0; r < RBW; ++r) {
-    const int rb = wrot + 4 * r;
-    const int wr = rb < NRB ? out_row_pair(rb * 16 + (lane & 15), NACT, KPAD) : -1;
-#pragma unroll
-    for (int ks = 0; ks < KS; ++ks)
-      wreg[r][ks] = wr >= 0 ? ldg(W + wr * KPAD + ks * 4 + (lane >> 4)) : 0.0;
-  }
-  for (int x = t; x < NP * Nb; x += 256) Tb[x] = ldg(pB + x);
-  for (int x = NP * LDT + t; x < KR * LDT; x += 256) Ds[x] = 0.0;
-  __syncthreads();
-
-  // column position of this thread in a tile (past the item's end: the last
-  // determinant, with weight zero)
-  auto colpos = [&](int tile, int& ka, int& kb, double& kp) {
-    int k = tile * TN + col;
-    kp = k < nd ? 1.0 : 0.0;
-    if (k >= nd) k = nd - 1;
-    ka = k / Nb;
-    kb = k - ka * Nb;
-  };
-  // first alpha string of a tile (its c rows are staged from there)
-  auto row_lo = [&](int tile) { return (tile * TN) / Nb; };
-  int32_t ea[NPER];  // alpha pair-table entries of the tile
-  double ga[NPER];   // the c values they address (alpha half of D+)
-  double cr[CPT];    // this thread's share of the tile's c rows
-  auto load_entries = [&](int ka, int32_t (&xa)[NPER]) {
-#pragma unroll
-    for (int i = 0; i < NPER; ++i) {
-      const int ab = sub + NSUB * i;
-      xa[i] = ab < NP ? ldg(pA + ka * NP + ab) : 0;
-    }
-  };
-  auto load_values = [&](int tile, int kb) {
-#pragma unroll
-    for (int i = 0; i < NPER; ++i) ga[i] = ea[i] ? ldg(c + ((ea[i] >> 1) - 1) * Nb + kb) : 0.0;
-    const int lo = row_lo(tile) * Nb;
-#pragma unroll
-    for (int j = 0; j < CPT; ++j) {
-      const int x = lo + t + 256 * j;
-      cr[j] = (t + 256 * j < CRMAX && x < nd) ? ldg(c + x) : 0.0;
-    }
-  };
-  int ka, kb;
-  double keep;
-  colpos(wk.begin, ka, kb, keep);
-  load_entries(ka, ea);
-  load_values(wk.begin, kb);
-
-  for (int tile = wk.begin; tile < wk.end; ++tile) {
-    const bool more = tile + 1 < wk.end;
-    int kan = 0, kbn = 0;
-    double keepn = 0.0;
-    int32_t ean[NPER];
-#pragma unroll
-    for (int j = 0; j < CPT; ++j)
-      if (t + 256 * j < CRMAX) Cr[t + 256 * j] = cr[j];
-    if (more) {
-      colpos(tile + 1, kan, kbn, keepn);
-      load_entries(kan, ean);
-    } else {
-#pragma unroll
-      for (int i = 0; i < NPER; ++i) ean[i] = 0;
-    }
-    __syncthreads();
-    const int crow = (ka - row_lo(tile)) * Nb;  // this column's c row in Cr
-#pragma unroll
-    for (int i = 0; i < NPER; ++i) {
-      const int ab = sub + NSUB * i;
-      if (ab < NP) {
-        const int32_t eb = Tb[ab * Nb + kb];
-        const int jb = eb ? (eb >> 1) - 1 : 0;
-        const double fa = ea[i] ? ((ea[i] & 1) ? -keep : keep) : 0.0;
-        const double fb = eb ? ((eb & 1) ? -keep : keep) : 0.0;
-        Ds[ab * LDT + col] = fa * ga[i] + fb * Cr[crow + jb];
-      }
-    }
-    __syncthreads();
-    if (more) {
-#pragma unroll
-      for (int i = 0; i < NPER; ++i) ea[i] = ean[i];
-      ka = kan;
-      kb = kbn;
-      keep = keepn;
-      load_values(tile + 1, kb);
-    }
-#pragma unroll
-    for (int r = 0; r < RBW; ++r) {
-      const int rb = wrot + 4 * r;
-      if (rb >= NRB) continue;
-      double4_t acc[NCB];
-#pragma unroll
-      for (int cb2 = 0; cb2 < NCB; ++cb2) acc[cb2] = (double4_t){0.0, 0.0, 0.0, 0.0};
-      double bq[2][NCB];
-      const double* bbase = Ds + (lane >> 4) * LDT + (lane & 15);
-#pragma unroll
-      for (int cb2 = 0; cb2 < NCB; ++cb2) bq[0][cb2] = bbase[cb2 * 16];
-#pragma unroll
-      for (int ks = 0; ks < KS; ++ks) {
-        if (ks + 1 < KS) {
-#pragma unroll
-          for (int cb2 = 0; cb2 < NCB; ++cb2)
-            bq[(ks + 1) & 1][cb2] = bbase[(ks + 1) * 4 * LDT + cb2 * 16];
-        }
-#pragma unroll
-        for (int cb2 = 0; cb2 < NCB; ++cb2)
-          acc[cb2] = __builtin_amdgcn_mfma_f64_16x16x4f64(wreg[r][ks], bq[ks & 1][cb2], acc[cb2],
-                                                          0, 0, 0);
-      }
-      __builtin_amdgcn_sched_group_barrier(0x100, NCB, 0);
-#pragma unroll
-      for (int ks = 0; ks < KS; ++ks) {
-        if (ks + 1 < KS) __builtin_amdgcn_sched_group_barrier(0x100, NCB, 0);
-        __builtin_amdgcn_sched_group_barrier(0x008, NCB, 0);
-      }
-#pragma unroll
-      for (int cb2 = 0; cb2 < NCB; ++cb2) {
-        const int Kc = tile * TN + cb2 * 16 + (lane & 15);
-        const int Kq = Kc < nd ? Kc : nd - 1;
-        const int kac = Kq / Nb, kbc = Kq - kac * Nb;
-        if (rb == NRB - 1) {  // the diagonal pairs' part of sigma, as in k_sigma_dgemm
-          const uint32_t sa = (uint32_t)ldg(I.strA + kac), sb = (uint32_t)ldg(I.strB + kbc);
-          double pd = 0.0;
-#pragma unroll
-          for (int v = 0; v < 4; ++v) {
-            const int k = (lane >> 4) + 4 * v - (16 - NACT);
-            if (k >= 0) pd += (double)(((sa >> k) & 1) + ((sb >> k) & 1)) * acc[cb2][v];
-          }
-          pd += __shfl_xor(pd, 16, 64);
-          pd += __shfl_xor(pd, 32, 64);
-          if ((lane >> 4) == 0 && Kc < nd) Sarena[(int64_t)vs * ntot + I.off + Kc] = pd;
-        }
-        if (Kc < nd) {
-          double* __restrict__ Grow = G + (int64_t)kac * NO * g_stride(Nb) + kbc;
-#pragma unroll
-          for (int v = 0; v < 4; ++v) {
-            const int row = rb * 16 + (lane >> 4) + 4 * v;
-            if (row < NO) Grow[row * g_stride(Nb)] = acc[cb2][v];
-          }
-        }
-      }
-    }
-    // No barrier here: the next tile's Cr stores follow this tile's second
-    // barrier (every D+ read of Cr is done), and its D+ stores follow the
-    // next first barrier (every MFMA read of Ds is done).
-  }
-}
-
 // sigma_I = sum_{links (x,y,J,s) of Ia} s G_xy[J, Ib] + sum_{links of Ib} s G_xy[Ia, J].
-// Up to kFoldMax orbitals the contraction wrote the diagonal links' part to
-// sigma beforehand, G holds the off-diagonal rows and this adds the
-// off-diagonal links (their entries carry G's row offdiag_index(x, y));
-// above, it sums every link over G's pair_index rows.
 // One wave per 64-determinant segment of one alpha row (segments are
 // row-aligned), so the alpha string and its links are wave-uniform (scalar
 // loads) and the alpha-part reads of G are coalesced rows.  Work units run
@@ -1184,13 +1197,10 @@ __global__ void __launch_bounds__(256) k_sigma_gather(const Item* __restrict__ i
   const int Gs = g_stride(Nb);  // row stride of G
   const int La = I.La, Lb = I.Lb;
   double acc0 = 0.0, acc1 = 0.0;
-  // up to kFoldMax orbitals the contraction summed the diagonal links' part
-  // and G holds the off-diagonal rows; otherwise G holds every pair row
-  const bool fold = I.n <= kFoldMax;
-  const int np = fold ? I.npair - I.n : I.npair;  // rows of G per alpha string
+  const int np = I.npair;  // rows of G per alpha string
   const uint32_t* __restrict__ la = I.linkA + Ka * La;
   const double* __restrict__ Gcol = G + Kb;  // G[(Ja * npair + pair) * Gs + Kb]
-  int l = fold ? I.na : 0;  // the first na links are the diagonal ones
+  int l = 0;
   for (; l + 3 < La; l += 4) {
     const uint32_t e0 = ldc(la + l), e1 = ldc(la + l + 1), e2 = ldc(la + l + 2), e3 = ldc(la + l + 3);
     const double g0 = ldg(Gcol + (int64_t)(link_addr(e0) * np + link_pair(e0)) * Gs);
@@ -1204,11 +1214,10 @@ __global__ void __launch_bounds__(256) k_sigma_gather(const Item* __restrict__ i
     const uint32_t e0 = ldc(la + l);
     acc0 += link_sign(e0) * ldg(Gcol + (int64_t)(link_addr(e0) * np + link_pair(e0)) * Gs);
   }
-  const int Lo = fold ? Lb - I.nb : Lb;  // the links held in linkBT
   const uint32_t* __restrict__ lb = I.linkBT + Kb;               // link l of Kb: lb[l * Nb]
   const double* __restrict__ Grow = G + (int64_t)Ka * np * Gs;  // G[(Ka * npair + pair) * Gs + Jb]
   l = 0;
-  for (; l + 3 < Lo; l += 4) {
+  for (; l + 3 < Lb; l += 4) {
     const uint32_t e0 = ldg(lb + l * Nb), e1 = ldg(lb + (l + 1) * Nb), e2 = ldg(lb + (l + 2) * Nb),
                    e3 = ldg(lb + (l + 3) * Nb);
     const double g0 = ldg(Grow + link_pair(e0) * Gs + link_addr(e0));
@@ -1218,13 +1227,11 @@ __global__ void __launch_bounds__(256) k_sigma_gather(const Item* __restrict__ i
     acc0 += link_sign(e0) * g0 + link_sign(e2) * g2;
     acc1 += link_sign(e1) * g1 + link_sign(e3) * g3;
   }
-  for (; l < Lo; ++l) {
+  for (; l < Lb; ++l) {
     const uint32_t e0 = ldg(lb + l * Nb);
     acc0 += link_sign(e0) * ldg(Grow + link_pair(e0) * Gs + link_addr(e0));
   }
-  double* __restrict__ out = Sarena + (int64_t)vs * ntot + I.off + (int64_t)Ka * Nb + Kb;
-  if (fold) *out += acc0 + acc1;
-  else *out = acc0 + acc1;
+  Sarena[(int64_t)vs * ntot + I.off + (int64_t)Ka * Nb + Kb] = acc0 + acc1;
 }
 
 // ------------------------------------------------------ input validation
@@ -2487,57 +2494,6 @@ __global__ void __launch_bounds__(256) k_pspace_select(const Item* __restrict__ 
   }
 }
 
-// Matrix element <I|H - E_core|J> between two different determinants of the
-// active space (Slater-Condon rules; strings are bit masks over the active
-// orbitals, alpha string before beta string, each in ascending order).
-__device__ inline int between_parity(uint64_t s, int p, int q) {
-  const int lo = p < q ? p : q, hi = p < q ? q : p;
-  const uint64_t m = (((uint64_t)1 << hi) - 1) & ~((((uint64_t)1 << lo) << 1) - 1);
-  return __builtin_popcountll(s & m) & 1;
-}
-__device__ double sc_offdiag(const ItemHam& H, uint64_t ia, uint64_t ib, uint64_t ja,
-                             uint64_t jb) {
-  const uint64_t xa = ia ^ ja, xb = ib ^ jb;
-  const int da = __builtin_popcountll(xa) >> 1, db = __builtin_popcountll(xb) >> 1;
-  if (da + db > 2) return 0.0;
-  const double* __restrict__ eri = H.eri;
-  const int M = H.M;
-  auto g = [&](int p, int q, int r, int s) -> double {
-    return ldg(eri + (((int64_t)H.act[p] * M + H.act[q]) * M + H.act[r]) * M + H.act[s]);
-  };
-  if (da + db == 1) {
-    // one excitation q -> p in the string of spin sigma
-    const uint64_t is = da ? ia : ib, js = da ? ja : jb, jo = da ? jb : ja;
-    const int p = __builtin_ctzll(is & ~js), q = __builtin_ctzll(js & ~is);
-    double v = H.heff[p * kMaxActive + q];
-    for (uint64_t x = js; x; x &= x - 1) {
-      const int r = __builtin_ctzll(x);
-      v += g(p, q, r, r) - g(p, r, r, q);   // r = q contributes zero
-    }
-    for (uint64_t x = jo; x; x &= x - 1) {
-      const int r = __builtin_ctzll(x);
-      v += g(p, q, r, r);
-    }
-    return between_parity(js, p, q) ? -v : v;
-  }
-  if (da == 1 && db == 1) {
-    const int p = __builtin_ctzll(ia & ~ja), q = __builtin_ctzll(ja & ~ia);
-    const int r = __builtin_ctzll(ib & ~jb), s = __builtin_ctzll(jb & ~ib);
-    const double v = g(p, q, r, s);
-    return (between_parity(ja, p, q) ^ between_parity(jb, r, s)) ? -v : v;
-  }
-  // two excitations in one string: holes q1 < q2, particles p1 < p2;
-  // I = E_p1q1 E_p2q2 J (up to the sign), element (p1 q1|p2 q2) - (p1 q2|p2 q1)
-  const uint64_t is = da ? ia : ib, js = da ? ja : jb;
-  uint64_t pp = is & ~js, hh = js & ~is;
-  const int p1 = __builtin_ctzll(pp), p2 = 63 - __builtin_clzll(pp);
-  const int q1 = __builtin_ctzll(hh), q2 = 63 - __builtin_clzll(hh);
-  const uint64_t k = (js & ~((uint64_t)1 << q2)) | ((uint64_t)1 << p2);
-  const int par = between_parity(js, p2, q2) ^ between_parity(k, p1, q1);
-  const double v = g(p1, q1, p2, q2) - g(p1, q2, p2, q1);
-  return par ? -v : v;
-}
-
 // One block per item: build H_PP (packed lower triangle in LDS) and reduce
 // it to tridiagonal form by Householder reflections, H_PP = Q T Q^T (T:
 // diagonal d, off-diagonal e; Q accumulated explicitly for a P-space).
@@ -3643,7 +3599,7 @@ __global__ void k_mbe_setup_list(MbeSpaces sp, const uint64_t* __restrict__ mask
   __syncthreads();
   const Item& I = items[it];
   build_item_hamiltonian(s, sp.M, h1, eri, e_const, I.na + I.nb, &hams[I.ham],
-                         I.ndet > 1 ? warena + I.woff : nullptr, I.kpad);
+                         pair_matrix(I) ? warena + I.woff : nullptr, I.kpad);
 }
 
 // Computed tuples of the lower orders, each order's masks in ascending
@@ -3742,57 +3698,83 @@ void launch_hdiag(const Item* items, const Work* work, int nwork, const ItemHam*
     hipLaunchKernelGGL(k_hdiag, dim3(nwork), dim3(256), 0, s, items, work, hams, diag);
 }
 
-template <int NACT, int TN>
-static void sigma_dgemm_t(const Item* items, const Work* work, int nwork, const double* warena,
-                          const double* V, int64_t ntot, double* G, double* Sv,
-                          const DavState* st, int slot, hipStream_t s) {
-  if constexpr (NACT > kFoldMax)
-    hipLaunchKernelGGL((k_sigma_dgemm_pairrows<NACT, TN>), dim3(nwork), dim3(dgemm_threads(NACT)),
-                       0, s, items, work, warena, V, ntot, G, st, slot);
+void launch_string_links(int n, int ne, int64_t N, uint32_t* alpha, uint32_t* beta,
+                         hipStream_t s) {
+  if (N > 0)
+    hipLaunchKernelGGL(k_string_links, dim3(nblk(N, 64)), dim3(64), 0, s, n, ne, N, alpha, beta);
+}
+void launch_sigma_operands(const Item* items, int nitem, int64_t most, const ItemHam* hams,
+                           double* warena, hipStream_t s) {
+  // two elements per thread of the largest CASCI
+  const int y = (int)(most <= 512 ? 1 : most >= 512 * 256 ? 256 : (most + 511) / 512);
+  if (nitem > 0 && most > 0)
+    hipLaunchKernelGGL(k_sigma_operands, dim3(nitem, y), dim3(256), 0, s, items, hams, warena);
+}
+void launch_sigma_same_spin(const Item* items, const Work* work, int nwork, bool small,
+                            const double* warena, const double* V, int64_t ntot, double* Sv,
+                            const DavState* st, int slot, hipStream_t s) {
+  if (nwork <= 0) return;
+  if (small)
+    hipLaunchKernelGGL((k_sigma_same_spin<1, 1>), dim3(nblk(nwork, 4)), dim3(256), 0, s, items,
+                       work, nwork, warena, V, ntot, Sv, st, slot);
   else
-    hipLaunchKernelGGL((k_sigma_dgemm<NACT, TN>), dim3(nwork), dim3(dgemm_threads(NACT)), 0, s,
-                       items, work, warena, V, ntot, G, Sv, st, slot);
+    hipLaunchKernelGGL((k_sigma_same_spin<2, 4>), dim3(nblk(nwork, 4)), dim3(256), 0, s, items,
+                       work, nwork, warena, V, ntot, Sv, st, slot);
 }
 
-template <int TN>
-static bool sigma_dgemm_n(int n, const Item* items, const Work* work, int nwork,
-                          const double* warena, const double* V, int64_t ntot, double* G,
-                          double* Sv, const DavState* st, int slot, hipStream_t s) {
-  switch (n) {
-#define MBEFCI_CASE(N) \
-  case N: sigma_dgemm_t<N, TN>(items, work, nwork, warena, V, ntot, G, Sv, st, slot, s); return true;
-    MBEFCI_CASE(2) MBEFCI_CASE(3) MBEFCI_CASE(4) MBEFCI_CASE(5) MBEFCI_CASE(6) MBEFCI_CASE(7)
-    MBEFCI_CASE(10) MBEFCI_CASE(11) MBEFCI_CASE(12)
-#undef MBEFCI_CASE
-    case 8:  // three-wave workgroups: up to 64 columns
-      if constexpr (TN <= 64) { sigma_dgemm_t<8, TN>(items, work, nwork, warena, V, ntot, G, Sv, st, slot, s); return true; }
-      return false;
-    case 9:
-      if constexpr (TN <= 64) { sigma_dgemm_t<9, TN>(items, work, nwork, warena, V, ntot, G, Sv, st, slot, s); return true; }
-      return false;
-    case 13:
-      if constexpr (TN <= 64) { sigma_dgemm_t<13, TN>(items, work, nwork, warena, V, ntot, G, Sv, st, slot, s); return true; }
-      return false;
-    case 14:
-      if constexpr (TN <= 64) { sigma_dgemm_t<14, TN>(items, work, nwork, warena, V, ntot, G, Sv, st, slot, s); return true; }
-      return false;
-    default: return false;
+template <int NACT, int TN>
+static bool sigma_string_t(const Item* items, const Work* work, int nwork, const double* warena,
+                           const double* V, int64_t ntot, double* Sv, const DavState* st, int slot,
+                           hipStream_t s) {
+  if constexpr (TN == 128 && (NACT == 8 || NACT == 9)) {
+    return false;  // not compiled
+  } else {
+    constexpr int WPS = string_wps(NACT, TN), SPW = string_spw(NACT, TN);
+    hipLaunchKernelGGL((k_sigma_dgemm<NACT, WPS, SPW>), dim3(nwork), dim3(64 * WPS * SPW), 0, s,
+                       items, work, warena, V, ntot, Sv, st, slot);
+    return true;
   }
 }
-
-template <int TN>
-static bool sigma_dgemm_flat_n(int n, const Item* items, const Work* work, int nwork,
-                               const double* warena, const double* V, int64_t ntot, double* G,
-                               double* Sv, const DavState* st, int slot, hipStream_t s) {
-  switch (n) {
-#define MBEFCI_CASE(N)                                                                       \
-  case N:                                                                                    \
-    hipLaunchKernelGGL((k_sigma_dgemm_flat<N, TN>), dim3(nwork), dim3(256), 0, s, items,     \
-                       work, warena, V, ntot, G, Sv, st, slot);                              \
-    return true;
-    MBEFCI_CASE(2) MBEFCI_CASE(3) MBEFCI_CASE(4) MBEFCI_CASE(5) MBEFCI_CASE(6) MBEFCI_CASE(7)
-    MBEFCI_CASE(8) MBEFCI_CASE(9)
+template <int NACT>
+static bool sigma_string_n(int tn, const Item* items, const Work* work, int nwork,
+                           const double* warena, const double* V, int64_t ntot, double* Sv,
+                           const DavState* st, int slot, hipStream_t s) {
+  switch (tn) {
+#define MBEFCI_CASE(T) \
+  case T: return sigma_string_t<NACT, T>(items, work, nwork, warena, V, ntot, Sv, st, slot, s);
+    MBEFCI_CASE(32) MBEFCI_CASE(64) MBEFCI_CASE(128)
+    default: break;
+  }
+  if constexpr (NACT <= 9) {
+    switch (tn) {
+      MBEFCI_CASE(-32) MBEFCI_CASE(-64)
+      default: break;
+    }
+  }
 #undef MBEFCI_CASE
+  return false;
+}
+
+template <int NACT, int TN>
+static bool sigma_pairs_t(const Item* items, const Work* work, int nwork, const double* warena,
+                          const double* V, int64_t ntot, double* G, const DavState* st, int slot,
+                          hipStream_t s) {
+  if constexpr (TN == 128 && NACT >= 13) {
+    return false;  // more LDS than a CU holds
+  } else {
+    hipLaunchKernelGGL((k_sigma_dgemm_pairrows<NACT, TN>), dim3(nwork), dim3(dgemm_threads(NACT)),
+                       0, s, items, work, warena, V, ntot, G, st, slot);
+    return true;
+  }
+}
+template <int NACT>
+static bool sigma_pairs_n(int tn, const Item* items, const Work* work, int nwork,
+                          const double* warena, const double* V, int64_t ntot, double* G,
+                          const DavState* st, int slot, hipStream_t s) {
+  switch (tn) {
+    case 32: return sigma_pairs_t<NACT, 32>(items, work, nwork, warena, V, ntot, G, st, slot, s);
+    case 64: return sigma_pairs_t<NACT, 64>(items, work, nwork, warena, V, ntot, G, st, slot, s);
+    case 128: return sigma_pairs_t<NACT, 128>(items, work, nwork, warena, V, ntot, G, st, slot, s);
     default: return false;
   }
 }
@@ -3801,16 +3783,16 @@ bool launch_sigma_dgemm(int n, int tn, const Item* items, const Work* work, int 
                         const double* warena, const double* V, int64_t ntot, double* G,
                         double* Sv, const DavState* st, int slot, hipStream_t s) {
   if (nwork <= 0) return true;
-  switch (tn) {
-    case -32: return sigma_dgemm_flat_n<32>(n, items, work, nwork, warena, V, ntot, G, Sv, st, slot, s);
-    case -64: return sigma_dgemm_flat_n<64>(n, items, work, nwork, warena, V, ntot, G, Sv, st, slot, s);
-    case 32: return sigma_dgemm_n<32>(n, items, work, nwork, warena, V, ntot, G, Sv, st, slot, s);
-    case 64: return sigma_dgemm_n<64>(n, items, work, nwork, warena, V, ntot, G, Sv, st, slot, s);
-    case 128:
-      // not compiled for n >= 13 (more LDS than one CU holds) nor for the
-      // three-wave workgroups of n = 8, 9: the work units must not be built
-      // for it (the caller maps such a schedule to 64 columns)
-      return sigma_dgemm_n<128>(n, items, work, nwork, warena, V, ntot, G, Sv, st, slot, s);
+  switch (n) {
+#define MBEFCI_CASE(N) \
+  case N: return sigma_string_n<N>(tn, items, work, nwork, warena, V, ntot, Sv, st, slot, s);
+    MBEFCI_CASE(2) MBEFCI_CASE(3) MBEFCI_CASE(4) MBEFCI_CASE(5) MBEFCI_CASE(6) MBEFCI_CASE(7)
+    MBEFCI_CASE(8) MBEFCI_CASE(9) MBEFCI_CASE(10)
+#undef MBEFCI_CASE
+#define MBEFCI_CASE(N) \
+  case N: return sigma_pairs_n<N>(tn, items, work, nwork, warena, V, ntot, G, st, slot, s);
+    MBEFCI_CASE(11) MBEFCI_CASE(12) MBEFCI_CASE(13) MBEFCI_CASE(14)
+#undef MBEFCI_CASE
     default: return false;
   }
 }

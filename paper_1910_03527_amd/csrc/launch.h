@@ -12,6 +12,20 @@ void launch_strings(int n, int ne, int64_t N, uint64_t* out, hipStream_t s);
 void launch_links(int n, int ne, int64_t N, uint32_t* packed, uint32_t* packedT, int32_t* abi4,
                   hipStream_t s);
 void launch_pair_table(int n, int ne, int64_t N, int32_t* out, int32_t* outT, hipStream_t s);
+void launch_string_links(int n, int ne, int64_t N, uint32_t* alpha, uint32_t* beta, hipStream_t s);
+// doubles of a CASCI's sigma operands (k_sigma_operands), n <= kStringMax
+inline int64_t sigma_operand_size(int n, int64_t Na, int64_t Nb, bool same) {
+  const int64_t pa = (Na + 15) & ~(int64_t)15, pb = (Nb + 15) & ~(int64_t)15;
+  return (n * (n - 1) / 2 + Na + 1) * string_kp(n) + pa * pa + (same ? 0 : pb * pb);
+}
+// most: the largest sigma_operand_size of the items
+void launch_sigma_operands(const Item* items, int nitem, int64_t most, const ItemHam* hams,
+                           double* warena, hipStream_t s);
+// Same-spin part of sigma; work units are wave tiles (alpha tile begin, beta
+// tile end) of 32 x 64 strings, or of 16 x 16 where `small`.
+void launch_sigma_same_spin(const Item* items, const Work* work, int nwork, bool small,
+                            const double* warena, const double* V, int64_t ntot, double* Sv,
+                            const DavState* st, int slot, hipStream_t s);
 void launch_mbe_setup(const MbeSpaces* sp, const BucketDev* buckets, int nbucket, const Item* items,
                       int nitem, const double* h1, const double* eri, double e_const,
                       ItemHam* hams, double* warena, int32_t* tuple_pos, int max_order,
@@ -21,11 +35,20 @@ void launch_casci_setup(int n, const double* const* h1s, const double* const* er
                         double* warena, hipStream_t s);
 void launch_hdiag(const Item* items, const Work* work, int nwork, const ItemHam* hams,
                   double* diag, hipStream_t s);
-// tn: 32, 64 or 128 columns of one alpha string per tile; -32 or -64: flattened
-// tiles of that many consecutive determinants (active spaces of at most 9).
-// Up to kFoldMax orbitals it also writes the diagonal pairs' part of sigma to
-// Sv (the slot of the vector it reads from V), to which launch_sigma_gather
-// then adds the off-diagonal links.
+// Above kStringMax orbitals: G = W D+, tn columns of one alpha string per tile
+// (work units: tile ranges).  Up to kStringMax: the opposite-spin part of
+// sigma, added to the same-spin part (work units: alpha string ranges); |tn| /
+// 16 waves per workgroup, which share an alpha string as far as it has column
+// blocks (tn > 0) or take one string each (tn < 0, at most 9 orbitals).
+// waves that share an alpha string (a power of two, at most its column blocks)
+// and alpha strings a workgroup takes at a time, n <= kStringMax
+__host__ __device__ constexpr int string_wps(int n, int tn) {
+  const int cb = (string_binom(n, n / 2) + 15) / 16, most = cb > 4 ? 8 : cb > 2 ? 4 : cb;
+  return tn < 0 ? 1 : tn / 16 < most ? tn / 16 : most;
+}
+__host__ __device__ constexpr int string_spw(int n, int tn) {
+  return (tn < 0 ? -tn : tn) / 16 / string_wps(n, tn);
+}
 bool launch_sigma_dgemm(int n, int tn, const Item* items, const Work* work, int nwork,
                         const double* warena, const double* V, int64_t ntot, double* G,
                         double* Sv, const DavState* st, int slot, hipStream_t s);
@@ -40,7 +63,7 @@ void launch_sigma_gather(const Item* items, const Work* work, int nwork, const d
 // Measured (eight workgroups per CU uncapped): blocks of 112 KB (10
 // orbitals) do best at six per CU, blocks of 1 MB and more (13-14
 // orbitals) at four; blocks below 64 KB (9 orbitals and fewer) are not
-// capped.  (Sized by all npair rows; up to 10 orbitals G holds npair - n.)
+// capped.
 inline int gather_lds_bytes(int64_t row_block) {
   if (row_block >= ((int64_t)1 << 20)) return 40960;  // four workgroups per CU
   if (row_block >= 64 * 1024) return 26624;           // six

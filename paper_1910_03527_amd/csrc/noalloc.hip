@@ -9,6 +9,9 @@
 // with hipGetSymbolAddress (noalloc_init, called when a context is created,
 // or on the first call on a device) and kept in g_scratch[device].  The
 // kernels are those of mbefci_sigma (kernels.hip); only the storage differs.
+// Up to kStringMax orbitals no G or W is needed, and the sigma operands and
+// link tables take their place (less room: every shape is accepted or
+// refused as if G were there).
 // Calls that overlap on one GPU share the array and race.
 #include <hip/hip_runtime.h>
 
@@ -25,6 +28,7 @@ constexpr size_t kScratchBytes = (size_t)32 << 20;  // 32 MiB per GPU
 constexpr int kNoallocMaxDevices = 64;
 constexpr int kNoallocTile = 32;  // one alpha string x 32 beta strings per tile
 constexpr int kNoallocTpw = 16;   // tiles per workgroup
+constexpr int kNoallocStringTile = 64;  // four waves per workgroup up to kStringMax orbitals
 
 static __device__ __align__(256) unsigned char scratch[kScratchBytes];
 
@@ -44,11 +48,12 @@ int64_t binom(int n, int k) {
 struct Layout {
   size_t item, ham, st, hptr, gptr, ecore, tiles, segs, block, diag;
   size_t strA, strB, linkA, linkAT, linkB, linkBT, pairA, pairAT, pairB, pairBT, W, G;
+  size_t klink, glink, same;  // up to kStringMax orbitals, instead of links, pairs and G
   size_t total;
-  int ntiles, nsegs;
+  int ntiles, nsegs, nsame;
 };
 
-Layout layout(int n, int64_t Na, int64_t Nb, int La, int Lb) {
+Layout layout(int n, int na, int nb, int64_t Na, int64_t Nb, int La, int Lb) {
   Layout L{};
   size_t off = 0;
   auto take = [&](size_t bytes) {
@@ -58,10 +63,19 @@ Layout layout(int n, int64_t Na, int64_t Nb, int La, int Lb) {
   };
   const int64_t npair = (int64_t)n * (n + 1) / 2;
   const int64_t kpad = (npair + 15) / 16 * 16;
+  const bool strings = n <= kStringMax;
   const int64_t nblk = (Nb + kNoallocTile - 1) / kNoallocTile;
-  L.ntiles = (int)(nblk * ((Na + kNoallocTpw - 1) / kNoallocTpw));
   const int64_t nsg = Na * ((Nb + 63) / 64);
-  L.nsegs = (int)((nsg + 3) / 4);
+  if (strings) {  // one step of alpha strings per unit, 16 x 16 same-spin tiles
+    const int spw = string_spw(n, kNoallocStringTile);
+    L.ntiles = (int)((Na + spw - 1) / spw);
+    L.nsegs = 0;
+    L.nsame = (int)(((Na + 15) / 16) * ((Nb + 15) / 16));
+  } else {
+    L.ntiles = (int)(nblk * ((Na + kNoallocTpw - 1) / kNoallocTpw));
+    L.nsegs = (int)((nsg + 3) / 4);
+    L.nsame = 0;
+  }
   L.item = take(sizeof(Item));
   L.ham = take(sizeof(ItemHam));
   L.st = take(sizeof(DavState));
@@ -74,6 +88,14 @@ Layout layout(int n, int64_t Na, int64_t Nb, int La, int Lb) {
   L.diag = take(sizeof(double));
   L.strA = take(sizeof(uint64_t) * Na);
   L.strB = take(sizeof(uint64_t) * Nb);
+  if (strings) {
+    L.klink = take(sizeof(uint32_t) * Na * string_kslots(n, na));
+    L.glink = take(sizeof(uint32_t) * Nb * (string_gpairs(n, nb, 0) + string_gpairs(n, nb, 1)));
+    L.same = take(sizeof(Work) * (size_t)L.nsame);
+    L.W = take(sizeof(double) * (size_t)sigma_operand_size(n, Na, Nb, na == nb));
+    L.total = off;
+    return L;
+  }
   L.linkA = take(sizeof(uint32_t) * Na * La);
   L.linkAT = take(sizeof(uint32_t) * Na * La);
   L.linkB = take(sizeof(uint32_t) * Nb * Lb);
@@ -91,12 +113,14 @@ Layout layout(int n, int64_t Na, int64_t Nb, int La, int Lb) {
 // Writes the CASCI record, the integral pointers, the solver state of a single
 // caller vector in slot 0 and the work lists of the contraction (tiles of
 // kNoallocTile columns, kNoallocTpw alpha strings per unit, never crossing a
-// beta block), the gather (four row-aligned 64-determinant segments per unit)
-// and the diagonal (one 256-determinant block).  One block of 256 threads.
+// beta block; up to kStringMax orbitals one step of alpha strings per unit),
+// the gather (four row-aligned 64-determinant segments per unit) or the
+// same-spin part (16 x 16 tiles) and the diagonal (one 256-determinant block).
+// One block of 256 threads.
 __global__ void k_noalloc_prepare(Item item, Item* items, const double* h1, const double* eri,
                                   double e_core, const double** hptr, const double** gptr,
                                   double* ecore, DavState* st, Work* tiles, int ntiles,
-                                  Work* segs, int nsegs, Work* block) {
+                                  Work* segs, int nsegs, Work* same, int nsame, Work* block) {
   const int t = threadIdx.x;
   if (t == 0) {
     items[0] = item;
@@ -110,6 +134,13 @@ __global__ void k_noalloc_prepare(Item item, Item* items, const double* h1, cons
     block[0] = Work{0, 0, 1, 0};
   }
   const int Na = item.Na, Nb = item.Nb;
+  if (nsame > 0) {
+    const int spw = string_spw(item.n, kNoallocStringTile), cb = (Nb + 15) / 16;
+    for (int w = t; w < ntiles; w += blockDim.x)
+      tiles[w] = Work{0, w * spw, min((w + 1) * spw, Na), 0};
+    for (int w = t; w < nsame; w += blockDim.x) same[w] = Work{0, w / cb, w % cb, 0};
+    return;
+  }
   const int per_blk = (Na + kNoallocTpw - 1) / kNoallocTpw;
   for (int w = t; w < ntiles; w += blockDim.x) {
     const int bk = w / per_blk, a = (w % per_blk) * kNoallocTpw;
@@ -151,7 +182,7 @@ int noalloc_sigma(int device, int n, int na, int nb, const double* h1, const dou
   }
   const int64_t Na = binom(n, na), Nb = binom(n, nb);
   const int La = na * (n - na + 1), Lb = nb * (n - nb + 1);
-  const Layout L = layout(n, Na, Nb, La, Lb);
+  const Layout L = layout(n, na, nb, Na, Nb, La, Lb);
   if (L.total > kScratchBytes) {
     *why = "CASCI (" + std::to_string(n) + "," + std::to_string(na) + "," + std::to_string(nb) +
            ") needs " + std::to_string(L.total) + " bytes of scratch; the no-allocation sigma holds " +
@@ -183,13 +214,19 @@ int noalloc_sigma(int device, int n, int na, int nb, const double* h1, const dou
   I.chunk0 = 0;
   I.nchunk = 0;
   I.shape = 0;
-  I.linkA = (const uint32_t*)at(L.linkA);
-  I.linkB = (const uint32_t*)at(L.linkB);
-  I.linkBT = (const uint32_t*)at(L.linkBT);
+  const bool strings = n <= kStringMax;
   I.strA = (const uint64_t*)at(L.strA);
   I.strB = (const uint64_t*)at(L.strB);
-  I.pairA = (const int32_t*)at(L.pairA);
-  I.pairB = (const int32_t*)at(L.pairBT);
+  if (strings) {
+    I.klink = (const uint32_t*)at(L.klink);
+    I.glink = (const uint32_t*)at(L.glink);
+  } else {
+    I.linkA = (const uint32_t*)at(L.linkA);
+    I.linkB = (const uint32_t*)at(L.linkB);
+    I.linkBT = (const uint32_t*)at(L.linkBT);
+    I.pairA = (const int32_t*)at(L.pairA);
+    I.pairB = (const int32_t*)at(L.pairBT);
+  }
   Item* items = (Item*)at(L.item);
   ItemHam* hams = (ItemHam*)at(L.ham);
   DavState* st = (DavState*)at(L.st);
@@ -199,26 +236,37 @@ int noalloc_sigma(int device, int n, int na, int nb, const double* h1, const dou
   Work* tiles = (Work*)at(L.tiles);
   Work* segs = (Work*)at(L.segs);
   Work* block = (Work*)at(L.block);
+  Work* same = (Work*)at(L.same);
   double* W = (double*)at(L.W);
   double* G = (double*)at(L.G);
   hipLaunchKernelGGL(k_noalloc_prepare, dim3(1), dim3(256), 0, s, I, items, h1, eri, e_core,
-                     hptr, gptr, ecore, st, tiles, L.ntiles, segs, L.nsegs, block);
+                     hptr, gptr, ecore, st, tiles, L.ntiles, segs, L.nsegs, same, L.nsame, block);
   launch_strings(n, na, Na, (uint64_t*)at(L.strA), s);
   launch_strings(n, nb, Nb, (uint64_t*)at(L.strB), s);
-  launch_links(n, na, Na, (uint32_t*)at(L.linkA), (uint32_t*)at(L.linkAT), nullptr, s);
-  launch_links(n, nb, Nb, (uint32_t*)at(L.linkB), (uint32_t*)at(L.linkBT), nullptr, s);
-  launch_pair_table(n, na, Na, (int32_t*)at(L.pairA), (int32_t*)at(L.pairAT), s);
-  launch_pair_table(n, nb, Nb, (int32_t*)at(L.pairB), (int32_t*)at(L.pairBT), s);
+  if (!strings) {
+    launch_links(n, na, Na, (uint32_t*)at(L.linkA), (uint32_t*)at(L.linkAT), nullptr, s);
+    launch_links(n, nb, Nb, (uint32_t*)at(L.linkB), (uint32_t*)at(L.linkBT), nullptr, s);
+    launch_pair_table(n, na, Na, (int32_t*)at(L.pairA), (int32_t*)at(L.pairAT), s);
+    launch_pair_table(n, nb, Nb, (int32_t*)at(L.pairB), (int32_t*)at(L.pairBT), s);
+  } else if (I.ndet > 1) {
+    launch_string_links(n, na, Na, (uint32_t*)at(L.klink), nullptr, s);
+    launch_string_links(n, nb, Nb, nullptr, (uint32_t*)at(L.glink), s);
+  }
   launch_casci_setup(n, hptr, gptr, ecore, items, 1, hams, W, s);
   if (I.ndet > 1) {
     // the caller's vectors stand in for slot 0 of the solver arenas
-    if (!launch_sigma_dgemm(n, kNoallocTile, items, tiles, L.ntiles, W, c, I.ndet, G, sigma, st,
+    if (strings) {
+      launch_sigma_operands(items, 1, sigma_operand_size(n, Na, Nb, na == nb), hams, W, s);
+      launch_sigma_same_spin(items, same, L.nsame, true, W, c, I.ndet, sigma, st, 0, s);
+    }
+    if (!launch_sigma_dgemm(n, strings ? kNoallocStringTile : kNoallocTile, items, tiles, L.ntiles, W, c, I.ndet, G, sigma, st,
                             0, s)) {
       *why = "no sigma kernel for n=" + std::to_string(n);
       return MBEFCI_EUNSUPPORTED;
     }
-    launch_sigma_gather(items, segs, L.nsegs, G, sigma, I.ndet, st, 0,
-                        gather_lds_bytes((int64_t)I.npair * g_stride(I.Nb) * 8), s);
+    if (!strings)
+      launch_sigma_gather(items, segs, L.nsegs, G, sigma, I.ndet, st, 0,
+                          gather_lds_bytes((int64_t)I.npair * g_stride(I.Nb) * 8), s);
     launch_axpy_out(sigma, sigma, c, e_core, I.ndet, s);
   } else {
     double* diag = (double*)at(L.diag);

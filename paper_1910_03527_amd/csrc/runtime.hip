@@ -67,6 +67,8 @@ struct StringTab {
   uint64_t* str = nullptr;
   int32_t* pair = nullptr;
   int32_t* pairT = nullptr;
+  uint32_t* klink = nullptr;  // up to kStringMax orbitals: k_string_links
+  uint32_t* glink = nullptr;
 };
 
 // Tables of a point-group blocked CASCI shape (n, na, nb, the irreps of the
@@ -130,6 +132,12 @@ struct Plan {
   std::vector<int> sym_blk_lo, sym_blk_hi;
   Work* d_sym_blocks = nullptr;
   bool has_sym = false;
+  // same-spin part of the CASCIs of up to kStringMax orbitals: wave tiles
+  std::vector<Work> same;
+  std::vector<int> same_lo, same_hi;
+  Work* d_same = nullptr;
+  bool same_small = false;    // 16 x 16 tiles instead of 32 x 64
+  int64_t operand_most = 0;   // largest sigma_operand_size
   int nitem = 0, nchunk = 0, nblock = 0, nseg = 0;
   int gather_lds = 0;  // LDS reserved per gather workgroup (an occupancy cap), gather_lds_bytes
   int64_t ntot = 0, gtot = 0, wtot = 0;
@@ -290,7 +298,14 @@ const StringTab& string_tab(mbefci_ctx* c, int n, int ne) {
   t.ne = ne;
   t.N = binom_host(n, ne);
   t.L = ne * (n - ne + 1);
-  if (t.N * t.L > 0) {
+  if (n <= kStringMax && n >= 2) {
+    const int64_t ka = t.N * string_kslots(n, ne);
+    const int64_t gb = t.N * (string_gpairs(n, ne, 0) + string_gpairs(n, ne, 1));
+    HIPCHK(hipMalloc(&t.klink, sizeof(uint32_t) * ka));
+    HIPCHK(hipMalloc(&t.glink, sizeof(uint32_t) * std::max<int64_t>(gb, 1)));
+    launch_string_links(n, ne, t.N, t.klink, t.glink, c->stream);
+    HIPCHK(hipGetLastError());
+  } else if (t.N * t.L > 0) {
     HIPCHK(hipMalloc(&t.link, sizeof(uint32_t) * t.N * t.L));
     HIPCHK(hipMalloc(&t.linkT, sizeof(uint32_t) * t.N * t.L));
     launch_links(n, ne, t.N, t.link, t.linkT, nullptr, c->stream);
@@ -555,22 +570,33 @@ void save_tune_cache(mbefci_ctx* c) {
 // Sigma-contraction work units of group gi: tiles (one alpha string x tn beta
 // strings) numbered column-major, tile = block * Na + Ka; a unit covers
 // tiles_per_wg alpha strings of one beta block and never crosses a block.
-// With flattened tiles (tn < 0) tile f holds determinants f|tn| .. f|tn|+|tn|-1
-// of the item and a unit covers tiles_per_wg consecutive tiles.
+// Up to kStringMax orbitals a unit is a range of alpha strings, tiles_per_wg
+// steps of the strings a workgroup takes at a time; fewer steps where the
+// group would give less than kStringUnits units (four per CU).
+constexpr int64_t kStringUnits = 1024;
+void build_string_units(Plan& P, int gi) {
+  Group& g = P.groups[gi];
+  int64_t strings = 0;
+  for (int i = 0; i < P.nitem; ++i)
+    if (P.item_group[i] == gi) strings += P.items[i].Na;
+  const int spw = string_spw(g.n, g.tn);
+  const int64_t most = strings / (spw * kStringUnits);
+  const int len = spw * (int)std::max<int64_t>(1, std::min<int64_t>(g.tiles_per_wg, most));
+  for (int i = 0; i < P.nitem; ++i) {
+    if (P.item_group[i] != gi) continue;
+    g.item_lo[i] = (int)g.tiles.size();
+    for (int a = 0; a < P.items[i].Na; a += len)
+      g.tiles.push_back(Work{i, a, std::min(a + len, P.items[i].Na), 0});
+    g.item_hi[i] = (int)g.tiles.size();
+  }
+}
 void build_tiles(Plan& P, int gi) {
   Group& g = P.groups[gi];
   g.tiles.clear();
+  if (g.n <= kStringMax) return build_string_units(P, gi);
   for (int i = 0; i < P.nitem; ++i) {
     if (P.item_group[i] != gi) continue;
     const Item& I = P.items[i];
-    if (g.tn < 0) {
-      const int nt = (int)((I.ndet - g.tn - 1) / -g.tn);
-      g.item_lo[i] = (int)g.tiles.size();
-      for (int a = 0; a < nt; a += g.tiles_per_wg)
-        g.tiles.push_back(Work{i, a, std::min(a + g.tiles_per_wg, nt), 0});
-      g.item_hi[i] = (int)g.tiles.size();
-      continue;
-    }
     const int nblk = (I.Nb + g.tn - 1) / g.tn;
     g.item_lo[i] = (int)g.tiles.size();
     for (int bk = 0; bk < nblk; ++bk)
@@ -611,8 +637,7 @@ int64_t build_passes(mbefci_ctx* c, Plan& P) {
     for (int i = 0; i < P.nitem; ++i) {
       Item& I = P.items[i];
       if (I.ndet <= 1 || I.sym) continue;
-      // G rows per alpha string: the off-diagonal pairs up to kFoldMax orbitals
-      const int64_t gb = (int64_t)(I.n <= kFoldMax ? I.npair - I.n : I.npair) * I.Na * g_stride(I.Nb);
+      const int64_t gb = I.n <= kStringMax ? 0 : (int64_t)I.npair * I.Na * g_stride(I.Nb);
       if (gpass > 0 && (((gpass + 15) & ~(int64_t)15) + gb) * 8 > cap) close(i);
       gpass = (gpass + 15) & ~(int64_t)15;  // a 128-byte line
       I.goff = gpass;
@@ -620,8 +645,10 @@ int64_t build_passes(mbefci_ctx* c, Plan& P) {
       const int g = P.item_group[i];
       cur.tile_lo[g] = std::min(cur.tile_lo[g], P.groups[g].item_lo[i]);
       cur.tile_hi[g] = std::max(cur.tile_hi[g], P.groups[g].item_hi[i]);
-      cur.seg_lo = std::min(cur.seg_lo, P.seg_lo[i]);
-      cur.seg_hi = std::max(cur.seg_hi, P.seg_hi[i]);
+      if (P.seg_hi[i] > P.seg_lo[i]) {
+        cur.seg_lo = std::min(cur.seg_lo, P.seg_lo[i]);
+        cur.seg_hi = std::max(cur.seg_hi, P.seg_hi[i]);
+      }
     }
     close(P.nitem);
     return gmax;
@@ -699,6 +726,35 @@ void build_sym_work(Plan& P, int64_t& gtot) {
   }
 }
 
+// Same-spin wave tiles of the CASCIs of up to kStringMax orbitals: 32 alpha x
+// 64 beta strings, or 16 x 16 where those would give less than 2048 waves (two
+// per SIMD; one CASCI of 10 orbitals has 32 of the large and 256 of the
+// small, and a wave's chain of products is as long as the strings are many).
+void build_same_units(Plan& P) {
+  P.same.clear();
+  P.same_lo.assign(P.nitem, 0);
+  P.same_hi.assign(P.nitem, 0);
+  P.operand_most = 0;
+  auto tiles = [](int n, int w) { return (n + w - 1) / w; };
+  int64_t large = 0;
+  for (int i = 0; i < P.nitem; ++i) {
+    const Item& I = P.items[i];
+    if (I.ndet <= 1 || I.sym || I.n > kStringMax) continue;
+    large += (int64_t)tiles(I.Na, 32) * tiles(I.Nb, 64);
+    P.operand_most = std::max(P.operand_most, sigma_operand_size(I.n, I.Na, I.Nb, I.na == I.nb));
+  }
+  P.same_small = large < 2048;
+  const int wa = P.same_small ? 16 : 32, wb = P.same_small ? 16 : 64;
+  for (int i = 0; i < P.nitem; ++i) {
+    const Item& I = P.items[i];
+    P.same_lo[i] = (int)P.same.size();
+    if (I.ndet > 1 && !I.sym && I.n <= kStringMax)
+      for (int a = 0; a < tiles(I.Na, wa); ++a)
+        for (int b = 0; b < tiles(I.Nb, wb); ++b) P.same.push_back(Work{i, a, b, 0});
+    P.same_hi[i] = (int)P.same.size();
+  }
+}
+
 // items must have n, na, nb filled; computes every derived field, work lists
 // and allocates the arenas.
 // The P-space machinery gives every solve its guess (and solves every CASCI
@@ -708,7 +764,7 @@ void build_sym_work(Plan& P, int64_t& gtot) {
 void finalize_plan(mbefci_ctx* c, Plan& P, int nguess_slots) {
   const int mmax = c->opts.max_space;
   P.nitem = (int)P.items.size();
-  int64_t off = 0, goff = 0, woff = 0;
+  int64_t off = 0, woff = 0;
   int chunk = 0;
   std::map<int, int> group_of_n;
   P.item_group.assign(P.nitem, -1);
@@ -743,6 +799,8 @@ void finalize_plan(mbefci_ctx* c, Plan& P, int nguess_slots) {
       I.linkA = sy->linkA;
       I.linkB = sy->linkB;
       I.linkBT = sy->linkBT;
+      I.klink = nullptr;
+      I.glink = nullptr;
       I.strA = sy->strA;
       I.strB = sy->strB;
       I.pairA = sy->pairA;
@@ -761,6 +819,8 @@ void finalize_plan(mbefci_ctx* c, Plan& P, int nguess_slots) {
       I.linkA = ta.link;
       I.linkB = tb.link;
       I.linkBT = tb.linkT;
+      I.klink = ta.klink;
+      I.glink = tb.glink;
       I.strA = ta.str;
       I.strB = tb.str;
       I.pairA = ta.pair;
@@ -775,11 +835,12 @@ void finalize_plan(mbefci_ctx* c, Plan& P, int nguess_slots) {
     I.ham = i;
     P.ndet_total += I.ndet;
     if (I.ndet > 1) {
-      goff = (goff + 15) & ~(int64_t)15;  // a 128-byte line
-      I.goff = goff;
-      goff += sy ? sy->gsize : (int64_t)I.npair * I.Na * g_stride(I.Nb);
+      I.goff = 0;  // set by build_passes and build_sym_work
+      woff = (woff + 15) & ~(int64_t)15;  // a 128-byte line
       I.woff = woff;
-      woff += (int64_t)I.kpad * I.kpad;
+      woff += sy || I.n > kStringMax
+                  ? (int64_t)I.kpad * I.kpad
+                  : sigma_operand_size(I.n, I.Na, I.Nb, I.na == I.nb);
     } else {
       I.goff = 0;
       I.woff = 0;
@@ -797,7 +858,7 @@ void finalize_plan(mbefci_ctx* c, Plan& P, int nguess_slots) {
     for (int k = 0; k < nbk; ++k) P.blocks.push_back(Work{i, k, k + 1, 0});
     P.block_hi[i] = (int)P.blocks.size();
     P.seg_lo[i] = (int)P.segs.size();
-    if (I.ndet > 1 && !sy) {
+    if (I.ndet > 1 && !sy && I.n > kStringMax) {
       const int nsg = I.Na * ((I.Nb + 63) / 64);
       for (int b = 0; b * 4 < nsg; ++b) P.segs.push_back(Work{i, b, nsg, 0});
     }
@@ -817,8 +878,9 @@ void finalize_plan(mbefci_ctx* c, Plan& P, int nguess_slots) {
     }
   }
   for (size_t gi = 0; gi < P.groups.size(); ++gi) build_tiles(P, (int)gi);
-  goff = build_passes(c, P);
+  int64_t goff = build_passes(c, P);
   build_sym_work(P, goff);
+  build_same_units(P);
   P.ntot = std::max<int64_t>(off, 64);
   P.gtot = goff;
   P.wtot = woff;
@@ -911,6 +973,8 @@ void finalize_plan(mbefci_ctx* c, Plan& P, int nguess_slots) {
   upload(c, P.d_chunks, P.chunks);
   upload(c, P.d_blocks, P.blocks);
   upload(c, P.d_segs, P.segs);
+  P.d_same = arena<Work>(c, "same", std::max<size_t>(P.same.size(), 1), &grown);
+  upload(c, P.d_same, P.same);
   for (auto& g : P.groups) upload(c, g.d_tiles, g.tiles);
   (void)nguess_slots;
 }
@@ -931,7 +995,8 @@ View single(const Plan& P, int i) {
 
 // One launch of the sigma sweep: kind 0 = contraction of group `group`,
 // kind 1 = gather, kind 2 = blocked contraction of sym group `group`, kind 3 =
-// blocked gather; work-list range [lo, lo + cnt).
+// blocked gather, kind 4 = same-spin part (before the group's kernel, which
+// adds to it); work-list range [lo, lo + cnt).
 struct SigmaLaunch {
   int kind, group, lo, cnt;
 };
@@ -957,12 +1022,16 @@ std::vector<SigmaLaunch> sigma_launches(const Plan& P, const View& v) {
     }
     const int g = P.item_group[v.item];
     if (g < 0) return out;
+    const bool strings = P.groups[g].n <= kStringMax;
+    if (strings)
+      out.push_back({4, -1, P.same_lo[v.item], P.same_hi[v.item] - P.same_lo[v.item]});
     out.push_back({0, g, P.groups[g].item_lo[v.item],
                    P.groups[g].item_hi[v.item] - P.groups[g].item_lo[v.item]});
-    out.push_back({1, -1, v.seg_lo, v.nseg});
+    if (!strings) out.push_back({1, -1, v.seg_lo, v.nseg});
     return out;
   }
   if (P.has_sym) sym_launches(P, -1, out);
+  if (!P.same.empty()) out.push_back({4, -1, 0, (int)P.same.size()});
   for (const Pass& ps : P.passes) {
     bool any = false;
     for (size_t g = 0; g < P.groups.size(); ++g)
@@ -970,7 +1039,7 @@ std::vector<SigmaLaunch> sigma_launches(const Plan& P, const View& v) {
         out.push_back({0, (int)g, ps.tile_lo[g], ps.tile_hi[g] - ps.tile_lo[g]});
         any = true;
       }
-    if (any) out.push_back({1, -1, ps.seg_lo, ps.seg_hi - ps.seg_lo});
+    if (any && ps.seg_hi > ps.seg_lo) out.push_back({1, -1, ps.seg_lo, ps.seg_hi - ps.seg_lo});
   }
   return out;
 }
@@ -990,10 +1059,20 @@ void sigma_launch(mbefci_ctx* c, Plan& P, const SigmaLaunch& L, int slot) {
                                 P.G, P.st, slot, c->stream))
       throw Error(MBEFCI_EUNSUPPORTED, "no blocked sigma kernel for " + std::to_string(sg.npc) +
                                            " pairs in a class");
+  } else if (L.kind == 4) {
+    launch_sigma_same_spin(P.d_items, P.d_same + L.lo, L.cnt, P.same_small, P.W, P.V, P.ntot, P.S,
+                           P.st, slot, c->stream);
   } else {
     launch_sigma_sym_gather(P.d_items, P.d_sym_blocks + L.lo, L.cnt, P.G, P.S, P.ntot, P.st, slot,
                             c->stream);
   }
+}
+
+// The sigma operands of the CASCIs of up to kStringMax orbitals, from their
+// folded Hamiltonians.
+void build_operands(mbefci_ctx* c, Plan& P) {
+  launch_sigma_operands(P.d_items, P.nitem, P.operand_most, P.hams, P.W, c->stream);
+  HIPCHK(hipGetLastError());
 }
 
 void sigma(mbefci_ctx* c, Plan& P, const View& v, int slot) {
@@ -1384,6 +1463,7 @@ void casci_plan(mbefci_ctx* c, int nprob, int n, int na, int nb, const double* c
   upload(c, d_e, ev);
   launch_casci_setup(n, d_h, d_g, d_e, P.d_items, P.nitem, P.hams, P.W, c->stream);
   HIPCHK(hipGetLastError());
+  build_operands(c, P);
   P.ready = true;
 }
 
@@ -1592,6 +1672,8 @@ void mbefci_destroy(mbefci_ctx* c) {
     if (kv.second.str) (void)hipFree(kv.second.str);
     if (kv.second.pair) (void)hipFree(kv.second.pair);
     if (kv.second.pairT) (void)hipFree(kv.second.pairT);
+    if (kv.second.klink) (void)hipFree(kv.second.klink);
+    if (kv.second.glink) (void)hipFree(kv.second.glink);
   }
   for (auto& kv : c->symtabs)
     if (kv.second.block) (void)hipFree(kv.second.block);
@@ -2085,6 +2167,7 @@ int mbefci_mbe_forward(mbefci_ctx* c, const mbefci_problem* pb, double* e_ref, d
     launch_mbe_setup(&P.sp, P.d_buckets, (int)P.buckets.size(), P.d_items, P.nitem, pb->h1,
                      pb->eri, pb->e_const, P.hams, P.W, P.tuple_pos, P.max_order, P.act, c->stream);
     HIPCHK(hipGetLastError());
+    build_operands(c, P);
     mbefci_stats st{};
     solve_plan(c, P, &st);
     launch_item_energy(P.d_items, P.hams, P.st, P.nitem, P.f, c->stream);
@@ -2275,6 +2358,7 @@ int mbefci_mbe_screened(mbefci_ctx* c, const mbefci_problem* pb, const mbefci_sc
         launch_mbe_setup_list(&P.sp, d_masks, P.d_items, P.nitem, pb->h1, pb->eri, pb->e_const,
                               P.hams, P.W, c->stream);
         HIPCHK(hipGetLastError());
+        build_operands(c, P);
         P.ready = true;
         mbefci_stats st{};
         solve_plan(c, P, &st);
@@ -2528,10 +2612,19 @@ int mbefci_time_kernels(mbefci_ctx* c, int32_t reps, mbefci_kernel_time* out, in
         for (int w = L.lo; w < L.lo + L.cnt; ++w)
           if (g.tiles[w].begin == 0) nd += (double)P.items[g.tiles[w].item].ndet;
         const double np = g.n * (g.n + 1) / 2;
-        flops = 2.0 * np * np * nd;
-        // c read once, G written once (up to kFoldMax orbitals its off-diagonal
-        // rows, and sigma's diagonal part)
-        bytes = 8.0 * (g.n <= kFoldMax ? 2.0 + np - g.n : 1.0 + np) * nd;
+        if (g.n <= kStringMax) {
+          // every pair row of E from the alpha string's links; c read, sigma
+          // read and written
+          for (int w = L.lo; w < L.lo + L.cnt; ++w)
+            if (g.tiles[w].begin == 0) {
+              const Item& I = P.items[g.tiles[w].item];
+              flops += 2.0 * np * (1 + I.na * (I.n - I.na)) * I.ndet;
+            }
+          bytes = 24.0 * nd;
+        } else {
+          flops = 2.0 * np * np * nd;
+          bytes = 8.0 * (1.0 + np) * nd;  // c read once, G written once
+        }
         name = (g.tn < 0 ? "sigma_dgemm_flat<n=" : "sigma_dgemm<n=") + std::to_string(g.n) +
                ",tile=" + std::to_string(g.tn < 0 ? -g.tn : g.tn) + ">";
       } else if (L.kind == 1) {
@@ -2539,9 +2632,7 @@ int mbefci_time_kernels(mbefci_ctx* c, int32_t reps, mbefci_kernel_time* out, in
           if (P.segs[w].begin == 0) {
             const Item& I = P.items[P.segs[w].item];
             nd += (double)I.ndet;
-            // G read once, sigma written (up to kFoldMax orbitals: G's
-            // off-diagonal rows, sigma read and written)
-            bytes += 8.0 * (I.n <= kFoldMax ? I.npair - I.n + 2.0 : I.npair + 1.0) * I.ndet;
+            bytes += 8.0 * (I.npair + 1.0) * I.ndet;  // G read once, sigma written
           }
         name = "sigma_gather";
       } else if (L.kind == 2) {
@@ -2562,6 +2653,17 @@ int mbefci_time_kernels(mbefci_ctx* c, int32_t reps, mbefci_kernel_time* out, in
           bytes += 8.0 * (1.0 + nps) * d;
         }
         name = "sigma_sym_dgemm<npc=" + std::to_string(sg.npc) + ">";
+      } else if (L.kind == 4) {
+        for (int w = L.lo; w < L.lo + L.cnt; ++w)
+          if (P.same[w].begin == 0 && P.same[w].end == 0) {
+            const Item& I = P.items[P.same[w].item];
+            nd += (double)I.ndet;
+            // the string Hamiltonians of both spins, c read, sigma written
+            flops += 2.0 * (I.Na + I.Nb) * I.ndet;
+            bytes += 8.0 * (2.0 * I.ndet + (double)I.Na * I.Na +
+                            (I.na == I.nb ? 0.0 : (double)I.Nb * I.Nb));
+          }
+        name = "sigma_same_spin";
       } else {
         for (int w = L.lo; w < L.lo + L.cnt; ++w)
           if (P.sym_blocks[w].begin == 0) {
