@@ -42,7 +42,6 @@ __host__ __device__ inline int offdiag_index(int a, int b) { return a * (a - 1) 
 // determinant into the array G (k_sigma_dgemm_pairrows, k_sigma_gather).
 // The shapes below fix the layout of their link tables and of E.
 constexpr int kStringMax = 10;
-constexpr int kStringPassRows = 28;  // off-diagonal pairs of 8 orbitals
 __host__ __device__ constexpr int string_binom(int n, int k) {
   int r = 1;
   for (int i = 1; i <= k; ++i) r = r * (n - k + i) / i;
@@ -50,10 +49,17 @@ __host__ __device__ constexpr int string_binom(int n, int k) {
 }
 // columns of an integral row: the pairs, rounded up to 4
 __host__ __device__ constexpr int string_kp(int n) { return (n * (n + 1) / 2 + 3) / 4 * 4; }
-// E in one pass of all rows, or from 9 orbitals on in two of 28 rows
-__host__ __device__ constexpr int string_passes(int n) { return n >= 9 ? 2 : 1; }
+// rows of E formed at a time (a pass; a multiple of 4), and the passes.  The
+// A operand of a pass stays in registers, so its rows set the registers of a
+// wave and the LDS of a workgroup.  Sigma sweeps in ms: 10 orbitals
+// (Hubbard-16) 16, 20, 24 rows 0.836, 0.820, 0.846; 9 orbitals (synthetic
+// M = 40) 16, 20, 24, 28 rows 3.00, 3.08, 3.03, 2.97; 8 orbitals (18 sites,
+// 4-orbital reference, order 4) 12, 20, 24, 36 rows 0.165, 0.160, 0.167, 0.181.
 __host__ __device__ constexpr int string_rows(int n) {
-  return n >= 9 ? kStringPassRows : string_kp(n);
+  return n == 10 ? 20 : n == 9 ? 28 : n == 8 ? 20 : string_kp(n);
+}
+__host__ __device__ constexpr int string_passes(int n) {
+  return (string_kp(n) + string_rows(n) - 1) / string_rows(n);
 }
 // row stride of E in LDS: the most strings rounded up to an odd multiple of 16
 // doubles, which spreads the rows of one store over the banks
@@ -68,18 +74,17 @@ __host__ __device__ constexpr int string_kslots(int n, int ne) {
   const int k = (1 + ne * (n - ne) + 3) / 4, least = most > 2 ? most - 2 : 1;
   return 4 * (k > least ? k : least);
 }
-// pairs of 16-bit link entries of a beta string in pass p, the most of any
-// string: with k electrons in the lowest 8 orbitals a string has k (8 - k)
-// links among them
-__host__ __device__ constexpr int string_gpairs(int n, int ne, int p) {
-  const int all = ne * (n - ne) + ne;
-  if (string_passes(n) == 1) return p == 0 ? (all + 1) / 2 : 0;
-  int most = 0;
-  for (int k = ne > n - 8 ? ne - (n - 8) : 0; k <= ne && k <= 8; ++k) {
-    const int c = p == 0 ? k * (8 - k) : all - k * (8 - k);
-    most = c > most ? c : most;
-  }
-  return (most + 1) / 2;
+// Pairs of 16-bit link entries of a beta string in pass p: half the most links
+// (occupied diagonal ones included) that any string of any electron count has
+// among the rows of the pass.
+__host__ __device__ constexpr int string_gpairs(int n, int p) {
+  constexpr int one_pass[8] = {0, 1, 1, 2, 3, 5, 6, 8};
+  return n == 10 ? (p == 0 ? 6 : p == 1 ? 9 : 7) : n == 9 ? 8 : n == 8 ? (p == 0 ? 6 : 7) : one_pass[n];
+}
+__host__ __device__ constexpr int string_gtotal(int n) {
+  int s = 0;
+  for (int p = 0; p < string_passes(n); ++p) s += string_gpairs(n, p);
+  return s;
 }
 
 // Load through the global address space (pointers read from device structs

@@ -500,8 +500,9 @@ __device__ inline double rot_blocks(double x) {  // block b takes block (b - R) 
   }
 }
 // Load at a byte offset of 32 bits from a uniform base (one address register).
-__device__ inline double ldg_at(const double* base, uint32_t bytes) {
-  return ldg((const double*)((const char*)base + bytes));
+template <class T>
+__device__ inline T ldg_at(const void* base, uint32_t bytes) {
+  return ldg((const T*)((const char*)base + bytes));
 }
 __device__ inline double mfma4(double a, double b, double c) {
   return __builtin_amdgcn_mfma_f64_4x4x4f64(a, b, c, 0, 0, 0);
@@ -521,11 +522,12 @@ __device__ inline int xcd_unit(int block, int n) {
   return (k / kRun * kXcds + x) * kRun + k % kRun;
 }
 
-// Integral rows of k_sigma_dgemm, per CASCI [no + Na + 1][kp] (no = n (n-1) / 2
-// off-diagonal pairs, kp = npair rounded up to 4): column c is (.|c) for
-// off-diagonal pair c < no (offdiag_index) and (.|kk) for c = no + k; row
-// kl < no is the integral row (kl|c), row no + Ia the sum over the occupied
-// orbitals of alpha string Ia of (kk|c), the last row zero.  Then Ha and, for
+// Integral rows of k_sigma_dgemm, per CASCI [2 no + Na + 1][kp] (no =
+// n (n-1) / 2 off-diagonal pairs, kp = npair rounded up to 4): column c is
+// (.|c) for off-diagonal pair c < no (offdiag_index) and (.|kk) for c = no + k;
+// rows kl and no + kl are (kl|c) and -(kl|c), for links of either sign, row
+// 2 no + Ia the sum over the occupied orbitals of alpha string Ia of (kk|c), the
+// last row zero.  Then Ha and, for
 // unequal electron counts, Hb, [np][np] with np = strings rounded up to 16 and
 // zero padding.
 __global__ void __launch_bounds__(256) k_sigma_operands(const Item* __restrict__ items,
@@ -540,7 +542,7 @@ __global__ void __launch_bounds__(256) k_sigma_operands(const Item* __restrict__
   auto g = [&](int p, int q, int r, int s) -> double {
     return ldg(eri + (((int64_t)H.act[p] * M + H.act[q]) * M + H.act[r]) * M + H.act[s]);
   };
-  const int64_t nv = (int64_t)(no + I.Na + 1) * kp;
+  const int64_t nv = (int64_t)(2 * no + I.Na + 1) * kp;
   const int pa = (I.Na + 15) & ~15, pb = (I.Nb + 15) & ~15;
   const int64_t na2 = (int64_t)pa * pa, nb2 = I.na != I.nb ? (int64_t)pb * pb : 0;
   double* __restrict__ out = warena + I.woff;
@@ -558,12 +560,14 @@ __global__ void __launch_bounds__(256) k_sigma_operands(const Item* __restrict__
         a = b = c - no;
       }
       if (a < n) {
-        if (row < no) {
+        if (row < 2 * no) {
+          const int kl = row < no ? row : row - no;
           int k = 1;
-          while ((k + 1) * k / 2 <= row) ++k;
-          v = g(k, row - k * (k - 1) / 2, a, b);
-        } else if (row < no + I.Na) {
-          for (uint64_t m = I.strA[row - no]; m; m &= m - 1) {
+          while ((k + 1) * k / 2 <= kl) ++k;
+          v = g(k, kl - k * (k - 1) / 2, a, b);
+          if (row >= no) v = -v;
+        } else if (row < 2 * no + I.Na) {
+          for (uint64_t m = I.strA[row - 2 * no]; m; m &= m - 1) {
             const int k = __builtin_ctzll(m);
             v += g(k, k, a, b);
           }
@@ -597,9 +601,9 @@ __global__ void __launch_bounds__(256) k_sigma_operands(const Item* __restrict__
 
 // Link tables of k_sigma_dgemm (either may be null), one thread per string of
 // ne electrons.
-// alpha [N][ks] (ks = string_kslots): slot k is the address Ja (bits 0..9), the
-// integral row (bits 10..20) and the sign (bit 31) of one off-diagonal link,
-// then the diagonal slot (own address, row no + I), then zero-row slots.
+// alpha [N][ks] (ks = string_kslots): slot k is the address Ja (bits 0..9) and
+// the signed integral row (bits 10..20) of one off-diagonal link, then the
+// diagonal slot (own address, row 2 no + I), then zero-row slots.
 // beta [entry pairs of pass 0, then of pass 1][N]: two 16-bit entries each,
 // bits 0..14 the position of E[rs][Jb] in LDS (row in the pass times
 // string_stride plus Jb), bit 15 the sign, links in ascending row order,
@@ -609,7 +613,7 @@ __global__ void k_string_links(int n, int ne, int64_t N, uint32_t* alpha, uint32
   if (I >= N) return;
   const uint64_t m = string_unrank(I, n, ne);
   const int no = n * (n - 1) / 2, ks = string_kslots(n, ne);
-  const int S = string_stride(n), passes = string_passes(n), rp = string_rows(n);
+  const int S = string_stride(n), rp = string_rows(n);
   uint32_t* __restrict__ al = alpha ? alpha + I * ks : nullptr;
   int k = 0, pass = 0, cnt = 0, base = 0;
   uint32_t held = 0;
@@ -620,30 +624,33 @@ __global__ void k_string_links(int n, int ne, int64_t N, uint32_t* alpha, uint32
     ++cnt;
   };
   auto close = [&]() {  // fill the pass up to its entry count with zeros
-    const int full = 2 * string_gpairs(n, ne, pass);
+    const int full = 2 * string_gpairs(n, pass);
     while (beta && cnt < full) put((uint32_t)(rp * S));
     base += full / 2;
     cnt = 0;
     ++pass;
   };
+  auto link = [&](int r, uint32_t J, uint32_t neg) {  // rows ascend from call to call
+    while (r >= (pass + 1) * rp) close();
+    put((uint32_t)((r - pass * rp) * S) + J | (neg << 15));
+  };
   for (int a = 1; a < n; ++a)
     for (int b = 0; b < a; ++b) {
       const int r = a * (a - 1) / 2 + b;
-      if (pass + 1 < passes && r == (pass + 1) * rp) close();
       const bool ia = m >> a & 1, ib = m >> b & 1;
       if (ia == ib) continue;
       const uint64_t o = (m ^ ((uint64_t)1 << a)) ^ ((uint64_t)1 << b);
       const uint64_t between = (((uint64_t)1 << a) - 1) & ~((((uint64_t)1 << b) << 1) - 1);
       const uint32_t neg = __builtin_popcountll(m & between) & 1;
       const uint32_t J = (uint32_t)string_addr(o);
-      if (al) al[k++] = J | ((uint32_t)r << 10) | (neg << 31);
-      put((uint32_t)((r - pass * rp) * S) + J | (neg << 15));
+      if (al) al[k++] = J | ((uint32_t)(r + (neg ? no : 0)) << 10);
+      link(r, J, neg);
     }
-  if (al) al[k++] = (uint32_t)I | ((uint32_t)(no + I) << 10);
-  while (al && k < ks) al[k++] = (uint32_t)I | ((uint32_t)(no + N) << 10);
+  if (al) al[k++] = (uint32_t)I | ((uint32_t)(2 * no + I) << 10);
+  while (al && k < ks) al[k++] = (uint32_t)I | ((uint32_t)(2 * no + N) << 10);
   for (int o = 0; o < n; ++o)
-    if (m >> o & 1) put((uint32_t)((no + o - pass * rp) * S) + (uint32_t)I);
-  close();
+    if (m >> o & 1) link(no + o, (uint32_t)I, 0u);
+  while (pass < string_passes(n)) close();
 }
 
 // sigma = Ha C + C Hb.  One wave per tile of 16 RB alpha x 16 CB beta strings,
@@ -654,6 +661,7 @@ __global__ void k_string_links(int n, int ne, int64_t N, uint32_t* alpha, uint32
 // is permuted to match.  Bound by the FP64 matrix pipe (2 (Na + Nb) flops per
 // determinant, operands from L2).
 typedef double double2u_t __attribute__((ext_vector_type(2), aligned(8)));
+typedef double double2_t __attribute__((ext_vector_type(2)));
 template <int RB, int CB>
 __global__ void __launch_bounds__(256, 2) k_sigma_same_spin(
     const Item* __restrict__ items, const Work* __restrict__ work, int nwork,
@@ -672,7 +680,7 @@ __global__ void __launch_bounds__(256, 2) k_sigma_same_spin(
   const int pa = (Na + 15) & ~15, pb = (Nb + 15) & ~15;
   const double* __restrict__ c = V + (int64_t)vs * ntot + I.off;
   const double* __restrict__ Ha = warena + I.woff +
-                                  (int64_t)(I.n * (I.n - 1) / 2 + Na + 1) * string_kp(I.n);
+                                  (int64_t)(I.n * (I.n - 1) + Na + 1) * string_kp(I.n);
   const double* __restrict__ Hb = I.na != I.nb ? Ha + (int64_t)pa * pa : Ha;
   const int r0 = wk.begin * 16 * RB, c0 = wk.end * 16 * CB;  // first alpha, beta string
   int ia[RB], jb[CB];
@@ -769,16 +777,22 @@ __global__ void __launch_bounds__(256, 2) k_sigma_same_spin(
 }
 
 // Opposite-spin part, added to the same-spin part in sigma.  A workgroup of
-// WPS x SPW waves takes SPW alpha strings at a time, WPS waves each: the waves
-// of a string share its 16-column blocks of E, then thread Ib sums E over the
-// links of beta string Ib.  Links and their LDS positions stay in registers
-// for the whole work unit, the string's integral rows (A operand, rotated
-// copies of the 16-row block and replicated 4-row tails) for one pass.  From 9
-// orbitals on E is formed in two passes of 28 rows (the pairs of the lowest
-// 8 orbitals, then the rest and the diagonal pairs), so that two workgroups
-// of 10 orbitals share a CU and one's sums run under the other's products.
-// Every E element is one chain over the string's links in slot order and
-// every sum has a fixed order: sigma does not depend on WPS or SPW.
+// WPS x SPW waves takes SPW alpha strings at a time, WPS waves each.  Per pass
+// of string_rows rows of E: a wave takes the rows' A operand (the string's
+// integral rows, staged in LDS) into registers, every group of 4 rows
+// replicated over the four MFMA blocks, multiplies its 16-column blocks of C
+// rows (registers, loaded during the last pass of the string before) and
+// stores E; then thread Ib sums E over the links of beta string Ib.  Loads for
+// the next pass and string are in flight under the products, and a second
+// workgroup's products run under one's sums.  Every E element is one chain
+// over the string's links in slot order and every sum has a fixed order:
+// sigma does not depend on WPS or SPW.  Bound by the FP64 matrix pipe and the
+// vector instructions of the sums, which share its issue.  Measured, sweep of
+// Hubbard-16 (10 orbitals, 12.8 M determinants in all): 0.82 ms, 37 TFLOP/s of
+// E products (45 issued); before, the contraction of all pairs and its gather
+// took 1.92 + 1.07 ms.  Rotating A's blocks through DPP moves instead of
+// replicating them costs 0.89 ms, loads under branches (each of which makes
+// the compiler wait for every load in flight) 1.06 ms.
 template <int NACT>
 struct StringShape {
   static constexpr int NP = NACT * (NACT + 1) / 2, NO = NP - NACT;
@@ -788,39 +802,51 @@ struct StringShape {
   static constexpr int KS = (1 + (NACT / 2) * ((NACT + 1) / 2) + 3) / 4;  // most k-steps
   static constexpr int KS0 = KS > 2 ? KS - 2 : 1;  // the tables hold at least these
   static constexpr int groups(int p) { return ((p + 1) * RP <= KP ? RP : KP - p * RP) / 4; }
-  static constexpr int gpairs(int p) {  // most entry pairs of a pass
-    int m = 0;
-    for (int ne = 0; ne <= NACT; ++ne) m = string_gpairs(NACT, ne, p) > m ? string_gpairs(NACT, ne, p) : m;
-    return m;
+  static constexpr int gbefore(int p) {  // entry pairs of the passes before p
+    int s = 0;
+    for (int q = 0; q < p; ++q) s += string_gpairs(NACT, q);
+    return s;
   }
 };
 
+// waves per SIMD to compile for: 256, 168 and 128 registers suffice without
+// spills, except two waves per string of 10 orbitals (eight column blocks each)
+constexpr int string_waves(int nact, int wps) {
+  return nact == 10 && wps == 2 ? 1 : nact >= 9 ? 2 : nact == 8 ? 3 : 4;
+}
 template <int NACT, int WPS, int SPW>
-__global__ void __launch_bounds__(64 * WPS * SPW, NACT >= 8 ? 2 : NACT == 7 ? 3 : 4) k_sigma_dgemm(
+__global__ void __launch_bounds__(64 * WPS * SPW, string_waves(NACT, WPS)) k_sigma_dgemm(
     const Item* __restrict__ items, const Work* __restrict__ work,
     const double* __restrict__ warena, const double* __restrict__ V, int64_t ntot,
     double* __restrict__ Sarena, const DavState* __restrict__ st, int slot) {
   using T = StringShape<NACT>;
-  constexpr int KS = T::KS, KS0 = T::KS0, S = T::S;
+  constexpr int S = T::S, P = T::P;
   constexpr int TPS = 64 * WPS;                       // threads per string
   constexpr int JPT = (T::CMAX + TPS - 1) / TPS;      // beta strings per thread
+  constexpr int CPW = ((T::CMAX + 15) / 16 + WPS - 1) / WPS;  // column blocks per wave
   constexpr int ELDS = T::RP * S + 2;                 // E of a string, then a zero
+  constexpr int RP2 = T::RP / 2;                      // 16-byte pieces of a row in a pass
+  constexpr int PCS = (4 * T::KS * RP2 + TPS - 1) / TPS;  // pieces per thread, rounded up
   __shared__ double Es[SPW * ELDS];
+  __shared__ __align__(16) double As[SPW * 2 * PCS * TPS];
   const Work wk = work[xcd_unit((int)blockIdx.x, (int)gridDim.x)];
   const Item& I = items[wk.item];
   const DavState& D = st[wk.item];
   if (!item_active(D, slot)) return;
   const int vs = vec_slot(D, slot);
-  const int Na = I.Na, Nb = I.Nb;
+  const int Nb = I.Nb;
   const double* __restrict__ c = V + (int64_t)vs * ntot + I.off;
   const double* __restrict__ W = warena + I.woff;
   double* __restrict__ out = Sarena + (int64_t)vs * ntot + I.off;
+  const uint32_t* __restrict__ klink = I.klink;
+  const uint32_t* __restrict__ glink = I.glink;
 
   const int lane = threadIdx.x & 63, li = lane & 15, lk = lane >> 4;
   const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
   const int sw = wave / WPS, wi = wave % WPS;  // string of this wave, wave of the string
   const int ts = (int)threadIdx.x - sw * TPS;
   double* __restrict__ E = Es + sw * ELDS;
+  double* __restrict__ Al = As + sw * 2 * PCS * TPS;  // [slot][row of the pass]
   if (ts == 0) E[T::RP * S] = 0.0;  // where filled-up entries point
   auto sync = [&]() {
     if constexpr (WPS > 1) {
@@ -830,124 +856,136 @@ __global__ void __launch_bounds__(64 * WPS * SPW, NACT >= 8 ? 2 : NACT == 7 ? 3 
       __builtin_amdgcn_wave_barrier();
     }
   };
-  // link entries of this thread's beta strings
-  constexpr int G0 = T::gpairs(0), G1 = T::P > 1 ? T::gpairs(1) : 0;
-  uint32_t gl0[JPT][G0], gl1[JPT][G1 > 0 ? G1 : 1];
-  const int n0 = string_gpairs(NACT, I.nb, 0), n1 = T::P > 1 ? string_gpairs(NACT, I.nb, 1) : 0;
-#pragma unroll
-  for (int j = 0; j < JPT; ++j) {
-    const int kb = min(ts + j * TPS, Nb - 1);
-#pragma unroll
-    for (int q = 0; q < G0; ++q) gl0[j][q] = q < n0 ? ldg(I.glink + q * Nb + kb) : 0u;
-#pragma unroll
-    for (int q = 0; q < G1; ++q) gl1[j][q] = q < n1 ? ldg(I.glink + (n0 + q) * Nb + kb) : 0u;
-  }
-  const int kslots = string_kslots(NACT, I.na), nks = kslots / 4;
   const int ncb = (Nb + 15) >> 4;
-  uint32_t e[KS];
-  auto load_links = [&](int ka) {
-#pragma unroll
-    for (int k = 0; k < KS; ++k)
-      if (k < KS0 || k < nks) e[k] = ldg(I.klink + ka * kslots + 4 * k + lk);
-  };
-  load_links(min(wk.begin + sw, wk.end - 1));
+  auto string_at = [&](int s) { return min(s + sw, wk.end - 1); };
 
-  for (int s0 = wk.begin; s0 < wk.end; s0 += SPW) {
-    const bool live = s0 + sw < wk.end;
-    const int Ka = live ? s0 + sw : wk.end - 1;
-    uint32_t boff[KS], aoff[KS], sg[KS];  // byte offsets of C row and integral row
+  // Every global load below is unconditional (clamped addresses): a load
+  // under a branch would make the compiler wait for all loads in flight.
+  auto body = [&](auto ks) {
+    constexpr int KS = decltype(ks)::value;  // k-steps of this item's strings
+    // Links of one string: per lane those of its k-steps (rows of C), per
+    // thread those whose integral rows it copies to LDS.
+    uint32_t eb[KS], ep[PCS], ep0[PCS];
+    auto load_links = [&](int ka) {
+      const uint32_t* __restrict__ row = klink + ka * (4 * KS);
 #pragma unroll
-    for (int k = 0; k < KS; ++k)
-      if (k < KS0 || k < nks) {
-        boff[k] = (e[k] & 0x3FFu) * (uint32_t)(8 * Nb);
-        aoff[k] = ((e[k] >> 10) & 0x7FFu) * (uint32_t)(8 * T::KP);
-        sg[k] = e[k];
-      }
-    if (s0 + SPW < wk.end) load_links(min(s0 + SPW + sw, wk.end - 1));
-    double sum0[JPT], sum1[JPT];
+      for (int k = 0; k < KS; ++k) eb[k] = ldg_at<uint32_t>(row + 4 * k, 4u * (uint32_t)lk);
 #pragma unroll
-    for (int j = 0; j < JPT; ++j) sum0[j] = sum1[j] = 0.0;
-
-    auto pass = [&](auto pc) {
-      constexpr int p = decltype(pc)::value;
-      constexpr int NG = T::groups(p), NB = NG / 4, NT = NG % 4;  // 16-row blocks, 4-row tails
-      double a[KS][NB > 0 ? 4 * NB : 1], at[KS][NT > 0 ? NT : 1], b[2][KS];
-      auto load_b = [&](int cb, double (&x)[KS]) {
-        const uint32_t col = 8 * (uint32_t)min(cb * 16 + li, Nb - 1);
-#pragma unroll
-        for (int k = 0; k < KS; ++k)
-          if (k < KS0 || k < nks) x[k] = ldg_at(c, boff[k] + col);
-      };
-      if (wi < ncb) load_b(wi, b[0]);
+      for (int x = 0; x < PCS; ++x) ep[x] = ldg_at<uint32_t>(row, 4u * (uint32_t)min((ts + x * TPS) / RP2, 4 * KS - 1));
+    };
+    double B[CPW][KS];  // this wave's columns of the string's C rows
+    auto load_b = [&](int cw) {
+      const uint32_t col = 8 * (uint32_t)min((wi + cw * WPS) * 16 + li, Nb - 1);
 #pragma unroll
       for (int k = 0; k < KS; ++k)
-        if (k < KS0 || k < nks) {
-          const uint32_t w = aoff[k] + 8 * p * T::RP;
+        B[cw][k] = ldg_at<double>(c, (eb[k] & 0x3FFu) * (uint32_t)(8 * Nb) + col);
+    };
+    double2_t pr[PCS];  // integral rows on their way to LDS
+    auto load_rows = [&](int p, const uint32_t (&e)[PCS]) {
 #pragma unroll
-          for (int r = 0; r < NB; ++r) {
-            const double x = flip_sign(ldg_at(W, w + 8 * (16 * r + li)), sg[k]);
-            a[k][4 * r] = x;
-            a[k][4 * r + 1] = rot_blocks<1>(x);
-            a[k][4 * r + 2] = rot_blocks<2>(x);
-            a[k][4 * r + 3] = rot_blocks<3>(x);
-          }
-#pragma unroll
-          for (int t = 0; t < NT; ++t)
-            at[k][t] = flip_sign(ldg_at(W, w + 8 * (16 * NB + 4 * t + (lane & 3))), sg[k]);
-        }
-      const int blk = (lane >> 2) & 3;
-      auto block = [&](int cb, const double (&x)[KS]) {
-        double acc[NG];
-#pragma unroll
-        for (int g = 0; g < NG; ++g) acc[g] = 0.0;
-#pragma unroll
-        for (int k = 0; k < KS; ++k)
-          if (k < KS0 || k < nks) {
-#pragma unroll
-            for (int g = 0; g < 4 * NB; ++g) acc[g] = mfma4(a[k][g], x[k], acc[g]);
-#pragma unroll
-            for (int t = 0; t < NT; ++t) acc[4 * NB + t] = mfma4(at[k][t], x[k], acc[4 * NB + t]);
-          }
-        double* __restrict__ Ec = E + cb * 16 + li;
-#pragma unroll
-        for (int g = 0; g < 4 * NB; ++g)
-          Ec[(16 * (g / 4) + 4 * ((blk - g) & 3) + lk) * S] = acc[g];
-#pragma unroll
-        for (int t = 0; t < NT; ++t) Ec[(16 * NB + 4 * t + lk) * S] = acc[4 * NB + t];
-      };
-      for (int cb = wi; cb < ncb; cb += 2 * WPS) {
-        if (cb + WPS < ncb) load_b(cb + WPS, b[1]);
-        block(cb, b[0]);
-        if (cb + WPS < ncb) {
-          if (cb + 2 * WPS < ncb) load_b(cb + 2 * WPS, b[0]);
-          block(cb + WPS, b[1]);
-        }
+      for (int x = 0; x < PCS; ++x) {
+        const uint32_t col = (uint32_t)min(p * T::RP + 2 * ((ts + x * TPS) % RP2), T::KP - 2);
+        pr[x] = ldg_at<double2_t>(W, (((e[x] >> 10) & 0x7FFu) * (uint32_t)T::KP + col) * 8);
       }
-      sync();
+    };
+    auto store_rows = [&]() {
+#pragma unroll
+      for (int x = 0; x < PCS; ++x) *(double2_t*)(Al + 2 * (ts + x * TPS)) = pr[x];
+    };
+    load_links(string_at(wk.begin));
+#pragma unroll
+    for (int cw = 0; cw < CPW; ++cw) load_b(cw);
+    load_rows(0, ep);
+#pragma unroll
+    for (int x = 0; x < PCS; ++x) ep0[x] = ep[x];
+    store_rows();
+    load_links(string_at(wk.begin + SPW));
+    sync();
+
+    for (int s0 = wk.begin; s0 < wk.end; s0 += SPW) {
+      const int orow = string_at(s0) * Nb;
+      double sum0[JPT], sum1[JPT];
 #pragma unroll
       for (int j = 0; j < JPT; ++j) {
-        constexpr int GN = p == 0 ? G0 : G1;
-        const int nq = p == 0 ? n0 : n1;
-#pragma unroll
-        for (int q = 0; q < GN; ++q)
-          if (q < nq) {
-            const uint32_t u = p == 0 ? gl0[j][q] : gl1[j][q];
-            sum0[j] += flip_sign(E[u & 0x7FFFu], u << 16);
-            sum1[j] += flip_sign(E[(u >> 16) & 0x7FFFu], u);
-          }
+        sum0[j] = ldg(out + orow + min(ts + j * TPS, Nb - 1));  // the same-spin part
+        sum1[j] = 0.0;
       }
-      sync();
-    };
-    pass(std::integral_constant<int, 0>{});
-    if constexpr (T::P > 1) pass(std::integral_constant<int, 1>{});
-    if (live) {
+
+      auto pass = [&](auto pc) {
+        constexpr int p = decltype(pc)::value;
+        constexpr bool last = p + 1 == P;
+        constexpr int NG = T::groups(p);  // groups of 4 rows
+        // the rows of the next pass, or of the next string's first
+        if constexpr (last) load_rows(0, ep);
+        else load_rows(p + 1, ep0);
+        // link entries of this thread's beta strings in this pass
+        constexpr int GN = string_gpairs(NACT, p);
+        const uint32_t* __restrict__ gl = glink + T::gbefore(p) * Nb;
+        uint32_t u[JPT][GN];
+#pragma unroll
+        for (int j = 0; j < JPT; ++j) {
+          uint32_t kb = 4u * (uint32_t)min(ts + j * TPS, Nb - 1);
+          asm volatile("" : "+v"(kb));  // keeps the addresses out of registers between passes
+#pragma unroll
+          for (int q = 0; q < GN; ++q) u[j][q] = ldg_at<uint32_t>(gl + q * Nb, kb);
+        }
+        double a[KS][NG];  // the four blocks of a lane group hold the same 4 rows
+#pragma unroll
+        for (int k = 0; k < KS; ++k)
+#pragma unroll
+          for (int g = 0; g < NG; ++g)
+            a[k][g] = Al[(4 * k + lk) * T::RP + 4 * g + (lane & 3)];
+#pragma unroll
+        for (int cw = 0; cw < CPW; ++cw) {
+          const int cb = wi + cw * WPS;
+          if (cb < ncb) {
+            double acc[NG];
+#pragma unroll
+            for (int g = 0; g < NG; ++g) acc[g] = 0.0;
+#pragma unroll
+            for (int k = 0; k < KS; ++k) {
+#pragma unroll
+              for (int g = 0; g < NG; ++g) acc[g] = mfma4(a[k][g], B[cw][k], acc[g]);
+            }
+            double* __restrict__ Ec = E + cb * 16 + li;
+#pragma unroll
+            for (int g = 0; g < NG; ++g) Ec[(4 * g + lk) * S] = acc[g];
+          }
+          if constexpr (last) {  // the next string's, into the registers just read
+            __builtin_amdgcn_sched_barrier(0);
+            load_b(cw);
+          }
+        }
+        sync();
+        store_rows();  // every wave has read this pass's rows
+#pragma unroll
+        for (int j = 0; j < JPT; ++j)
+#pragma unroll
+          for (int q = 0; q < GN; ++q) {
+            sum0[j] += flip_sign(E[u[j][q] & 0x7FFFu], u[j][q] << 16);
+            sum1[j] += flip_sign(E[(u[j][q] >> 16) & 0x7FFFu], u[j][q]);
+          }
+        sync();
+      };
+      pass(std::integral_constant<int, 0>{});
+      if constexpr (P > 1) pass(std::integral_constant<int, 1>{});
+      if constexpr (P > 2) pass(std::integral_constant<int, 2>{});
+      if constexpr (P > 3) pass(std::integral_constant<int, 3>{});
+      static_assert(P <= 4, "passes");
 #pragma unroll
       for (int j = 0; j < JPT; ++j) {
         const int kb = ts + j * TPS;
-        if (kb < Nb) out[Ka * Nb + kb] += sum0[j] + sum1[j];
+        if (s0 + sw < wk.end && kb < Nb) out[orow + kb] = sum0[j] + sum1[j];
       }
+#pragma unroll
+      for (int x = 0; x < PCS; ++x) ep0[x] = ep[x];
+      load_links(string_at(s0 + 2 * SPW));
     }
-  }
+  };
+  const int nks = string_kslots(NACT, I.na) / 4;
+  if (nks == T::KS) body(std::integral_constant<int, T::KS>{});
+  else if (nks == T::KS - 1 && T::KS > T::KS0) body(std::integral_constant<int, (T::KS - 1 > T::KS0 ? T::KS - 1 : T::KS0)>{});
+  else body(std::integral_constant<int, T::KS0>{});
 }
 
 // Above kStringMax orbitals: contraction G = W D+ over all pairs.  A tile is

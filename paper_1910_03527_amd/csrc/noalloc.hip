@@ -90,7 +90,7 @@ Layout layout(int n, int na, int nb, int64_t Na, int64_t Nb, int La, int Lb) {
   L.strB = take(sizeof(uint64_t) * Nb);
   if (strings) {
     L.klink = take(sizeof(uint32_t) * Na * string_kslots(n, na));
-    L.glink = take(sizeof(uint32_t) * Nb * (string_gpairs(n, nb, 0) + string_gpairs(n, nb, 1)));
+    L.glink = take(sizeof(uint32_t) * Nb * string_gtotal(n));
     L.same = take(sizeof(Work) * (size_t)L.nsame);
     L.W = take(sizeof(double) * (size_t)sigma_operand_size(n, Na, Nb, na == nb));
     L.total = off;

@@ -300,7 +300,7 @@ const StringTab& string_tab(mbefci_ctx* c, int n, int ne) {
   t.L = ne * (n - ne + 1);
   if (n <= kStringMax && n >= 2) {
     const int64_t ka = t.N * string_kslots(n, ne);
-    const int64_t gb = t.N * (string_gpairs(n, ne, 0) + string_gpairs(n, ne, 1));
+    const int64_t gb = t.N * string_gtotal(n);
     HIPCHK(hipMalloc(&t.klink, sizeof(uint32_t) * ka));
     HIPCHK(hipMalloc(&t.glink, sizeof(uint32_t) * std::max<int64_t>(gb, 1)));
     launch_string_links(n, ne, t.N, t.klink, t.glink, c->stream);
