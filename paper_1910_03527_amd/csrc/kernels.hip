@@ -527,9 +527,9 @@ __device__ inline int xcd_unit(int block, int n) {
 // (.|c) for off-diagonal pair c < no (offdiag_index) and (.|kk) for c = no + k;
 // rows kl and no + kl are (kl|c) and -(kl|c), for links of either sign, row
 // 2 no + Ia the sum over the occupied orbitals of alpha string Ia of (kk|c), the
-// last row zero.  Then Ha and, for
-// unequal electron counts, Hb, [np][np] with np = strings rounded up to 16 and
-// zero padding.
+// last row zero.  Then Ha and, for unequal electron counts, Hb, [np + 1][np] with np
+// = strings rounded up to 16 and zero padding: the off-diagonal part and, in
+// the last row, the diagonal.
 __global__ void __launch_bounds__(256) k_sigma_operands(const Item* __restrict__ items,
                                                         const ItemHam* __restrict__ hams,
                                                         double* __restrict__ warena) {
@@ -544,7 +544,7 @@ __global__ void __launch_bounds__(256) k_sigma_operands(const Item* __restrict__
   };
   const int64_t nv = (int64_t)(2 * no + I.Na + 1) * kp;
   const int pa = (I.Na + 15) & ~15, pb = (I.Nb + 15) & ~15;
-  const int64_t na2 = (int64_t)pa * pa, nb2 = I.na != I.nb ? (int64_t)pb * pb : 0;
+  const int64_t na2 = (int64_t)(pa + 1) * pa, nb2 = I.na != I.nb ? (int64_t)(pb + 1) * pb : 0;
   double* __restrict__ out = warena + I.woff;
   const int64_t step = (int64_t)gridDim.y * 256;
   for (int64_t x = (int64_t)blockIdx.y * 256 + threadIdx.x; x < nv + na2 + nb2; x += step) {
@@ -578,11 +578,11 @@ __global__ void __launch_bounds__(256) k_sigma_operands(const Item* __restrict__
       const int64_t y = x - nv - (beta ? na2 : 0);
       const int np = beta ? pb : pa, N = beta ? I.Nb : I.Na;
       const int i = (int)(y / np), j = (int)(y % np);
-      if (i < N && j < N) {
-        const uint64_t* str = beta ? I.strB : I.strA;
-        const uint64_t mi = str[i], mj = str[j];
-        if (i == j) {
-          for (uint64_t z = mi; z; z &= z - 1) {
+      const uint64_t* str = beta ? I.strB : I.strA;
+      if ((i < N || i == np) && j < N && i != j) {
+        const uint64_t mj = str[j];
+        if (i == np) {  // the diagonal
+          for (uint64_t z = mj; z; z &= z - 1) {
             const int p = __builtin_ctzll(z);
             v += H.heff[p * kMaxActive + p];
             for (uint64_t w = z & (z - 1); w; w &= w - 1) {
@@ -591,7 +591,7 @@ __global__ void __launch_bounds__(256) k_sigma_operands(const Item* __restrict__
             }
           }
         } else {
-          v = sc_offdiag(H, mi, 0, mj, 0);
+          v = sc_offdiag(H, str[i], 0, mj, 0);
         }
       }
     }
@@ -681,7 +681,7 @@ __global__ void __launch_bounds__(256, 2) k_sigma_same_spin(
   const double* __restrict__ c = V + (int64_t)vs * ntot + I.off;
   const double* __restrict__ Ha = warena + I.woff +
                                   (int64_t)(I.n * (I.n - 1) + Na + 1) * string_kp(I.n);
-  const double* __restrict__ Hb = I.na != I.nb ? Ha + (int64_t)pa * pa : Ha;
+  const double* __restrict__ Hb = I.na != I.nb ? Ha + (int64_t)(pa + 1) * pa : Ha;
   const int r0 = wk.begin * 16 * RB, c0 = wk.end * 16 * CB;  // first alpha, beta string
   int ia[RB], jb[CB];
 #pragma unroll
@@ -757,12 +757,15 @@ __global__ void __launch_bounds__(256, 2) k_sigma_same_spin(
   }
   // instruction v of lane l is row 4 ((b - v) & 3) + l/16: put row block v
   // into register v, so that a store covers whole 128-byte row pieces
+  // The diagonal, the largest terms, is added to the finished sums: at the
+  // start or middle of a chain every later term would round against it.
   double* __restrict__ out = Sarena + (int64_t)vs * ntot + I.off;
   const bool b1 = lane & 4, b2 = lane & 8;
 #pragma unroll
   for (int r = 0; r < RB; ++r)
 #pragma unroll
     for (int q = 0; q < CB; ++q) {
+      const double db = ldg(Hb + pb * pb + jb[q]);
       const double* x = acc[r][q];
       const double t0 = b1 ? x[1] : x[0], t1 = b1 ? x[0] : x[3], t2 = b1 ? x[3] : x[2],
                    t3 = b1 ? x[2] : x[1];
@@ -771,7 +774,8 @@ __global__ void __launch_bounds__(256, 2) k_sigma_same_spin(
 #pragma unroll
       for (int v = 0; v < 4; ++v) {
         const int ka = r0 + 16 * r + 4 * v + lk;
-        if (ka < Na && kb < Nb) out[ka * Nb + kb] = y[v];
+        if (ka < Na && kb < Nb)
+          out[ka * Nb + kb] = fma(ldg(Ha + pa * pa + ka) + db, ldg(c + ka * Nb + kb), y[v]);
       }
     }
 }
@@ -904,11 +908,11 @@ __global__ void __launch_bounds__(64 * WPS * SPW, string_waves(NACT, WPS)) k_sig
 
     for (int s0 = wk.begin; s0 < wk.end; s0 += SPW) {
       const int orow = string_at(s0) * Nb;
-      double sum0[JPT], sum1[JPT];
+      double same[JPT], sum0[JPT], sum1[JPT];
 #pragma unroll
       for (int j = 0; j < JPT; ++j) {
-        sum0[j] = ldg(out + orow + min(ts + j * TPS, Nb - 1));  // the same-spin part
-        sum1[j] = 0.0;
+        same[j] = ldg(out + orow + min(ts + j * TPS, Nb - 1));  // added last: the larger part
+        sum0[j] = sum1[j] = 0.0;
       }
 
       auto pass = [&](auto pc) {
@@ -975,7 +979,7 @@ __global__ void __launch_bounds__(64 * WPS * SPW, string_waves(NACT, WPS)) k_sig
 #pragma unroll
       for (int j = 0; j < JPT; ++j) {
         const int kb = ts + j * TPS;
-        if (s0 + sw < wk.end && kb < Nb) out[orow + kb] = sum0[j] + sum1[j];
+        if (s0 + sw < wk.end && kb < Nb) out[orow + kb] = same[j] + (sum0[j] + sum1[j]);
       }
 #pragma unroll
       for (int x = 0; x < PCS; ++x) ep0[x] = ep[x];

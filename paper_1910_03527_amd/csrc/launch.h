@@ -16,7 +16,8 @@ void launch_string_links(int n, int ne, int64_t N, uint32_t* alpha, uint32_t* be
 // doubles of a CASCI's sigma operands (k_sigma_operands), n <= kStringMax
 inline int64_t sigma_operand_size(int n, int64_t Na, int64_t Nb, bool same) {
   const int64_t pa = (Na + 15) & ~(int64_t)15, pb = (Nb + 15) & ~(int64_t)15;
-  return (n * (n - 1) + Na + 1) * string_kp(n) + pa * pa + (same ? 0 : pb * pb);
+  return (n * (n - 1) + Na + 1) * string_kp(n) + (pa + 1) * pa +
+         (same ? 0 : (pb + 1) * pb);
 }
 // most: the largest sigma_operand_size of the items
 void launch_sigma_operands(const Item* items, int nitem, int64_t most, const ItemHam* hams,
