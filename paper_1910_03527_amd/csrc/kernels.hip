@@ -1585,21 +1585,47 @@ __global__ void __launch_bounds__(256) k_sigma_sym_gather(const Item* __restrict
 }
 
 // ---------------------------------------------------------------- Davidson
-// Block-level fixed-order reduction of NV values per thread (256 threads).
+// Sum over the 16 lanes of a row, in every lane of it: four DPP steps (a
+// shuffle through the LDS crossbar takes several times as long as a step).
+template <int CTRL>
+__device__ inline double dpp_move(double x) {
+  const int lo = __builtin_amdgcn_mov_dpp(__double2loint(x), CTRL, 0xf, 0xf, true);
+  const int hi = __builtin_amdgcn_mov_dpp(__double2hiint(x), CTRL, 0xf, 0xf, true);
+  return __hiloint2double(hi, lo);
+}
+__device__ inline double row_sum(double x) {
+  x += dpp_move<0xB1>(x);   // quad_perm [1, 0, 3, 2]
+  x += dpp_move<0x4E>(x);   // quad_perm [2, 3, 0, 1]
+  x += dpp_move<0x141>(x);  // row_half_mirror
+  x += dpp_move<0x140>(x);  // row_mirror
+  return x;
+}
+__device__ inline double lane_value(double x, int lane) {  // lane: wave-uniform
+  const int lo = __builtin_amdgcn_readlane(__double2loint(x), lane);
+  const int hi = __builtin_amdgcn_readlane(__double2hiint(x), lane);
+  return __hiloint2double(hi, lo);
+}
+// Sum over the wave (all 64 lanes active), the same value in every lane.
+__device__ inline double wave_sum64(double v) {
+  v = row_sum(v);
+  return (lane_value(v, 0) + lane_value(v, 16)) + (lane_value(v, 32) + lane_value(v, 48));
+}
+
+// Block-level fixed-order reduction of values per thread (256 threads): slots
+// i < m and i >= fixed of v; the others are not written.
 template <int NV>
-__device__ inline void block_reduce_store(double (&v)[NV], double* out) {
+__device__ inline void block_reduce_store(double (&v)[NV], int m, int fixed, double* out) {
   __shared__ double red[4][NV];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
 #pragma unroll
-  for (int i = 0; i < NV; ++i) {
-    double x = v[i];
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) x += __shfl_down(x, o, 64);
-    if (lane == 0) red[wave][i] = x;
-  }
+  for (int i = 0; i < NV; ++i)
+    if (i < m || i >= fixed) {  // uniform
+      const double x = wave_sum64(v[i]);
+      if (lane == 0) red[wave][i] = x;
+    }
   __syncthreads();
   for (int i = threadIdx.x; i < NV; i += blockDim.x)
-    out[i] = ((red[0][i] + red[1][i]) + red[2][i]) + red[3][i];
+    if (i < m || i >= fixed) out[i] = ((red[0][i] + red[1][i]) + red[2][i]) + red[3][i];
   __syncthreads();
 }
 
@@ -1744,7 +1770,29 @@ __global__ void __launch_bounds__(256) k_dav_dots(const Item* __restrict__ items
         if (i < m) acc[i] += V[(int64_t)i * ntot + I.off + e] * s;
     }
   }
-  block_reduce_store<kMaxSpace>(acc, part + (int64_t)wk.begin * kPart);
+  block_reduce_store<kMaxSpace>(acc, m, kMaxSpace, part + (int64_t)wk.begin * kPart);
+}
+
+// Totals of an item's chunk partials by one wave: lane s < kPart returns slot s,
+// summed over chunks g, g + 3, ... by the lanes of group g, then over g.
+__device__ inline double wave_parts(const double* __restrict__ part, const Item& I) {
+  const int lane = threadIdx.x & 63, s = lane % kPart, g = lane / kPart;
+  const double* __restrict__ p = part + (int64_t)I.chunk0 * kPart + s;
+  double v = 0.0;
+  if (g < 3) {
+    int c = g;
+    for (; c + 21 < I.nchunk; c += 24) {  // eight loads in flight
+      double x[8];
+#pragma unroll
+      for (int q = 0; q < 8; ++q) x[q] = ldg(p + (int64_t)(c + 3 * q) * kPart);
+#pragma unroll
+      for (int q = 0; q < 8; ++q) v += x[q];
+    }
+    for (; c < I.nchunk; c += 3) v += ldg(p + (int64_t)c * kPart);
+  }
+  static_assert(3 * kPart <= 64, "three lane groups");
+  const double v1 = __shfl(v, s + kPart, 64), v2 = __shfl(v, s + 2 * kPart, 64);
+  return (v + v1) + v2;
 }
 
 // Symmetric Jacobi eigen-solve of the m x m subspace matrix by one wave of
@@ -1827,9 +1875,8 @@ __global__ void k_dav_rr(const Item* __restrict__ items, int ibase,
   const int lane = threadIdx.x;
   // the Ritz coefficients of the subspace before the newest vector
   const double yold = (lane < kMaxSpace && lane < j) ? S.y[lane] : 0.0;
+  const double v = wave_parts(part, I);
   if (lane < m) {
-    double v = 0.0;
-    for (int c = 0; c < I.nchunk; ++c) v += part[(int64_t)(I.chunk0 + c) * kPart + lane];
     S.Hs[lane * kMaxSpace + j] = v;
     S.Hs[j * kMaxSpace + lane] = v;
   }
@@ -2037,7 +2084,7 @@ __global__ void __launch_bounds__(256) k_dav_residual(const Item* __restrict__ i
         if (i < m) acc[i] += v[i] * tv;
     }
   }
-  block_reduce_store<kMaxSpace + 2>(acc, part + (int64_t)wk.begin * kPart);
+  block_reduce_store<kMaxSpace + 2>(acc, m, kMaxSpace, part + (int64_t)wk.begin * kPart);
 }
 
 // Olsen-corrected preconditioner.  With x = V y the Ritz vector and
@@ -2083,25 +2130,22 @@ __global__ void __launch_bounds__(256) k_dav_residual_olsen(
     acc[1] += x * r / den;
     acc[2] += x * x / den;
   }
-  block_reduce_store<3>(acc, part + (int64_t)wk.begin * kPart);
+  block_reduce_store<3>(acc, 3, 3, part + (int64_t)wk.begin * kPart);
 }
 
 __global__ void k_dav_reduce1_olsen(const Item* __restrict__ items,
                                     const double* __restrict__ part, DavState* st, int ibase,
                                     int nitem, double tol, int max_iter, int all) {
-  int it = blockIdx.x * blockDim.x + threadIdx.x;
+  int it = blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);  // a wave per item
   if (it >= nitem) return;
   it += ibase;
+  const int lane = threadIdx.x & 63;
   const Item& I = items[it];
   DavState& S = st[it];
   if (S.conv || !(all || S.olsen)) return;
-  double rr = 0.0, a = 0.0, b = 0.0;
-  for (int c = 0; c < I.nchunk; ++c) {
-    const double* p = part + (int64_t)(I.chunk0 + c) * kPart;
-    rr += p[0];
-    a += p[1];
-    b += p[2];
-  }
+  const double v = wave_parts(part, I);
+  const double rr = lane_value(v, 0), a = lane_value(v, 1), b = lane_value(v, 2);
+  if (lane != 0) return;
   S.rnorm = sqrt(rr);
   S.eps = (b != 0.0) ? a / b : 0.0;
   if (S.rnorm <= tol || S.m >= I.ndet) {
@@ -2137,26 +2181,22 @@ __global__ void __launch_bounds__(256) k_dav_precond_olsen(
     for (int i = 0; i < kMaxSpace; ++i)
       if (i < m) acc[i] += V[(int64_t)i * ntot + I.off + e] * tv;
   }
-  block_reduce_store<kMaxSpace>(acc, part + (int64_t)wk.begin * kPart);
+  block_reduce_store<kMaxSpace>(acc, m, kMaxSpace, part + (int64_t)wk.begin * kPart);
 }
 
 // first Gram-Schmidt coefficients from the partial dots
 __global__ void k_dav_reduce_coef(const Item* __restrict__ items, const double* __restrict__ part,
                                   DavState* st, int ibase, int nitem, int all) {
-  int it = blockIdx.x * blockDim.x + threadIdx.x;
+  int it = blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);  // a wave per item
   if (it >= nitem) return;
   it += ibase;
+  const int lane = threadIdx.x & 63;
   const Item& I = items[it];
   DavState& S = st[it];
   if (S.conv || !(all || S.olsen)) return;
-  double cf[kMaxSpace];
-  for (int i = 0; i < kMaxSpace; ++i) cf[i] = 0.0;
-  for (int c = 0; c < I.nchunk; ++c) {
-    const double* p = part + (int64_t)(I.chunk0 + c) * kPart;
-    for (int i = 0; i < S.m; ++i) cf[i] += p[i];
-  }
-  for (int i = 0; i < kMaxSpace; ++i) S.coef[i] = cf[i];
-  S.onepass = 0;
+  const double v = wave_parts(part, I);
+  if (lane < kMaxSpace) S.coef[lane] = lane < S.m ? v : 0.0;
+  if (lane == 0) S.onepass = 0;
 }
 
 // Convergence test and first Gram-Schmidt coefficients.  An unconverged
@@ -2165,32 +2205,29 @@ __global__ void k_dav_reduce_coef(const Item* __restrict__ items, const double* 
 __global__ void k_dav_reduce1(const Item* __restrict__ items, const double* __restrict__ part,
                               const double* __restrict__ pdots, DavState* st, int ibase,
                               int nitem, double tol, int max_iter, double olsen_below) {
-  int it = blockIdx.x * blockDim.x + threadIdx.x;
+  int it = blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);  // a wave per item
   if (it >= nitem) return;
   it += ibase;
+  const int lane = threadIdx.x & 63;
   const Item& I = items[it];
   DavState& S = st[it];
   if (S.conv || S.olsen) return;
-  double rr = 0.0, tt = 0.0;
-  double cf[kMaxSpace];
-  for (int i = 0; i < kMaxSpace; ++i) cf[i] = 0.0;
-  for (int c = 0; c < I.nchunk; ++c) {
-    const double* p = part + (int64_t)(I.chunk0 + c) * kPart;
-    rr += p[kMaxSpace];
-    tt += p[kMaxSpace + 1];
-    for (int i = 0; i < S.m; ++i) cf[i] += p[i];
-  }
-  if (pdots && S.np > 0) {  // the P-space correction changed t on the P block
-    const double* pd = pdots + (int64_t)it * (kMaxSpace + 1);
-    for (int i = 0; i < S.m; ++i) cf[i] += pd[i];
-    tt += pd[kMaxSpace];
-  }
-  S.rnorm = sqrt(rr);
-  for (int i = 0; i < kMaxSpace; ++i) S.coef[i] = cf[i];
+  double v = wave_parts(part, I);
+  const int m = S.m;
+  // the P-space correction changed t on the P block
+  const bool corrected = pdots && S.np > 0;
+  const double* pd = pdots + (int64_t)it * (kMaxSpace + 1);
+  if (corrected && lane < m) v += pd[lane];
+  const double rr = lane_value(v, kMaxSpace);
+  double tt = lane_value(v, kMaxSpace + 1);
+  if (corrected) tt += pd[kMaxSpace];
+  const double cf = lane < m ? v : 0.0;
   // one Gram-Schmidt pass suffices when it keeps at least half of |t|^2
   // (the Daniel-Gragg-Kaufman-Stewart criterion); |t - V c|^2 = |t|^2 - |c|^2
-  double n1 = tt;
-  for (int i = 0; i < S.m; ++i) n1 -= cf[i] * cf[i];
+  const double n1 = tt - wave_sum64(cf * cf);
+  if (lane < kMaxSpace) S.coef[lane] = cf;
+  if (lane != 0) return;
+  S.rnorm = sqrt(rr);
   S.onepass = (n1 >= 0.5 * tt && n1 > 1e-28) ? 1 : 0;
   S.tnorm2 = n1;
   if (S.rnorm <= tol || S.m >= I.ndet) {
@@ -2283,28 +2320,23 @@ __global__ void __launch_bounds__(256) k_dav_orth(const Item* __restrict__ items
       acc[kMaxSpace] += tv * tv;
     }
   }
-  block_reduce_store<kMaxSpace + 1>(acc, part + (int64_t)wk.begin * kPart);
+  block_reduce_store<kMaxSpace + 1>(acc, m, kMaxSpace, part + (int64_t)wk.begin * kPart);
 }
 
 __global__ void k_dav_reduce2(const Item* __restrict__ items, const double* __restrict__ part,
                               DavState* st, int ibase, int nitem) {
-  int it = blockIdx.x * blockDim.x + threadIdx.x;
+  int it = blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);  // a wave per item
   if (it >= nitem) return;
   it += ibase;
+  const int lane = threadIdx.x & 63;
   const Item& I = items[it];
   DavState& S = st[it];
   if (S.conv || S.onepass) return;
-  double tt = 0.0;
-  double cf[kMaxSpace];
-  for (int i = 0; i < kMaxSpace; ++i) cf[i] = 0.0;
-  for (int c = 0; c < I.nchunk; ++c) {
-    const double* p = part + (int64_t)(I.chunk0 + c) * kPart;
-    tt += p[kMaxSpace];
-    for (int i = 0; i < S.m; ++i) cf[i] += p[i];
-  }
-  double n2 = tt;
-  for (int i = 0; i < S.m; ++i) n2 -= cf[i] * cf[i];
-  for (int i = 0; i < kMaxSpace; ++i) S.coef[i] = cf[i];
+  const double v = wave_parts(part, I);
+  const double cf = lane < S.m ? v : 0.0;
+  const double n2 = lane_value(v, kMaxSpace) - wave_sum64(cf * cf);
+  if (lane < kMaxSpace) S.coef[lane] = cf;
+  if (lane != 0) return;
   S.tnorm2 = n2;
   if (!(n2 > 1e-28)) {  // the correction lies in the subspace: accept
     S.conv = 1;
@@ -2383,7 +2415,7 @@ template <class KeyAt>
 __device__ void select_lowest(const KeyAt& key_at, int64_t n, int np, uint64_t* khi,
                               uint32_t* klo) {
   const int t = threadIdx.x;
-  __shared__ uint32_t hist[256];
+  __shared__ uint32_t hist[256], wtot[4];
   __shared__ uint64_t pre_hi;
   __shared__ uint32_t pre_lo;
   __shared__ int64_t need;
@@ -2414,16 +2446,24 @@ __device__ void select_lowest(const KeyAt& key_at, int64_t n, int np, uint64_t* 
         if (match) atomicAdd(&hist[b], 1u);
       }
       __syncthreads();
-      if (t == 0) {
-        int64_t k = need, cum = 0;
-        int b = 0;
-        for (; b < 255; ++b) {
-          if (cum + hist[b] >= k) break;
-          cum += hist[b];
-        }
-        need = k - cum;
-        if (dg < 8) pre_hi |= (uint64_t)b << (56 - 8 * dg);
-        else pre_lo |= (uint32_t)b << (24 - 8 * (dg - 8));
+      // the digit whose running count first reaches `need`: thread t holds
+      // digit t, a wave scan and the totals of the lower waves
+      const int64_t k = need;
+      const uint32_t h = hist[t];
+      uint32_t incl = h;
+#pragma unroll
+      for (int o = 1; o < 64; o <<= 1) {
+        const uint32_t up = __shfl_up(incl, o, 64);
+        if ((t & 63) >= o) incl += up;
+      }
+      if ((t & 63) == 63) wtot[t >> 6] = incl;
+      __syncthreads();
+      for (int w = 0; w < (t >> 6); ++w) incl += wtot[w];
+      const int64_t below = (int64_t)incl - h;
+      if (below < k && ((int64_t)incl >= k || t == 255)) {
+        need = k - below;
+        if (dg < 8) pre_hi |= (uint64_t)t << (56 - 8 * dg);
+        else pre_lo |= (uint32_t)t << (24 - 8 * (dg - 8));
       }
       __syncthreads();
     }
@@ -2688,14 +2728,9 @@ __global__ void __launch_bounds__(NT) k_pspace_eigen(
   __syncthreads();
 
   // ---- Householder reduction: step k annihilates A[k+2.., k].  The two
-  // dot products of a step are formed by every wave for itself (a butterfly
-  // over the wave leaves the same value in every lane of every wave), so a
+  // dot products of a step are formed by every wave for itself (the wave sum
+  // leaves the same value in every lane of every wave), so a
   // step needs three block barriers.
-  auto wave_sum = [&](double x) -> double {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) x += __shfl_xor(x, o, 64);
-    return x;
-  };
   for (int k = 0; k + 2 < n; ++k) {
     const int m = n - k - 1;
     double sq = 0.0;
@@ -2703,7 +2738,7 @@ __global__ void __launch_bounds__(NT) k_pspace_eigen(
       const double xi = A[L(k + 1 + i, k)];
       sq += xi * xi;
     }
-    const double sig = wave_sum(sq);
+    const double sig = wave_sum64(sq);
     const double x0 = A[L(k + 1, k)];
     const double sg = sqrt(sig);
     const double alpha = x0 >= 0.0 ? -sg : sg;
@@ -2730,7 +2765,7 @@ __global__ void __launch_bounds__(NT) k_pspace_eigen(
       __syncthreads();
       double pv = 0.0;
       for (int i = lane; i < m; i += 64) pv += pw[i] * vv[i];
-      const double Kc = 0.5 * bt * wave_sum(pv);
+      const double Kc = 0.5 * bt * wave_sum64(pv);
       // B -= v w^T + w v^T with w = p - K v (lower triangle), rows strided
       // by 64, columns by 8
       for (int i = t >> 3; i < m; i += NT / 8) {
@@ -2861,7 +2896,7 @@ __global__ void __launch_bounds__(NT) k_pspace_eigen(
       const int m = n - k - 1;
       double sp = 0.0;
       for (int i = lane; i < m; i += 64) sp += A[L(k + 1 + i, k)] * zz[k + 1 + i];
-      const double sc = bt * wave_sum(sp);
+      const double sc = bt * wave_sum64(sp);
       for (int i = lane; i < m; i += 64) zz[k + 1 + i] -= sc * A[L(k + 1 + i, k)];
       __builtin_amdgcn_wave_barrier();  // the next step reads other lanes' updates
     }
@@ -2959,7 +2994,7 @@ __global__ void __launch_bounds__(256) k_pspace_correct(const Item* __restrict__
       if (i < m) acc[i] = V[(int64_t)i * ntot + I.off + e] * dl;
     acc[kMaxSpace] = tnew * tnew - told * told;
   }
-  block_reduce_store<kMaxSpace + 1>(acc, pdots + (int64_t)it * (kMaxSpace + 1));
+  block_reduce_store<kMaxSpace + 1>(acc, m, kMaxSpace, pdots + (int64_t)it * (kMaxSpace + 1));
 }
 
 // ------------------------------------------------------------------- RDMs
@@ -3065,27 +3100,39 @@ __global__ void __launch_bounds__(256) k_rdm_syrk(const Item* __restrict__ items
 }
 
 // Sum the partials of every item in work order; fill the lower triangle.
-// rdmp: [item][KPAD*KPAD] (KPAD of that item).
-__global__ void k_rdm_reduce(const Item* __restrict__ items, const int32_t* __restrict__ wlo,
-                             const int32_t* __restrict__ whi, const double* __restrict__ part,
-                             const int64_t* __restrict__ poff, double* rdmp,
-                             const int64_t* __restrict__ roff) {
+// rdmp: [item][KPAD*KPAD] (KPAD of that item).  Grid (items, blocks of 256
+// elements of the largest item): a thread sums one element, eight partials in
+// flight (one block per item took 7.9 ms for CAS(14,14)'s 512 partials).
+__global__ void __launch_bounds__(256) k_rdm_reduce(
+    const Item* __restrict__ items, const int32_t* __restrict__ wlo,
+    const int32_t* __restrict__ whi, const double* __restrict__ part,
+    const int64_t* __restrict__ poff, double* rdmp, const int64_t* __restrict__ roff) {
   const int it = blockIdx.x;
   const Item& I = items[it];
   const int kp = I.kpad;
-  double* out = rdmp + roff[it];
-  for (int x = threadIdx.x; x < kp * kp; x += blockDim.x) {
-    const int r = x / kp, cc = x % kp;
-    const int rr = r < cc ? r : cc, c2 = r < cc ? cc : r;  // upper triangle holds the data
-    double sacc = 0.0;
-    if (I.ndet == 1) {
-      // single determinant: D+_aa = occupation, c = 1
-      sacc = 0.0;
-    } else {
-      for (int w = wlo[it]; w < whi[it]; ++w) sacc += part[poff[w] + rr * kp + c2];
+  const int x = blockIdx.y * 256 + threadIdx.x;
+  if (x >= kp * kp) return;
+  const int r = x / kp, cc = x % kp;
+  double* __restrict__ out = rdmp + roff[it];
+  if (r > cc) return;  // the upper triangle holds the data
+  double sacc = 0.0;   // a single determinant has none
+  if (I.ndet > 1) {
+    // an item's partials follow each other, kp * kp apart
+    const int w0 = wlo[it], nw = whi[it] - w0;
+    const double* __restrict__ p = part + poff[w0] + x;
+    const int64_t step = (int64_t)kp * kp;
+    int w = 0;
+    for (; w + 7 < nw; w += 8) {
+      double y[8];
+#pragma unroll
+      for (int q = 0; q < 8; ++q) y[q] = ldg(p + (w + q) * step);
+#pragma unroll
+      for (int q = 0; q < 8; ++q) sacc += y[q];
     }
-    out[x] = sacc;
+    for (; w < nw; ++w) sacc += ldg(p + w * step);
   }
+  out[x] = sacc;
+  out[cc * kp + r] = sacc;
 }
 
 // ------------------------------------------------------ gradient assembly
@@ -3167,11 +3214,6 @@ __device__ double sym_gamma2(int p, int q, int r, int s, int cp, int cq, int cr,
 
 // Sum over a wave by a butterfly: every lane ends with the same value, and
 // the order of the additions is fixed by the lane numbering alone.
-__device__ inline double wave_sum64(double v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-  return v;
-}
 
 // Orbitals on which a CASCI's full-space RDMs can be non-zero: its active
 // orbitals and the occupied orbitals of the reference determinant (frozen
@@ -3966,7 +4008,7 @@ void launch_dav_iteration(const Item* items, int ibase, int nitem, const Work* c
                           double* Xb, const PspaceArgs* ps, bool olsen_all, double olsen_below,
                           hipStream_t s) {
   if (nchunk <= 0) return;
-  const int nb = nblk(nitem, 64);
+  const int nb = nblk(nitem, 64), nw = nblk(nitem, 4);
   hipLaunchKernelGGL(k_dav_collapse, dim3(nchunk), dim3(256), 0, s, items, chunks, V, Sv, ntot, st,
                      mmax);
   hipLaunchKernelGGL(k_dav_collapse_state, dim3(nb), dim3(64), 0, s, items, st, ibase, nitem,
@@ -3978,11 +4020,11 @@ void launch_dav_iteration(const Item* items, int ibase, int nitem, const Work* c
     const int all = olsen_all ? 1 : 0;
     hipLaunchKernelGGL(k_dav_residual_olsen, dim3(nchunk), dim3(256), 0, s, items, chunks, V, Sv,
                        diag, ntot, st, Rb, Xb, part, all);
-    hipLaunchKernelGGL(k_dav_reduce1_olsen, dim3(nb), dim3(64), 0, s, items, part, st, ibase,
+    hipLaunchKernelGGL(k_dav_reduce1_olsen, dim3(nw), dim3(256), 0, s, items, part, st, ibase,
                        nitem, tol, max_iter, all);
     hipLaunchKernelGGL(k_dav_precond_olsen, dim3(nchunk), dim3(256), 0, s, items, chunks, V, diag,
                        ntot, st, Rb, Xb, part, all);
-    hipLaunchKernelGGL(k_dav_reduce_coef, dim3(nb), dim3(64), 0, s, items, part, st, ibase, nitem,
+    hipLaunchKernelGGL(k_dav_reduce_coef, dim3(nw), dim3(256), 0, s, items, part, st, ibase, nitem,
                        all);
   }
   if (!olsen_all) {
@@ -3991,11 +4033,11 @@ void launch_dav_iteration(const Item* items, int ibase, int nitem, const Work* c
     if (ps)
       hipLaunchKernelGGL(k_pspace_correct, dim3(nitem), dim3(256), 0, s, items, ibase, ps->pidx,
                          ps->pQ, ps->pT, V, Sv, ntot, st, ps->pdots);
-    hipLaunchKernelGGL(k_dav_reduce1, dim3(nb), dim3(64), 0, s, items, part,
+    hipLaunchKernelGGL(k_dav_reduce1, dim3(nw), dim3(256), 0, s, items, part,
                        ps ? ps->pdots : nullptr, st, ibase, nitem, tol, max_iter, olsen_below);
   }
   hipLaunchKernelGGL(k_dav_orth, dim3(nchunk), dim3(256), 0, s, items, chunks, V, ntot, st, part);
-  hipLaunchKernelGGL(k_dav_reduce2, dim3(nb), dim3(64), 0, s, items, part, st, ibase, nitem);
+  hipLaunchKernelGGL(k_dav_reduce2, dim3(nw), dim3(256), 0, s, items, part, st, ibase, nitem);
   hipLaunchKernelGGL(k_dav_orth2, dim3(nchunk), dim3(256), 0, s, items, chunks, V, ntot, st);
   hipLaunchKernelGGL(k_dav_grow, dim3(nb), dim3(64), 0, s, st, ibase, nitem);
 }
@@ -4076,10 +4118,10 @@ bool launch_rdm_syrk(int n, int tn, const Item* items, const Work* work, int nwo
 }
 void launch_rdm_reduce(const Item* items, int nitem, const int32_t* wlo, const int32_t* whi,
                        const double* part, const int64_t* poff, double* rdmp, const int64_t* roff,
-                       hipStream_t s) {
+                       int kpad_max, hipStream_t s) {
   if (nitem > 0)
-    hipLaunchKernelGGL(k_rdm_reduce, dim3(nitem), dim3(256), 0, s, items, wlo, whi, part, poff,
-                       rdmp, roff);
+    hipLaunchKernelGGL(k_rdm_reduce, dim3(nitem, (kpad_max * kpad_max + 255) / 256), dim3(256), 0,
+                       s, items, wlo, whi, part, poff, rdmp, roff);
 }
 void launch_mbe_weights(const BucketDev* buckets, int nbucket, int nitem, int nexp, int max_order,
                         const double* g, double* w, hipStream_t s) {

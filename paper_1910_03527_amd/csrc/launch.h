@@ -197,7 +197,7 @@ bool launch_rdm_syrk(int n, int tn, const Item* items, const Work* work, int nwo
                      const double* civ, double* part, hipStream_t s);
 void launch_rdm_reduce(const Item* items, int nitem, const int32_t* wlo, const int32_t* whi,
                        const double* part, const int64_t* poff, double* rdmp, const int64_t* roff,
-                       hipStream_t s);
+                       int kpad_max, hipStream_t s);
 void launch_mbe_weights(const BucketDev* buckets, int nbucket, int nitem, int nexp, int max_order,
                         const double* g, double* w, hipStream_t s);
 // dE/dh and dE/d(pq|rs) from the weighted RDMs, in two launches around a

@@ -1484,7 +1484,9 @@ RdmOut rdm_pass(mbefci_ctx* c, Plan& P) {
   std::vector<int32_t> wlo(P.nitem, 0), whi(P.nitem, 0);
   std::vector<int64_t> roff(P.nitem, 0);
   int64_t rtot = 0;
+  int kpad_max = 0;
   for (int i = 0; i < P.nitem; ++i) {
+    kpad_max = std::max(kpad_max, P.items[i].kpad);
     roff[i] = rtot;
     rtot += (int64_t)P.items[i].kpad * P.items[i].kpad;
   }
@@ -1534,7 +1536,8 @@ RdmOut rdm_pass(mbefci_ctx* c, Plan& P) {
                          c->stream))
       throw Error(MBEFCI_EUNSUPPORTED, "no RDM kernel for n=" + std::to_string(P.groups[gi].n));
   }
-  launch_rdm_reduce(P.d_items, P.nitem, d_wlo, d_whi, part, d_poff, rdmp, d_roff, c->stream);
+  launch_rdm_reduce(P.d_items, P.nitem, d_wlo, d_whi, part, d_poff, rdmp, d_roff, kpad_max,
+                    c->stream);
   HIPCHK(hipGetLastError());
   return RdmOut{rdmp, d_roff};
 }
