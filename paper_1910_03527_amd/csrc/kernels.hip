@@ -433,14 +433,28 @@ __device__ double sc_offdiag(const ItemHam& H, uint64_t ia, uint64_t ib, uint64_
     // one excitation q -> p in the string of spin sigma
     const uint64_t is = da ? ia : ib, js = da ? ja : jb, jo = da ? jb : ja;
     const int p = __builtin_ctzll(is & ~js), q = __builtin_ctzll(js & ~is);
+    // sum over the occupied r of (pq|rr) per string less (pr|rq) for the
+    // string's own (r = q contributes zero); the loads don't wait for each
+    // other, as they would under a loop over set bits
     double v = H.heff[p * kMaxActive + q];
-    for (uint64_t x = js; x; x &= x - 1) {
-      const int r = __builtin_ctzll(x);
-      v += g(p, q, r, r) - g(p, r, r, q);   // r = q contributes zero
-    }
-    for (uint64_t x = jo; x; x &= x - 1) {
-      const int r = __builtin_ctzll(x);
-      v += g(p, q, r, r);
+    const int top = 64 - __builtin_clzll(js | jo);
+    const int ap = H.act[p], aq = H.act[q];
+    const double* __restrict__ epq = eri + ((int64_t)ap * M + aq) * M * M;
+    const double* __restrict__ ep = eri + (int64_t)ap * M * M * M + aq;
+    for (int r0 = 0; r0 < top; r0 += 5) {
+      double c[5], x[5];
+#pragma unroll
+      for (int u = 0; u < 5; ++u) {
+        const int a = H.act[min(r0 + u, top - 1)];
+        c[u] = ldg(epq + (int64_t)a * (M + 1));
+        x[u] = ldg(ep + ((int64_t)a * M + a) * M);
+      }
+#pragma unroll
+      for (int u = 0; u < 5; ++u) {
+        const bool in = r0 + u < top;
+        if (in && (js >> (r0 + u) & 1)) v += c[u] - x[u];
+        if (in && (jo >> (r0 + u) & 1)) v += c[u];
+      }
     }
     return between_parity(js, p, q) ? -v : v;
   }
@@ -1585,8 +1599,8 @@ __global__ void __launch_bounds__(256) k_sigma_sym_gather(const Item* __restrict
 }
 
 // ---------------------------------------------------------------- Davidson
-// Sum over the 16 lanes of a row, in every lane of it: four DPP steps (a
-// shuffle through the LDS crossbar takes several times as long as a step).
+// Sum over the 16 lanes of a row, the same value in every lane of it: four DPP
+// steps (a shuffle through the LDS crossbar takes several times as long).
 template <int CTRL>
 __device__ inline double dpp_move(double x) {
   const int lo = __builtin_amdgcn_mov_dpp(__double2loint(x), CTRL, 0xf, 0xf, true);
@@ -1594,6 +1608,7 @@ __device__ inline double dpp_move(double x) {
   return __hiloint2double(hi, lo);
 }
 __device__ inline double row_sum(double x) {
+#pragma clang fp contract(off)  // x may be a product: every lane has to round it
   x += dpp_move<0xB1>(x);   // quad_perm [1, 0, 3, 2]
   x += dpp_move<0x4E>(x);   // quad_perm [2, 3, 0, 1]
   x += dpp_move<0x141>(x);  // row_half_mirror
@@ -2199,28 +2214,14 @@ __global__ void k_dav_reduce_coef(const Item* __restrict__ items, const double* 
   if (lane == 0) S.onepass = 0;
 }
 
-// Convergence test and first Gram-Schmidt coefficients.  An unconverged
-// item whose residual fell below olsen_below takes the Olsen correction from
-// the next iteration on (0: never).
-__global__ void k_dav_reduce1(const Item* __restrict__ items, const double* __restrict__ part,
-                              const double* __restrict__ pdots, DavState* st, int ibase,
-                              int nitem, double tol, int max_iter, double olsen_below) {
-  int it = blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);  // a wave per item
-  if (it >= nitem) return;
-  it += ibase;
-  const int lane = threadIdx.x & 63;
-  const Item& I = items[it];
-  DavState& S = st[it];
-  if (S.conv || S.olsen) return;
-  double v = wave_parts(part, I);
-  const int m = S.m;
-  // the P-space correction changed t on the P block
-  const bool corrected = pdots && S.np > 0;
-  const double* pd = pdots + (int64_t)it * (kMaxSpace + 1);
-  if (corrected && lane < m) v += pd[lane];
-  const double rr = lane_value(v, kMaxSpace);
-  double tt = lane_value(v, kMaxSpace + 1);
-  if (corrected) tt += pd[kMaxSpace];
+// Convergence test and first Gram-Schmidt coefficients of an item, by one wave:
+// v holds in lane i < m the total of V_i . t, in lane kMaxSpace |r|^2 and in
+// lane kMaxSpace + 1 |t|^2.  An unconverged item whose residual fell below
+// olsen_below takes the Olsen correction from the next iteration on (0: never).
+__device__ inline void dav_test(const Item& I, DavState& S, double v, double tol, int max_iter,
+                                double olsen_below) {
+  const int lane = threadIdx.x & 63, m = S.m;
+  const double rr = lane_value(v, kMaxSpace), tt = lane_value(v, kMaxSpace + 1);
   const double cf = lane < m ? v : 0.0;
   // one Gram-Schmidt pass suffices when it keeps at least half of |t|^2
   // (the Daniel-Gragg-Kaufman-Stewart criterion); |t - V c|^2 = |t|^2 - |c|^2
@@ -2230,7 +2231,7 @@ __global__ void k_dav_reduce1(const Item* __restrict__ items, const double* __re
   S.rnorm = sqrt(rr);
   S.onepass = (n1 >= 0.5 * tt && n1 > 1e-28) ? 1 : 0;
   S.tnorm2 = n1;
-  if (S.rnorm <= tol || S.m >= I.ndet) {
+  if (S.rnorm <= tol || m >= I.ndet) {
     S.conv = 1;
   } else if (S.iters >= max_iter) {
     S.conv = 1;
@@ -2238,6 +2239,18 @@ __global__ void k_dav_reduce1(const Item* __restrict__ items, const double* __re
   } else if (S.rnorm < olsen_below) {
     S.olsen = 1;
   }
+}
+// (where no item has a P-space)
+__global__ void k_dav_reduce1(const Item* __restrict__ items, const double* __restrict__ part,
+                              DavState* st, int ibase, int nitem, double tol, int max_iter,
+                              double olsen_below) {
+  int it = blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);  // a wave per item
+  if (it >= nitem) return;
+  it += ibase;
+  const Item& I = items[it];
+  DavState& S = st[it];
+  if (S.conv || S.olsen) return;
+  dav_test(I, S, wave_parts(part, I), tol, max_iter, olsen_below);
 }
 
 // t -= sum_i coef_i V_i ; partial sums of V_i . t and |t|^2 (second pass).
@@ -2576,61 +2589,99 @@ __global__ void __launch_bounds__(256) k_pspace_select(const Item* __restrict__ 
   }
 }
 
-// One block per item: build H_PP (packed lower triangle in LDS) and reduce
-// it to tridiagonal form by Householder reflections, H_PP = Q T Q^T (T:
-// diagonal d, off-diagonal e; Q accumulated explicitly for a P-space).
-// The lowest eigenvalue of T comes from multisection on Sturm counts (every
-// thread evaluates one point per round), its eigenvector from inverse
-// iteration; the guess is Q z.  A CASCI of at most kMaxPspace determinants
-// is always solved from its whole-space block (the guess is then the exact
-// ground state, whatever pmax); larger ones use a P-space of
-// min(pmax, ndet / kPspaceRatio) determinants, since the reduction costs
-// about P^3 against a Davidson iteration's ndet npair^2; below kPspaceMinDim
-// (where small P-spaces can also steer the solver to an excited root) they
-// start from `nunit` lowest-diagonal unit vectors with the diagonal
-// correction.  The dense vector is always added.  The reduction runs in
-// five instantiations over host-built item lists: P-spaces of larger
-// CASCIs (512 threads, Q in LDS; sized for 112 and for 76), and CASCIs
-// solved from their whole space of at most 36 determinants (one wave),
-// 37..100 and 101..112 (256 threads), which need no Q; the sizes let
-// several blocks share a CU.
+// P-space reduction, one block per item: H_PP is reduced to tridiagonal form by
+// Householder reflections, H_PP = Q T Q^T (T: diagonal d, off-diagonal e; Q
+// accumulated explicitly for a P-space of a larger CASCI).  The lowest
+// eigenvalue of T comes from multisection (every thread tests one point per
+// round), its eigenvector from inverse iteration; the guess is Q z.  A CASCI of
+// at most kMaxPspace determinants is always solved from its whole-space block
+// (the guess is then the exact ground state, whatever pmax); larger ones use a
+// P-space of min(pmax, ndet / kPspaceRatio) determinants, since the reduction
+// costs about P^3 against a Davidson iteration's ndet npair^2; below
+// kPspaceMinDim (where small P-spaces can also steer the solver to an excited
+// root) they start from `nunit` lowest-diagonal unit vectors with the diagonal
+// correction.  The dense vector is always added.  Six instantiations run over
+// host-built item lists: three sizes, each for a P-space and for a whole
+// space.
 
-// Solve (theta - T) z = y for symmetric tridiagonal T (diagonal d, off-
-// diagonal e) by an LDL^T sweep without pivoting, pivots kept at |p| >= floor
-// (1e-8 for the correction, like the diagonal one; a tiny relative floor for
-// inverse iteration).  In the Davidson iteration theta never exceeds the
-// lowest eigenvalue of T, so theta - T is negative semidefinite and the sweep
-// is stable.  z may alias y.
+// (theta - T) z = y for symmetric tridiagonal T (diagonal d, off-diagonal e) by
+// one wave: a twisted factorisation without pivoting, lanes below 32 from the
+// first row and the others from the last, meeting in row n / 2 - which halves
+// the chain of dependent divides.  Pivots are kept at |p| >= floor (1e-8 for
+// the correction, like the diagonal one; a tiny relative floor for inverse
+// iteration).  In the Davidson iteration theta never exceeds the lowest
+// eigenvalue of T, so theta - T is negative semidefinite and the sweep is
+// stable.
 __device__ inline double floored(double p, double floor) {
   return fabs(p) < floor ? (p < 0 ? -floor : floor) : p;
 }
-__device__ inline void tridiag_shift_solve(const double* d, const double* e, int n, double theta,
-                                           const double* y, double* z, double* piv,
-                                           double floor) {
-  double p = floored(theta - d[0], floor);
-  piv[0] = p;
-  z[0] = y[0];
-  for (int i = 1; i < n; ++i) {
-    const double l = -e[i - 1] / p;           // multiplier of the off-diagonal (-e)
-    p = floored((theta - d[i]) + l * e[i - 1], floor);
-    piv[i] = p;
-    z[i] = y[i] - l * z[i - 1];
-  }
-  z[n - 1] = z[n - 1] / piv[n - 1];
-  for (int i = n - 2; i >= 0; --i) z[i] = (z[i] + e[i] * z[i + 1]) / piv[i];
+// 1/x to about one unit in the last place: the hardware's estimate and two
+// Newton steps (a third of the latency of a divide).
+__device__ inline double newton_rcp(double x) {
+  double y = __builtin_amdgcn_rcp(x);
+  y = fma(fma(-x, y, 1.0), y, y);
+  return fma(fma(-x, y, 1.0), y, y);
 }
-
-__device__ inline int sturm_count(const double* d, const double* e, int n, double x) {
-  int cnt = 0;
-  double q = d[0] - x;
-  if (q == 0.0) q = -1e-300;
-  cnt += q < 0.0;
-  for (int i = 1; i < n; ++i) {
-    q = (d[i] - x) - e[i - 1] * e[i - 1] / q;
-    if (q == 0.0) q = -1e-300;
-    cnt += q < 0.0;
+// LDS written by one lane of a wave and read by another
+__device__ inline void wave_lds_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+struct TwistedTri {      // of one lane
+  int n, steps;          // rows, rows of this half
+  double l0, l1;         // multipliers of the middle row with either half
+};
+// ll, ip, bb (LDS, n each): multiplier with the row before, 1/pivot and
+// off-diagonal over pivot.  n >= 2; all 64 lanes.
+__device__ inline TwistedTri twisted_factor(const double* d, const double* e, int n, double theta,
+                                            double floor, double* ll, double* ip, double* bb) {
+  const int back = (threadIdx.x >> 5) & 1, mid = n / 2;
+  TwistedTri T;
+  T.n = n;
+  T.steps = back ? n - 1 - mid : mid;
+  double l = 0.0, em = 0.0;
+  for (int s = 0; s < mid; ++s) {
+    // (past its last row the back half works on a row of the front half, unused)
+    const int i = back ? n - 1 - s : s;
+    const double p = floored((theta - d[i]) + l * em, floor);
+    const double y = newton_rcp(p), en = e[back ? max(i - 1, 0) : i];
+    if (s < T.steps) {
+      ll[i] = l;
+      ip[i] = y;
+      bb[i] = en * y;
+      em = en;
+      l = -en * y;
+    }
   }
-  return cnt;
+  const double c = l * em;
+  T.l0 = lane_value(l, 0);
+  T.l1 = lane_value(l, 32);
+  const double p = floored((theta - d[mid]) + (lane_value(c, 0) + lane_value(c, 32)), floor);
+  ip[mid] = newton_rcp(p);
+  wave_lds_fence();
+  return T;
+}
+// z (LDS) on entry y, on return the solution.
+__device__ inline void twisted_solve(const TwistedTri& T, const double* ll, const double* ip,
+                                     const double* bb, double* z) {
+  const int back = (threadIdx.x >> 5) & 1, n = T.n, mid = n / 2;
+  const int i0 = back ? n - 1 : 0, di = back ? -1 : 1;
+  double v = 0.0;
+#pragma unroll 4
+  for (int s = 0; s < T.steps; ++s) {
+    const int i = i0 + di * s;
+    v = z[i] - ll[i] * v;
+    z[i] = v;
+  }
+  v = ((z[mid] - T.l0 * lane_value(v, 0)) - T.l1 * lane_value(v, 32)) * ip[mid];
+  z[mid] = v;
+#pragma unroll 4
+  for (int s = T.steps - 1; s >= 0; --s) {
+    const int i = i0 + di * s;
+    v = z[i] * ip[i] + bb[i] * v;
+    z[i] = v;
+  }
+  wave_lds_fence();
 }
 
 // Guess of the CASCIs without a P-space, one 256-thread block per item of
@@ -2677,253 +2728,374 @@ __global__ void __launch_bounds__(256) k_pspace_guess(const Item* __restrict__ i
   }
 }
 
-// One block of NT threads per item of plist (absolute item indices).  PMAX
-// bounds the P-space held in LDS; EXACT: the items whose P-space is their
-// whole space (their guess is exact, so Q is not formed).
-template <int PMAX, int NT, bool EXACT>
-__global__ void __launch_bounds__(NT) k_pspace_eigen(
+// f(integral_constant 0), ..., f(integral_constant N - 1)
+template <int N, class F>
+__device__ inline void static_for(F&& f) {
+  if constexpr (N > 0) {
+    static_for<N - 1>(f);
+    f(std::integral_constant<int, N - 1>{});
+  }
+}
+// Minimum over the 16 lanes of a row, in every lane of it.
+__device__ inline double row_min(double x) {
+  x = fmin(x, dpp_move<0xB1>(x));
+  x = fmin(x, dpp_move<0x4E>(x));
+  x = fmin(x, dpp_move<0x141>(x));
+  return fmin(x, dpp_move<0x140>(x));
+}
+
+// H_PP of the items of plist, lower triangle, into the rows of pQ that Q takes
+// later.  Grid (items, blocks of kMatrixElems elements of the largest P-space
+// of the class): an element is a chain of loads (strings, orbitals,
+// integrals), so it needs many threads; in the reduction's own block it took
+// 28 us at n = 76 and 37 us at n = 112.
+constexpr int kMatrixElems = 512;
+__global__ void __launch_bounds__(256) k_pspace_matrix(
     const Item* __restrict__ items, const int32_t* __restrict__ plist,
     const ItemHam* __restrict__ hams, const double* __restrict__ diag,
+    const int32_t* __restrict__ pidx, double* __restrict__ pQ, int pmax) {
+  constexpr int PM = kMaxPspace;
+  __shared__ uint64_t sa[PM], sb[PM];
+  const int it = plist[blockIdx.x];
+  const Item& I = items[it];
+  const int n = pspace_dim(I.ndet, pmax), t = threadIdx.x;
+  const int x0 = blockIdx.y * kMatrixElems, x1 = min(x0 + kMatrixElems, n * (n + 1) / 2);
+  if (I.ndet == 1 || x0 >= x1) return;
+  const int32_t* __restrict__ idx = pidx + (int64_t)it * PM;
+  for (int k = t; k < n; k += 256) {
+    uint64_t ma, mb;
+    det_strings(I, idx[k], ma, mb);  // an address of this item: 0 <= idx < ndet
+    sa[k] = ma;
+    sb[k] = mb;
+  }
+  __syncthreads();
+  const ItemHam& H = hams[I.ham];
+  double* __restrict__ A = pQ + (int64_t)it * PM * PM;
+  for (int x = x0 + t; x < x1; x += 256) {
+    int i = (int)((sqrt(8.0 * x + 1.0) - 1.0) * 0.5);
+    while ((i + 1) * (i + 2) / 2 <= x) ++i;
+    while (i * (i + 1) / 2 > x) --i;
+    const int j = x - i * (i + 1) / 2;
+    A[i * PM + j] = (i == j) ? diag[I.off + idx[i]] : sc_offdiag(H, sa[i], sb[i], sa[j], sb[j]);
+  }
+}
+
+// One block per item of plist (absolute item indices) with a P-space of at
+// most 16 NB determinants, its matrix in the item's rows of pQ.  EXACT: the
+// P-space is the whole space; the guess is exact and needs no correction, so
+// Q and T are not formed or stored: u = Q z comes from the reflectors, kept
+// in LDS.
+//
+// The block is a chain of n steps, so what counts is the latency of a step.
+// The whole symmetric matrix and Q sit in registers, dealt cyclically over 16
+// rows x 16 columns of threads: thread (r, c) holds rows r + 16 i, columns
+// c + 16 j.  A DPP row of 16 lanes then holds complete matrix rows, so the
+// products B v and Q v end in DPP sums, and a step has one barrier: B v and
+// the next column go round through LDS together, and every thread brings
+// that column up to date for itself.  Q takes each reflector in the same step
+// (Q <- Q - (Q v) beta v^T).  Done columns drop out 16 at a time (kb
+// and the register indices are constants).  A wave per SIMD:
+// more waves repeat the step's scalar part and its LDS reads.
+// A matrix packed in LDS with Q in global memory, five barriers per step and
+// divides on the eigenvalue's chains took 446 us at n = 76 and 956 us at 112;
+// this form with the matrix from k_pspace_matrix takes 106 and 195 us, and
+// 0.35 ms instead of 0.69 for the 100-determinant CASCIs of an expansion.
+template <int NB, bool EXACT>
+__global__ void __launch_bounds__(256, EXACT ? 2 : 1) k_pspace_eigen(
+    const Item* __restrict__ items, const int32_t* __restrict__ plist,
     const int32_t* __restrict__ pidx, double* __restrict__ pQ, double* __restrict__ pT, double* V,
     int64_t ntot, DavState* st, int pmax) {
-  static_assert(NT >= PMAX && NT % 64 == 0, "a thread per P row");
-  static_assert(EXACT || NT / 4 >= PMAX, "four threads per column when forming Q");
+  constexpr int PMAX = 16 * NB, NT = 256;
   constexpr int PM = kMaxPspace;  // stride of the per-item arrays in global memory
-  __shared__ double A[PMAX * (PMAX + 1) / 2];
-  __shared__ uint64_t sa[PMAX], sb[PMAX];
-  __shared__ double vv[PMAX], pw[PMAX], dd[PMAX], ee[PMAX], beta[PMAX], zz[PMAX], piv[PMAX];
-  __shared__ double lo_hi[2];
-  __shared__ int cnt[NT];
+  static_assert(PMAX <= PM && PMAX <= NT, "a thread per P row");
+  __shared__ double refl[EXACT ? PMAX * (PMAX - 1) / 2 : 1], beta[EXACT ? PMAX : 1];
+  __shared__ double pv[2][PMAX], xo[2][PMAX], dd[PMAX], ee[PMAX], es[PMAX], zz[PMAX];
+  __shared__ double ll[PMAX], ip[PMAX], bb[PMAX], lo_hi[2];
+  __shared__ int neg[NT];
   const int it = plist[blockIdx.x];
   const Item& I = items[it];
   DavState& S = st[it];
-  const int t = threadIdx.x, lane = t & 63;
+  const int t = threadIdx.x, r = t >> 4, c = t & 15;
   const int64_t nd = I.ndet;
   const int32_t* __restrict__ idx = pidx + (int64_t)it * PM;
   const int n = pspace_dim(nd, pmax);
   // the list holds only this class (checked again: a mismatch would overrun LDS)
   if (nd == 1 || n == 0 || n > PMAX || (nd == n) != EXACT) return;
-  const ItemHam& H = hams[I.ham];
-  // Q is accumulated in place in the item's output rows (L2-resident):
-  // in LDS it would hold the CU to one workgroup
   double* __restrict__ Q = pQ + (int64_t)it * PM * PM;
-  for (int k = t; k < n; k += NT) {
-    const int e = idx[k];  // an address of this item: 0 <= e < ndet
-    uint64_t ma, mb;
-    det_strings(I, e, ma, mb);
-    sa[k] = ma;
-    sb[k] = mb;
-  }
-  __syncthreads();
-  auto L = [](int i, int j) { return i >= j ? i * (i + 1) / 2 + j : j * (j + 1) / 2 + i; };
-  // the packed lower triangle, its elements dealt evenly over the threads
-  // (element x is row i, column x - i(i+1)/2)
-  for (int x = t; x < n * (n + 1) / 2; x += NT) {
-    int i = (int)((sqrt(8.0 * x + 1.0) - 1.0) * 0.5);
-    while ((i + 1) * (i + 2) / 2 <= x) ++i;
-    while (i * (i + 1) / 2 > x) --i;
-    const int j = x - i * (i + 1) / 2;
-    A[x] = (i == j) ? diag[I.off + idx[i]] : sc_offdiag(H, sa[i], sb[i], sa[j], sb[j]);
-  }
-  __syncthreads();
+  double a[NB][NB], q[NB][NB];  // rows and columns >= n of a are zero
+#pragma unroll
+  for (int i = 0; i < NB; ++i)
+#pragma unroll
+    for (int j = 0; j < NB; ++j) {
+      const int row = r + 16 * i, col = c + 16 * j;
+      const int hi = max(row, col), lo = min(row, col);
+      const double x = Q[min(hi, n - 1) * PM + min(lo, n - 1)];
+      a[i][j] = hi < n ? x : 0.0;
+      q[i][j] = row == col ? 1.0 : 0.0;
+    }
+  if (t < PMAX) ee[t] = 0.0;
+  // offset of reflector k's row x (x = k + 1 .. PMAX - 1) in refl
+  auto refl_at = [](int k) { return k * (2 * PMAX - k - 1) / 2 - (k + 1); };
 
-  // ---- Householder reduction: step k annihilates A[k+2.., k].  The two
-  // dot products of a step are formed by every wave for itself (the wave sum
-  // leaves the same value in every lane of every wave), so a
-  // step needs three block barriers.
-  for (int k = 0; k + 2 < n; ++k) {
-    const int m = n - k - 1;
-    double sq = 0.0;
-    for (int i = lane; i < m; i += 64) {
-      const double xi = A[L(k + 1 + i, k)];
-      sq += xi * xi;
-    }
-    const double sig = wave_sum64(sq);
-    const double x0 = A[L(k + 1, k)];
-    const double sg = sqrt(sig);
-    const double alpha = x0 >= 0.0 ? -sg : sg;
-    const double bt = sig > 0.0 ? 1.0 / (sig - x0 * alpha) : 0.0;
-    if (t < m) vv[t] = t == 0 ? x0 - alpha : A[L(k + 1 + t, k)];
-    if (t == 0) {
-      ee[k] = sig > 0.0 ? alpha : x0;
-      beta[k] = bt;
-    }
-    __syncthreads();
-    if (bt != 0.0) {
-      // p = beta B v, four threads per row of the trailing block B
-      for (int row0 = 0; row0 < m; row0 += NT / 4) {
-        const int row = row0 + (t >> 2), part = t & 3;
-        double acc = 0.0;
-        if (row < m) {
-#pragma unroll 4
-          for (int j = part; j < m; j += 4) acc += A[L(k + 1 + row, k + 1 + j)] * vv[j];
+  // ---- Householder reduction: step k annihilates A[k+2.., k].  vr, vc: the
+  // column below its diagonal, then the reflector, zero up to row k.
+  if (c == 0) {
+#pragma unroll
+    for (int i = 0; i < NB; ++i) xo[1][r + 16 * i] = a[i][0];
+  }
+  __syncthreads();
+  double vr[NB], vc[NB], x0 = xo[1][1];
+#pragma unroll
+  for (int i = 0; i < NB; ++i) {
+    vr[i] = r + 16 * i > 0 ? xo[1][r + 16 * i] : 0.0;
+    vc[i] = c + 16 * i > 0 ? xo[1][c + 16 * i] : 0.0;
+  }
+  static_for<NB>([&](auto block) {
+    constexpr int kb = decltype(block)::value;
+    for (int kk = 0; kk < 16; ++kk) {
+      const int k = 16 * kb + kk;
+      if (k + 2 >= n) break;  // uniform
+      constexpr double kTiny = 1e-280;  // |x|^2 of a column that is done
+      double sq = 0.0;
+#pragma unroll
+      for (int j = kb; j < NB; ++j) sq += vc[j] * vc[j];
+      const double sig = row_sum(sq);
+      const bool some = sig > kTiny;  // uniform
+      // |x| = sig / sqrt(sig): the estimate of 1/sqrt and two Newton steps
+      const double ss = some ? sig : 1.0;
+      double y = __builtin_amdgcn_rsq(ss);
+      double g = ss * y, h = 0.5 * y;
+      double e1 = fma(-h, g, 0.5);
+      g = fma(g, e1, g);
+      h = fma(h, e1, h);
+      g = fma(fma(-g, g, ss), h, g);
+      const double alpha = x0 >= 0.0 ? -g : g;
+      const double bt = some ? newton_rcp(ss - x0 * alpha) : 0.0;
+      const double v1 = some ? x0 - alpha : 0.0;
+      if (t == 0) ee[k] = some ? alpha : x0;
+#pragma unroll
+      for (int j = kb; j < NB; ++j)
+        if (j <= kb + 1) {
+          if (c + 16 * j == k + 1) vc[j] = v1;
+          if (r + 16 * j == k + 1) vr[j] = v1;
         }
-        acc += __shfl_xor(acc, 1, 64);
-        acc += __shfl_xor(acc, 2, 64);
-        if (row < m && part == 0) pw[row] = bt * acc;
+      if constexpr (EXACT) {
+        const int o = refl_at(k);
+        if (r == 0) {
+#pragma unroll
+          for (int j = kb; j < NB; ++j)
+            if (c + 16 * j > k) refl[o + c + 16 * j] = vc[j];
+        }
+        if (t == 0) beta[k] = bt;
+      }
+      // p = beta B v and beta Q v
+      double pr[NB], qr[NB];
+#pragma unroll
+      for (int i = 0; i < NB; ++i) {
+        double s0 = 0.0, s1 = 0.0;
+#pragma unroll
+        for (int j = kb; j < NB; ++j) {
+          if (i >= kb) s0 += a[i][j] * vc[j];
+          if (!EXACT) s1 += q[i][j] * vc[j];
+        }
+        pr[i] = i >= kb ? bt * row_sum(s0) : 0.0;
+        qr[i] = !EXACT ? bt * row_sum(s1) : 0.0;
+      }
+      // p and column k + 1 as it was before this step
+      double* __restrict__ pb = pv[kk & 1];
+      double* __restrict__ xb = xo[kk & 1];
+      if (c == 0) {
+#pragma unroll
+        for (int i = kb; i < NB; ++i) pb[r + 16 * i] = pr[i];
+      }
+      if (c == ((kk + 1) & 15)) {
+#pragma unroll
+        for (int i = kb; i < NB; ++i)
+          xb[r + 16 * i] = kk == 15 && kb + 1 < NB ? a[i][kb + 1 < NB ? kb + 1 : kb] : a[i][kb];
       }
       __syncthreads();
-      double pv = 0.0;
-      for (int i = lane; i < m; i += 64) pv += pw[i] * vv[i];
-      const double Kc = 0.5 * bt * wave_sum64(pv);
-      // B -= v w^T + w v^T with w = p - K v (lower triangle), rows strided
-      // by 64, columns by 8
-      for (int i = t >> 3; i < m; i += NT / 8) {
-        const double vi = vv[i], wi = pw[i] - Kc * vi;
-#pragma unroll 4
-        for (int j = t & 7; j <= i; j += 8)
-          A[L(k + 1 + i, k + 1 + j)] -= vi * (pw[j] - Kc * vv[j]) + wi * vv[j];
+      double wc[NB], xc[NB], xr[NB], kv = 0.0;
+#pragma unroll
+      for (int j = kb; j < NB; ++j) {
+        wc[j] = pb[c + 16 * j];
+        xc[j] = xb[c + 16 * j];
+        xr[j] = xb[r + 16 * j];
+        kv += wc[j] * vc[j];
       }
-    }
-    // keep v in column k below the diagonal (A[k+1+i, k] = v_i)
-    if (t < m) A[L(k + 1 + t, k)] = vv[t];
-    __syncthreads();
-  }
-  for (int i = t; i < n; i += NT) {
-    dd[i] = A[L(i, i)];
-    if (i == n - 2) ee[i] = A[L(n - 1, n - 2)];
-  }
-  if (t == 0 && n >= 1) ee[n - 1] = 0.0;
-  // A CASCI whose P block is its whole space converges on this guess, so it
-  // needs no correction and no explicit Q: the guess Q z is formed from the
-  // reflectors below.
-  // ---- Q = H_0 H_1 ... H_{n-3}, accumulated backwards from the identity
-  if constexpr (!EXACT) {
-  for (int x = t; x < n * n; x += NT) Q[(x / n) * PM + (x % n)] = (x / n == x % n) ? 1.0 : 0.0;
-  __syncthreads();
-  for (int k = n - 3; k >= 0; --k) {
-    const int m = n - k - 1;
-    const double bt = beta[k];
-    if (bt == 0.0) continue;  // uniform
-    // s_j = sum_i v_i Q[k+1+i][j] for columns j > k (columns <= k are still
-    // those of the identity there); four threads per column
-    {
-      const int col = k + 1 + (t >> 2), part = t & 3;
-      double acc = 0.0;
-      if (col < n) {
-#pragma unroll 4
-        for (int i = part; i < m; i += 4) acc += A[L(k + 1 + i, k)] * Q[(k + 1 + i) * PM + col];
+      const double p1 = pb[k + 1];
+      // B -= v w^T + w v^T with w = p - K v (rows up to k of v are zero, so w
+      // there does no harm)
+      const double Kc = 0.5 * bt * row_sum(kv);
+      const double w1 = fma(-Kc, v1, p1);
+      double wr[NB], nr[NB], nc[NB];
+#pragma unroll
+      for (int j = kb; j < NB; ++j) {
+        // explicit operations: the row and the column copies of v have to
+        // agree to the last bit, a difference would grow by |B| per step
+        wc[j] = fma(-Kc, vc[j], wc[j]);
+        wr[j] = fma(-Kc, vr[j], pr[j]);
+        // column k + 1 after this step
+        nc[j] = c + 16 * j > k + 1 ? fma(-vc[j], w1, fma(-wc[j], v1, xc[j])) : 0.0;
+        nr[j] = r + 16 * j > k + 1 ? fma(-vr[j], w1, fma(-wr[j], v1, xr[j])) : 0.0;
       }
-      acc += __shfl_xor(acc, 1, 64);
-      acc += __shfl_xor(acc, 2, 64);
-      if (col < n && part == 0) pw[col - k - 1] = bt * acc;
-    }
-    __syncthreads();
-    // element x = i m + j of the trailing block, x = t, t + NT, ... (the
-    // row and column step by NT / m and NT % m)
-    {
-      const int di = NT / m, dj = NT % m;
-      int i = t / m, j = t % m;
-      while (i < m) {
-        Q[(k + 1 + i) * PM + (k + 1 + j)] -= A[L(k + 1 + i, k)] * pw[j];
-        i += di;
-        j += dj;
-        if (j >= m) {
-          j -= m;
-          ++i;
+      const double xs = kk >= 14 && kb + 1 < NB ? nc[kb + 1 < NB ? kb + 1 : kb] : nc[kb];
+      x0 = lane_value(xs, (k + 2) & 15);
+#pragma unroll
+      for (int i = 0; i < NB; ++i)
+#pragma unroll
+        for (int j = kb; j < NB; ++j) {
+          if (i >= kb) a[i][j] -= vr[i] * wc[j] + wr[i] * vc[j];
+          if (!EXACT) q[i][j] -= qr[i] * vc[j];
         }
+#pragma unroll
+      for (int j = kb; j < NB; ++j) {
+        vc[j] = nc[j];
+        vr[j] = nr[j];
       }
     }
-    __syncthreads();
-  }
-  }
+  });
+  if (t == 0) ee[n - 2] = x0;
+#pragma unroll
+  for (int i = 0; i < NB; ++i)
+    if (r == c) dd[r + 16 * i] = a[i][i];
+  __syncthreads();
   // ---- lowest eigenvalue of T: multisection on [lo, hi] (Gershgorin)
+  double glo = 1e300, ghi = 1e300, gsc = 0.0;
+  for (int i = c; i < n; i += 16) {
+    const double el = i > 0 ? fabs(ee[i - 1]) : 0.0, er = fabs(ee[i]);
+    glo = fmin(glo, dd[i] - (el + er));
+    ghi = fmin(ghi, -(dd[i] + (el + er)));
+    gsc = fmin(gsc, -(fabs(dd[i]) + 2.0 * er));
+  }
+  glo = row_min(glo);  // (DPP: with every lane active)
+  ghi = -row_min(ghi);
+  const double scale = -row_min(gsc);
+  __syncthreads();
   if (t == 0) {
-    double lo = 1e300, hi = -1e300;
-    for (int i = 0; i < n; ++i) {
-      const double rr = (i > 0 ? fabs(ee[i - 1]) : 0.0) + (i + 1 < n ? fabs(ee[i]) : 0.0);
-      lo = fmin(lo, dd[i] - rr);
-      hi = fmax(hi, dd[i] + rr);
-    }
-    lo_hi[0] = lo;
-    lo_hi[1] = hi;
+    lo_hi[0] = glo;
+    lo_hi[1] = ghi;
+  }
+  if (t < PMAX) {
+    es[t] = t > 0 && t < n ? ee[t - 1] * ee[t - 1] : 0.0;
+    // rows past n keep the sign of the minor before them
+    if (t >= n) dd[t] = ghi + (1.0 + scale);
   }
   __syncthreads();
-  // rounds of NT points narrow the interval by NT^rounds >= 1.8e16, to the
-  // rounding level of the spectrum (512^6, 256^7, 64^9)
-  constexpr int kRounds = NT >= 512 ? 6 : NT >= 256 ? 7 : 9;
-  for (int round = 0; round < kRounds; ++round) {
+  // 7 rounds of 256 points narrow the interval by 256^7 >= 1.8e16, to the
+  // rounding level of the spectrum
+  for (int round = 0; round < 7; ++round) {
     const double lo = lo_hi[0], hi = lo_hi[1];
     const double x = lo + (hi - lo) * (double)(t + 1) / (double)NT;
-    const int c = sturm_count(dd, ee, n, x);
-    // the first point with at least one eigenvalue below it (the count at
-    // the previous point is the previous thread's)
+    // an eigenvalue at or below x: a leading minor of T - x that is not
+    // positive.  The minors' own recurrence has one multiply-add on its chain
+    // per row (their ratios have a divide); rescaled every eight rows.
+    double pm = 0.0, p = 1.0, mn = 1.0;
+    for (int i0 = 0; i0 < n; i0 += 8) {
+#pragma unroll
+      for (int u = 0; u < 8; ++u) {
+        const double pn = (dd[i0 + u] - x) * p - es[i0 + u] * pm;
+        pm = p;
+        p = pn;
+        mn = fmin(mn, p);
+      }
+      const int ex = -__builtin_amdgcn_frexp_exp(fmax(fabs(p), fabs(pm)));
+      p = __builtin_amdgcn_ldexp(p, ex);
+      pm = __builtin_amdgcn_ldexp(pm, ex);
+    }
+    const int below = !(mn > 0.0);
+    // the first point with an eigenvalue at or below it (the answer at the
+    // previous point is the previous thread's)
+    neg[t] = below;
     __syncthreads();
-    cnt[t] = c;
-    __syncthreads();
-    if (c >= 1 && (t == 0 || cnt[t - 1] == 0)) {
+    if (below && (t == 0 || neg[t - 1] == 0)) {
       lo_hi[0] = lo + (hi - lo) * (double)t / (double)NT;
       lo_hi[1] = x;
     }
     __syncthreads();
   }
   const double lam0 = 0.5 * (lo_hi[0] + lo_hi[1]);
-  // ---- eigenvector of T for lam0: inverse iteration, (lam0 - T) z = z, with
-  // pivots floored at 1e-15 of the spectrum's scale
-  if (t == 0) {
-    double scale = 0.0;
-    for (int i = 0; i < n; ++i) scale = fmax(scale, fabs(dd[i]) + 2.0 * fabs(ee[i]));
-    const double floor = 1e-15 * fmax(scale, 1e-300);
-    for (int i = 0; i < n; ++i) zz[i] = 1.0;
+  // ---- eigenvector of T for lam0 by one wave: inverse iteration,
+  // (lam0 - T) z = z, with pivots floored at 1e-15 of the spectrum's scale
+  if (t < 64) {
+    const TwistedTri T =
+        twisted_factor(dd, ee, n, lam0, 1e-15 * fmax(scale, 1e-285), ll, ip, bb);
+    for (int i = t; i < n; i += 64) zz[i] = 1.0;
+    wave_lds_fence();
     for (int rep = 0; rep < 3; ++rep) {
-      tridiag_shift_solve(dd, ee, n, lam0, zz, zz, piv, floor);
+      twisted_solve(T, ll, ip, bb, zz);
       double s2 = 0.0;
-      for (int i = 0; i < n; ++i) s2 += zz[i] * zz[i];
-      const double inv = 1.0 / sqrt(s2);
-      for (int i = 0; i < n; ++i) zz[i] *= inv;
+      for (int i = t; i < n; i += 64) s2 += zz[i] * zz[i];
+      const double inv = 1.0 / sqrt(wave_sum64(s2));
+      for (int i = t; i < n; i += 64) zz[i] *= inv;
+      wave_lds_fence();
+    }
+    if constexpr (EXACT) {
+      // u = H_0 (H_1 (... (H_{n-3} z))), H_k = I - beta_k v_k v_k^T
+      static_assert(!EXACT || PMAX <= 128, "two rows per lane");
+      double u0 = t < n ? zz[t] : 0.0, u1 = t + 64 < n ? zz[t + 64] : 0.0;
+      auto v_at = [&](int k, int row) {
+        return row > k && row < n ? refl[refl_at(k) + row] : 0.0;
+      };
+      double a0 = 0.0, a1 = 0.0;
+      if (n > 2) {
+        a0 = v_at(n - 3, t);
+        a1 = v_at(n - 3, t + 64);
+      }
+      for (int k = n - 3; k >= 0; --k) {
+        const double b0 = a0, b1 = a1, bt = beta[k];
+        if (k > 0) {
+          a0 = v_at(k - 1, t);
+          a1 = v_at(k - 1, t + 64);
+        }
+        const double sc = bt * wave_sum64(b0 * u0 + b1 * u1);
+        u0 -= sc * b0;
+        u1 -= sc * b1;
+      }
+      if (t < n) pv[0][t] = u0;
+      if (t + 64 < n) pv[0][t + 64] = u1;
     }
   }
   __syncthreads();
-  // ---- outputs: T and the guess vectors (Q is in place)
+  // ---- outputs: T, Q and the guess vectors
   if constexpr (!EXACT) {
     double* __restrict__ To = pT + (int64_t)it * 2 * PM;
-    for (int i = t; i < n; i += NT) {
-      To[i] = dd[i];
-      To[PM + i] = ee[i];
+    if (t < n) {
+      To[t] = dd[t];
+      To[PM + t] = ee[t];
     }
     // u = Q z (row k: P position k)
-    if (t < n) {
+#pragma unroll
+    for (int i = 0; i < NB; ++i) {
       double u = 0.0;
-      for (int j = 0; j < n; ++j) u += Q[t * PM + j] * zz[j];
-      vv[t] = u;
+#pragma unroll
+      for (int j = 0; j < NB; ++j) {
+        const int row = r + 16 * i, col = c + 16 * j;
+        u += col < n ? q[i][j] * zz[col] : 0.0;
+        if (row < n && col < n) Q[row * PM + col] = q[i][j];
+      }
+      u = row_sum(u);
+      if (c == 0) pv[0][r + 16 * i] = u;
     }
-  } else if (t < 64) {  // EXACT
-    // u = H_0 (H_1 (... (H_{n-3} z))), H_k = I - beta_k v_k v_k^T with v_k in
-    // column k of A below the diagonal; one wave
-    for (int k = n - 3; k >= 0; --k) {
-      const double bt = beta[k];
-      if (bt == 0.0) continue;  // uniform
-      const int m = n - k - 1;
-      double sp = 0.0;
-      for (int i = lane; i < m; i += 64) sp += A[L(k + 1 + i, k)] * zz[k + 1 + i];
-      const double sc = bt * wave_sum64(sp);
-      for (int i = lane; i < m; i += 64) zz[k + 1 + i] -= sc * A[L(k + 1 + i, k)];
-      __builtin_amdgcn_wave_barrier();  // the next step reads other lanes' updates
-    }
-    for (int i = lane; i < n; i += 64) vv[i] = zz[i];
+    __syncthreads();
   }
-  __syncthreads();
   // guess 0: the P-space eigenvector u; guess 1: the dense vector
   // r = sign/sqrt(ndet) minus its component on u (u lives on the P block),
   // |r - c u|^2 = 1 - c^2
+  const double* __restrict__ u = pv[0];
   double* __restrict__ v0 = V + I.off;
-  for (int k = t; k < n; k += NT) v0[idx[k]] = vv[k];
-  if (t == 0) {
-    const double rs = 1.0 / sqrt((double)nd);
-    double c0 = 0.0;
-    for (int k = 0; k < n; ++k) c0 += vv[k] * hash_sign(idx[k]) * rs;
-    zz[0] = c0;
-    zz[2] = 1.0 - c0 * c0;
-  }
-  __syncthreads();
-  const bool dense = nd > n && zz[2] > 1e-6;
+  if (t < n) v0[idx[t]] = u[t];
+  const double rs = 1.0 / sqrt((double)nd);
+  double c0 = 0.0;
+  for (int k = c; k < n; k += 16) c0 += u[k] * hash_sign(idx[k]) * rs;
+  c0 = row_sum(c0);
+  const double rest = 1.0 - c0 * c0;
+  const bool dense = nd > n && rest > 1e-6;
   if (dense) {
-    const double rs = 1.0 / sqrt((double)nd), rn = 1.0 / sqrt(zz[2]);
-    double* __restrict__ vr = V + ntot + I.off;
-    for (int64_t K = t; K < nd; K += NT) vr[K] = hash_sign(K) * rs * rn;
+    const double rn = 1.0 / sqrt(rest);
+    double* __restrict__ v1 = V + ntot + I.off;
+    for (int64_t K = t; K < nd; K += NT) v1[K] = hash_sign(K) * rs * rn;
     __syncthreads();   // the P-block entries below overwrite the dense pass
-    for (int k = t; k < n; k += NT)
-      vr[idx[k]] = (hash_sign(idx[k]) * rs - zz[0] * vv[k]) * rn;
+    if (t < n) v1[idx[t]] = (hash_sign(idx[t]) * rs - c0 * u[t]) * rn;
   }
   if (t == 0) {
     S.m = 0;
@@ -2939,62 +3111,168 @@ __global__ void __launch_bounds__(NT) k_pspace_eigen(
   }
 }
 
-// P-space correction, run after k_dav_residual: on the P block replace the
-// diagonal correction by t_P = Q (theta - T)^-1 Q^T r_P = (theta - H_PP)^-1 r_P,
-// and store the change of the Gram-Schmidt dots V_i . t (i < m) and of |t|^2
-// in pdots[item][0..kMaxSpace] for k_dav_reduce1.
-__global__ void __launch_bounds__(256) k_pspace_correct(const Item* __restrict__ items, int ibase,
-                                                        const int32_t* __restrict__ pidx,
-                                                        const double* __restrict__ pQ,
-                                                        const double* __restrict__ pT, double* V,
-                                                        const double* __restrict__ Sv,
-                                                        int64_t ntot,
-                                                        const DavState* __restrict__ st,
-                                                        double* __restrict__ pdots) {
+// P-space correction and first Gram-Schmidt coefficients, run after
+// k_dav_residual: one block per item with a P-space (the lists of ps), then
+// blocks of one wave per item for the others.  On the P block the diagonal correction
+// is replaced by t_P = Q (theta - T)^-1 Q^T r_P = (theta - H_PP)^-1 r_P, and the
+// change of the dots V_i . t (i < m) and of |t|^2 enters the item's totals.
+//
+// A chain of short steps, so what counts is that each has its loads in flight
+// at once: waves 0..3 hold Q in registers (16 x 16 threads, dealt cyclically)
+// from one pass over it and use it for both products, wave 4 sums the chunk
+// partials and factors theta - T meanwhile.  (A thread per row or column
+// walking Q twice and a serial solve: 18.5 us at n = 76, 28 us at n = 112, and
+// 4.6 us of a reduction after it; now 12.5 and 18.2 us.)
+template <int NB>
+__device__ inline void pspace_products(const double* __restrict__ Qi, int np, double (&q)[NB][NB]) {
+  const int r = (threadIdx.x >> 4) & 15, c = threadIdx.x & 15;
+#pragma unroll
+  for (int i = 0; i < NB; ++i)
+#pragma unroll
+    for (int j = 0; j < NB; ++j) {
+      const int row = r + 16 * i, col = c + 16 * j;
+      const double x = Qi[min(row, np - 1) * kMaxPspace + min(col, np - 1)];
+      q[i][j] = row < np && col < np ? x : 0.0;
+    }
+}
+constexpr int kCorrectThreads = 320;
+__global__ void __launch_bounds__(kCorrectThreads) k_pspace_correct(
+    const Item* __restrict__ items, int ibase, int nitem, PspaceArgs ps, double* V,
+    const double* __restrict__ Sv, int64_t ntot, const double* __restrict__ part, DavState* st,
+    double tol, int max_iter, double olsen_below) {
   constexpr int PM = kMaxPspace;
-  const int it = ibase + blockIdx.x;
+  __shared__ double rr[PM], zz[PM], tn[PM], zp[16][PM], dd[PM], ee[PM], ll[PM], ip[PM], bb[PM];
+  __shared__ double dots[2][kMaxSpace + 1];
+  const int32_t* __restrict__ pidx = ps.pidx;
+  const double* __restrict__ pT = ps.pT;
+  const int t = threadIdx.x, listed = ps.n[0] + ps.n[1] + ps.n[2];
+  int b = blockIdx.x;
+  if (b >= listed) {  // items without a P-space, one per wave
+    const int j = (b - listed) * (kCorrectThreads / 64) + (t >> 6);
+    if (j >= nitem) return;
+    const int i = ibase + j;
+    DavState& S = st[i];
+    if (S.conv || S.olsen || S.np > 0) return;
+    dav_test(items[i], S, wave_parts(part, items[i]), tol, max_iter, olsen_below);
+    return;
+  }
+  int q = 0;
+  while (b >= ps.n[q]) b -= ps.n[q++];
+  const int it = ps.list[q][b];
   const Item& I = items[it];
-  const DavState& S = st[it];
-  if (S.conv || S.np == 0 || S.olsen) return;
-  const int np = S.np, m = S.m, t = threadIdx.x;
+  DavState& S = st[it];
+  if (S.conv || S.olsen || S.np == 0) return;
+  const int np = S.np, m = S.m;
   const double th = S.theta;
-  __shared__ double r[PM], z[PM], dd[PM], ee[PM], piv[PM];
-  const int32_t* __restrict__ idx = pidx + (int64_t)it * PM;
-  const double* __restrict__ Qi = pQ + (int64_t)it * PM * PM;
-  double tnew = 0.0, told = 0.0;
+  double total = 0.0;
+  TwistedTri T{};
+  if (t >= 256) {
+    const int lane = t & 63;
+    for (int i = lane; i < np; i += 64) {
+      dd[i] = pT[(int64_t)it * 2 * PM + i];
+      ee[i] = pT[(int64_t)it * 2 * PM + PM + i];
+    }
+    wave_lds_fence();
+    T = twisted_factor(dd, ee, np, th, 1e-8, ll, ip, bb);
+    total = wave_parts(part, I);
+  }
+  // residual on the P block (a thread per position; the other threads repeat
+  // the last one)
   int e = 0;
-  if (t < np) {
-    e = idx[t];
-    double rv = 0.0;
-    for (int i = 0; i < m; ++i)
-      rv += S.y[i] * (Sv[(int64_t)i * ntot + I.off + e] - th * V[(int64_t)i * ntot + I.off + e]);
-    r[t] = rv;
+  double told = 0.0;
+  if (t < 128) {
+    const int k = min(t, np - 1);
+    e = pidx[(int64_t)it * PM + k];
     told = V[(int64_t)m * ntot + I.off + e];
-    dd[t] = pT[(int64_t)it * 2 * PM + t];
-    ee[t] = pT[(int64_t)it * 2 * PM + PM + t];
-  }
-  __syncthreads();
-  if (t < np) {
-    double zj = 0.0;
-    for (int k = 0; k < np; ++k) zj += Qi[k * PM + t] * r[k];
-    z[t] = zj;
-  }
-  __syncthreads();
-  if (t == 0) tridiag_shift_solve(dd, ee, np, th, z, z, piv, 1e-8);
-  __syncthreads();
-  double acc[kMaxSpace + 1];
+    double rv = 0.0;
+    const bool unrolled = with_space(m, [&](auto mc) {
+      constexpr int M = decltype(mc)::value;
 #pragma unroll
-  for (int i = 0; i <= kMaxSpace; ++i) acc[i] = 0.0;
-  if (t < np) {
-    for (int j = 0; j < np; ++j) tnew += Qi[t * PM + j] * z[j];
-    V[(int64_t)m * ntot + I.off + e] = tnew;
-    const double dl = tnew - told;
-#pragma unroll
-    for (int i = 0; i < kMaxSpace; ++i)
-      if (i < m) acc[i] = V[(int64_t)i * ntot + I.off + e] * dl;
-    acc[kMaxSpace] = tnew * tnew - told * told;
+      for (int i = 0; i < M; ++i)
+        rv += S.y[i] *
+              (Sv[(int64_t)i * ntot + I.off + e] - th * V[(int64_t)i * ntot + I.off + e]);
+    });
+    if (!unrolled)
+      for (int i = 0; i < m; ++i)
+        rv += S.y[i] *
+              (Sv[(int64_t)i * ntot + I.off + e] - th * V[(int64_t)i * ntot + I.off + e]);
+    if (t < PM) rr[t] = t < np ? rv : 0.0;
   }
-  block_reduce_store<kMaxSpace + 1>(acc, m, kMaxSpace, pdots + (int64_t)it * (kMaxSpace + 1));
+  // z = Q^T r, (theta - T)^-1 z, t = Q z
+  auto products = [&](auto nb) {
+    constexpr int NB = decltype(nb)::value;
+    const int r = (t >> 4) & 15, c = t & 15;
+    double q[NB][NB];
+    if (t < 256) pspace_products<NB>(ps.pQ + (int64_t)it * PM * PM, np, q);
+    __syncthreads();
+    if (t < 256) {
+#pragma unroll
+      for (int j = 0; j < NB; ++j) {
+        double s = 0.0;
+#pragma unroll
+        for (int i = 0; i < NB; ++i) s += q[i][j] * rr[r + 16 * i];
+        zp[r][c + 16 * j] = s;
+      }
+    }
+    __syncthreads();
+    if (t < np) {
+      double s = 0.0;
+#pragma unroll
+      for (int u = 0; u < 16; ++u) s += zp[u][t];
+      zz[t] = s;
+    } else if (t < PM) {
+      zz[t] = 0.0;
+    }
+    __syncthreads();
+    if (t >= 256) twisted_solve(T, ll, ip, bb, zz);
+    __syncthreads();
+    if (t < 256) {
+#pragma unroll
+      for (int i = 0; i < NB; ++i) {
+        double s = 0.0;
+#pragma unroll
+        for (int j = 0; j < NB; ++j) s += q[i][j] * zz[c + 16 * j];
+        s = row_sum(s);
+        if (c == 0) tn[r + 16 * i] = s;
+      }
+    }
+    __syncthreads();
+  };
+  if (np <= kPspaceSmall) products(std::integral_constant<int, kPspaceSmall / 16>());
+  else if (np <= kPspaceMid) products(std::integral_constant<int, kPspaceMid / 16>());
+  else products(std::integral_constant<int, PM / 16>());
+  if (t < 128) {
+    const bool in = t < np;
+    const double tnew = in ? tn[t] : 0.0;
+    const double dl = in ? tnew - told : 0.0;
+    if (in) V[(int64_t)m * ntot + I.off + e] = tnew;
+    const double n2 = wave_sum64(in ? tnew * tnew - told * told : 0.0);
+    double* __restrict__ dw = dots[t >> 6];
+    if ((t & 63) == 0) dw[kMaxSpace] = n2;
+    const bool unrolled = with_space(m, [&](auto mc) {
+      constexpr int M = decltype(mc)::value;
+      double x[M > 0 ? M : 1];
+#pragma unroll
+      for (int i = 0; i < M; ++i) x[i] = V[(int64_t)i * ntot + I.off + e] * dl;
+#pragma unroll
+      for (int i = 0; i < M; ++i) {
+        const double s = wave_sum64(x[i]);
+        if ((t & 63) == 0) dw[i] = s;
+      }
+    });
+    if (!unrolled)
+      for (int i = 0; i < m; ++i) {
+        const double s = wave_sum64(V[(int64_t)i * ntot + I.off + e] * dl);
+        if ((t & 63) == 0) dw[i] = s;
+      }
+  }
+  __syncthreads();
+  if (t >= 256) {
+    const int lane = t & 63;
+    if (lane < m) total += dots[0][lane] + dots[1][lane];
+    if (lane == kMaxSpace + 1) total += dots[0][kMaxSpace] + dots[1][kMaxSpace];
+    dav_test(I, S, total, tol, max_iter, olsen_below);
+  }
 }
 
 // ------------------------------------------------------------------- RDMs
@@ -3986,21 +4264,22 @@ void launch_pspace_setup(const Item* items, int ibase, int nitem, const PspaceLi
                      sel.slot, sel.hi, sel.lo);
   hipLaunchKernelGGL(k_pspace_guess, dim3(nitem), dim3(256), 0, s, items, ibase, diag, pidx, V,
                      ntot, st, pmax, nunit);
-  if (pl.n[0] > 0)
-    hipLaunchKernelGGL((k_pspace_eigen<kMaxPspace, 512, false>), dim3(pl.n[0]), dim3(512), 0, s,
-                       items, pl.list[0], hams, diag, pidx, pQ, pT, V, ntot, st, pmax);
-  if (pl.n[1] > 0)
-    hipLaunchKernelGGL((k_pspace_eigen<kExactSmall, 64, true>), dim3(pl.n[1]), dim3(64), 0, s,
-                       items, pl.list[1], hams, diag, pidx, pQ, pT, V, ntot, st, pmax);
-  if (pl.n[2] > 0)
-    hipLaunchKernelGGL((k_pspace_eigen<kExactMid, 256, true>), dim3(pl.n[2]), dim3(256), 0, s,
-                       items, pl.list[2], hams, diag, pidx, pQ, pT, V, ntot, st, pmax);
-  if (pl.n[3] > 0)
-    hipLaunchKernelGGL((k_pspace_eigen<kMaxPspace, 256, true>), dim3(pl.n[3]), dim3(256), 0, s,
-                       items, pl.list[3], hams, diag, pidx, pQ, pT, V, ntot, st, pmax);
-  if (pl.n[4] > 0)
-    hipLaunchKernelGGL((k_pspace_eigen<kPspaceMid, 512, false>), dim3(pl.n[4]), dim3(512), 0, s,
-                       items, pl.list[4], hams, diag, pidx, pQ, pT, V, ntot, st, pmax);
+  auto reduce = [&](int cls, auto nb, auto exact) {
+    constexpr int NB = decltype(nb)::value;
+    constexpr int elems = 16 * NB * (16 * NB + 1) / 2;
+    if (pl.n[cls] == 0) return;
+    hipLaunchKernelGGL(k_pspace_matrix, dim3(pl.n[cls], (elems + kMatrixElems - 1) / kMatrixElems),
+                       dim3(256), 0, s, items, pl.list[cls], hams, diag, pidx, pQ, pmax);
+    hipLaunchKernelGGL((k_pspace_eigen<NB, decltype(exact)::value>), dim3(pl.n[cls]), dim3(256), 0,
+                       s, items, pl.list[cls], pidx, pQ, pT, V, ntot, st, pmax);
+  };
+  auto size = [&](int cls, auto nb) {
+    reduce(2 * cls, nb, std::false_type());
+    reduce(2 * cls + 1, nb, std::true_type());
+  };
+  size(0, std::integral_constant<int, kPspaceSmall / 16>());
+  size(1, std::integral_constant<int, kPspaceMid / 16>());
+  size(2, std::integral_constant<int, kMaxPspace / 16>());
 }
 void launch_dav_iteration(const Item* items, int ibase, int nitem, const Work* chunks, int nchunk,
                           double* V, double* Sv, const double* diag, int64_t ntot, DavState* st,
@@ -4030,11 +4309,14 @@ void launch_dav_iteration(const Item* items, int ibase, int nitem, const Work* c
   if (!olsen_all) {
     hipLaunchKernelGGL(k_dav_residual, dim3(nchunk), dim3(256), 0, s, items, chunks, V, Sv, diag,
                        ntot, st, part);
-    if (ps)
-      hipLaunchKernelGGL(k_pspace_correct, dim3(nitem), dim3(256), 0, s, items, ibase, ps->pidx,
-                         ps->pQ, ps->pT, V, Sv, ntot, st, ps->pdots);
-    hipLaunchKernelGGL(k_dav_reduce1, dim3(nw), dim3(256), 0, s, items, part,
-                       ps ? ps->pdots : nullptr, st, ibase, nitem, tol, max_iter, olsen_below);
+    const int listed = ps ? ps->n[0] + ps->n[1] + ps->n[2] : 0;
+    if (listed > 0) {
+      const int rest = listed < nitem ? nblk(nitem, kCorrectThreads / 64) : 0;
+      hipLaunchKernelGGL(k_pspace_correct, dim3(listed + rest), dim3(kCorrectThreads), 0, s, items,
+                         ibase, nitem, *ps, V, Sv, ntot, part, st, tol, max_iter, olsen_below);
+    } else
+      hipLaunchKernelGGL(k_dav_reduce1, dim3(nw), dim3(256), 0, s, items, part, st, ibase, nitem,
+                         tol, max_iter, olsen_below);
   }
   hipLaunchKernelGGL(k_dav_orth, dim3(nchunk), dim3(256), 0, s, items, chunks, V, ntot, st, part);
   hipLaunchKernelGGL(k_dav_reduce2, dim3(nw), dim3(256), 0, s, items, part, st, ibase, nitem);

@@ -101,13 +101,14 @@ void launch_dav_rr(const Item* items, int ibase, int nitem, const double* part, 
                    int slot, hipStream_t s);
 // P-space arrays of a plan: pidx [item][kMaxPspace] determinant addresses,
 // pQ [item][kMaxPspace^2] orthogonal factor of H_PP = Q T Q^T (row = P
-// position), pT [item][2][kMaxPspace] diagonal and off-diagonal of T, pdots
-// [item][kMaxSpace] Gram-Schmidt dot corrections.
+// position), pT [item][2][kMaxPspace] diagonal and off-diagonal of T.
 struct PspaceArgs {
   const int32_t* pidx;
   const double* pQ;
   const double* pT;
-  double* pdots;
+  // the items of a view that have a P-space, per size class
+  const int32_t* list[3];
+  int n[3];
 };
 // chunked P-space selection of large CASCIs: per chunk of kSelectChunk
 // determinants a work unit (item, chunk, first candidate slot of the item),
@@ -132,19 +133,17 @@ __host__ __device__ inline int pspace_dim(int64_t nd, int pmax) {
   const int64_t p = nd / kPspaceRatio < pmax ? nd / kPspaceRatio : pmax;
   return p >= kPspaceMinDim ? (int)p : 0;
 }
-// Which P-space reduction a CASCI takes: a P-space of a larger CASCI of
-// 0 more than kPspaceMid, 4 at most kPspaceMid determinants; its whole space
-// of 1 at most kExactSmall, 2 at most kExactMid, 3 at most kMaxPspace
-// determinants; -1 none (a single determinant or unit-vector guesses).
-constexpr int kExactSmall = 36;
-constexpr int kExactMid = 100;
-constexpr int kPspaceMid = 76;
-constexpr int kPspaceClasses = 5;
+// Which P-space reduction a CASCI takes: twice the size class of its P-space
+// (0 at most kPspaceSmall determinants, 1 at most kPspaceMid, 2 at most
+// kMaxPspace), plus 1 when that is its whole space; -1 none (a single
+// determinant or unit-vector guesses).
+constexpr int kPspaceSmall = 48;
+constexpr int kPspaceMid = 80;
+constexpr int kPspaceClasses = 6;
 __host__ __device__ inline int pspace_class(int64_t nd, int pmax) {
   const int p = nd <= 1 ? 0 : pspace_dim(nd, pmax);
   if (p == 0) return -1;
-  if (nd > kMaxPspace) return p <= kPspaceMid ? 4 : 0;
-  return nd <= kExactSmall ? 1 : nd <= kExactMid ? 2 : 3;
+  return 2 * (p <= kPspaceSmall ? 0 : p <= kPspaceMid ? 1 : 2) + (p == nd ? 1 : 0);
 }
 // per class, the items of a view that take it (absolute indices, ascending)
 struct PspaceLists {

@@ -154,7 +154,7 @@ struct Plan {
   // P-space (lowest-diagonal block of H): addresses, eigenvectors, eigenvalues,
   // Gram-Schmidt dot corrections; null when the P-space is off
   int32_t* pidx = nullptr;
-  double *pQ = nullptr, *pT = nullptr, *pdots = nullptr;
+  double *pQ = nullptr, *pT = nullptr;
   // the items of each P-space class (pspace_class), ascending; host copies
   // kept for the views' sub-ranges and while the uploads may be in flight
   std::vector<int32_t> pcls_h[kPspaceClasses];
@@ -916,7 +916,6 @@ void finalize_plan(mbefci_ctx* c, Plan& P, int nguess_slots) {
     P.pidx = arena<int32_t>(c, "pidx", (size_t)P.nitem * kMaxPspace, &grown);
     P.pQ = arena<double>(c, "pQ", (size_t)P.nitem * kMaxPspace * kMaxPspace, &grown);
     P.pT = arena<double>(c, "pT", (size_t)P.nitem * 2 * kMaxPspace, &grown);
-    P.pdots = arena<double>(c, "pdots", (size_t)P.nitem * (kMaxSpace + 1), &grown);
     for (int q = 0; q < kPspaceClasses; ++q) P.pcls_h[q].clear();
     for (int i = 0; i < P.nitem; ++i) {
       const int q = pspace_class(P.items[i].ndet, c->opts.pspace);
@@ -1091,9 +1090,28 @@ void add_vector(mbefci_ctx* c, Plan& P, const View& v, int slot) {
 // decides convergence and builds the next basis vector; step_b applies sigma
 // to it and updates the subspace matrix and Ritz pair.
 constexpr double kOlsenSwitch = 1e-7;
+// the view's items per P-space class
+PspaceLists pspace_lists(const Plan& P, const View& v) {
+  PspaceLists pl{};
+  for (int q = 0; q < kPspaceClasses; ++q) {
+    const auto& h = P.pcls_h[q];
+    const auto lo = std::lower_bound(h.begin(), h.end(), v.ibase);
+    const auto hi = std::lower_bound(lo, h.end(), v.ibase + v.nitem);
+    pl.list[q] = P.pcls[q] + (lo - h.begin());
+    pl.n[q] = (int)(hi - lo);
+  }
+  return pl;
+}
 void step_a(mbefci_ctx* c, Plan& P, const View& v) {
   const bool olsen = c->opts.precond == 1;
-  const PspaceArgs ps{P.pidx, P.pQ, P.pT, P.pdots};
+  PspaceArgs ps{P.pidx, P.pQ, P.pT, {}, {}};
+  if (P.pidx) {
+    const PspaceLists pl = pspace_lists(P, v);
+    for (int k = 0; k < 3; ++k) {  // the classes of partial P-spaces
+      ps.list[k] = pl.list[2 * k];
+      ps.n[k] = pl.n[2 * k];
+    }
+  }
   // with the diagonal / P-space correction a CASCI switches to the Olsen
   // correction once its residual is below kOlsenSwitch: that correction is
   // exact on the P block, so near convergence most of the new direction lies
@@ -1196,14 +1214,7 @@ void solve_view(mbefci_ctx* c, Plan& P, const View& v, int* graph_launches) {
   if (P.pidx) {
     const PspaceSelect sel{P.psel_work, (int)P.psel_works.size(), P.psel_slot, P.psel_hi,
                            P.psel_lo};
-    PspaceLists pl{};
-    for (int q = 0; q < kPspaceClasses; ++q) {
-      const auto& h = P.pcls_h[q];
-      const auto lo = std::lower_bound(h.begin(), h.end(), v.ibase);
-      const auto hi = std::lower_bound(lo, h.end(), v.ibase + v.nitem);
-      pl.list[q] = P.pcls[q] + (lo - h.begin());
-      pl.n[q] = (int)(hi - lo);
-    }
+    const PspaceLists pl = pspace_lists(P, v);
     launch_pspace_setup(P.d_items, v.ibase, v.nitem, pl, P.hams, P.diag, P.pidx, P.pQ, P.pT, P.V,
                         P.ntot, P.st, c->opts.pspace, g, sel, c->stream);
     g += 1;  // unit vectors (or the P-space eigenvector) and the dense vector
