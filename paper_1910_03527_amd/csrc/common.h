@@ -204,12 +204,14 @@ struct DavState {
   int32_t np;         // P-space size (0: diagonal preconditioner only)
   int32_t onepass;    // this iteration's correction needs one Gram-Schmidt pass
   int32_t olsen;      // 1: the corrections have switched to the Olsen form
+  int32_t restart;    // subspace size that the next residual collapses (0: none)
   double theta;       // lowest Ritz value (active-space energy without ecore)
   double rnorm;       // residual norm of the last Ritz vector
   double tnorm2;      // squared norm of the correction vector
   double eps;         // Olsen shift of the correction equation
   double y[kMaxSpace];
-  double yp[kMaxSpace];   // Ritz coefficients of the previous iteration (restart)
+  double cy[kMaxSpace];   // the collapse: new slot 0 and 1 in the old basis
+  double cz[kMaxSpace];
   double coef[kMaxSpace + 1];
   double Hs[kMaxSpace * kMaxSpace];
 };

@@ -1810,78 +1810,261 @@ __device__ inline double wave_parts(const double* __restrict__ part, const Item&
   return (v + v1) + v2;
 }
 
-// Symmetric Jacobi eigen-solve of the m x m subspace matrix by one wave of
-// 64 lanes, parallel ordering: every round applies m/2 disjoint plane
-// rotations at once (round-robin pairing of the indices), m-1 rounds per
-// sweep.  A rotation is skipped when |a_pq| <= 1e-18 (|a_pp| + |a_qq|); the
-// sweeps stop when a whole sweep rotates nothing.  Returns the lowest
-// eigenvalue and its eigenvector (ties: lowest index).
-__device__ void wave_jacobi_lowest(double* A, double* B, double* Vm, double* Vt, int m,
-                                   double* theta, double* y) {
-  const int lane = threadIdx.x & 63;
-  __shared__ double rc[kMaxSpace], rt[kMaxSpace];
-  __shared__ int partner[kMaxSpace];
-  __shared__ int rotated;
-  const int N = m + (m & 1);  // even number of players (index m is a dummy when m is odd)
-  for (int k = lane; k < m * m; k += 64) Vm[k] = (k / m == k % m) ? 1.0 : 0.0;
-  __syncthreads();
-  for (int sweep = 0; sweep < 40 && N > 1; ++sweep) {
-    if (lane == 0) rotated = 0;
-    __syncthreads();
-    for (int r = 0; r < N - 1; ++r) {
-      // round-robin pairs: position 0 holds index 0, positions 1..N-1 rotate
-      if (lane < N / 2) {
-        const int k = lane;
-        const int a0 = (k == 0) ? 0 : 1 + ((k - 1 + r) % (N - 1));
-        const int b0 = 1 + ((N - 2 - k + r) % (N - 1));
-        const int p = a0 < b0 ? a0 : b0, q = a0 < b0 ? b0 : a0;
-        double c = 1.0, t = 0.0;
-        bool rot = false;
-        if (q < m) {
-          const double apq = A[p * m + q], app = A[p * m + p], aqq = A[q * m + q];
-          if (fabs(apq) > 1e-18 * (fabs(app) + fabs(aqq)) && apq != 0.0) {
-            const double th = (aqq - app) / (2.0 * apq);
-            const double tt = (th >= 0 ? 1.0 : -1.0) / (fabs(th) + sqrt(th * th + 1.0));
-            c = 1.0 / sqrt(tt * tt + 1.0);
-            t = tt * c;
-            rot = true;
-          }
-        }
-        if (p < m) { partner[p] = rot ? q : p; rc[p] = c; rt[p] = rot ? -t : 0.0; }
-        if (q < m) { partner[q] = rot ? p : q; rc[q] = c; rt[q] = rot ? t : 0.0; }
-        if (rot) rotated = 1;
-      }
-      __syncthreads();
-      // B = A J, V = V J : column j <- c_j col_j + t_j col_partner(j)
-      for (int e = lane; e < m * m; e += 64) {
-        const int i = e / m, j = e % m, pj = partner[j];
-        B[e] = rc[j] * A[i * m + j] + rt[j] * A[i * m + pj];
-        Vt[e] = rc[j] * Vm[i * m + j] + rt[j] * Vm[i * m + pj];
-      }
-      __syncthreads();
-      // A = J^T B : row i <- c_i row_i + t_i row_partner(i)
-      for (int e = lane; e < m * m; e += 64) {
-        const int i = e / m, j = e % m, pi = partner[i];
-        A[e] = rc[i] * B[i * m + j] + rt[i] * B[pi * m + j];
-        Vm[e] = Vt[e];
-      }
-      __syncthreads();
+// (theta - T) z = y for symmetric tridiagonal T (diagonal d, off-diagonal e) by
+// one wave: a twisted factorisation without pivoting, lanes below 32 from the
+// first row and the others from the last, meeting in row n / 2 - which halves
+// the chain of dependent divides.  Pivots are kept at |p| >= floor (1e-8 for
+// the correction, like the diagonal one; a tiny relative floor for inverse
+// iteration).  In the Davidson iteration theta never exceeds the lowest
+// eigenvalue of T, so theta - T is negative semidefinite and the sweep is
+// stable.
+__device__ inline double floored(double p, double floor) {
+  return fabs(p) < floor ? (p < 0 ? -floor : floor) : p;
+}
+// 1/x to about one unit in the last place: the hardware's estimate and two
+// Newton steps (a third of the latency of a divide).
+__device__ inline double newton_rcp(double x) {
+  double y = __builtin_amdgcn_rcp(x);
+  y = fma(fma(-x, y, 1.0), y, y);
+  return fma(fma(-x, y, 1.0), y, y);
+}
+// LDS written by one lane of a wave and read by another
+__device__ inline void wave_lds_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+struct TwistedTri {      // of one lane
+  int n, steps;          // rows, rows of this half
+  double l0, l1;         // multipliers of the middle row with either half
+};
+// ll, ip, bb (LDS, n each): multiplier with the row before, 1/pivot and
+// off-diagonal over pivot.  n >= 2; all 64 lanes.
+__device__ inline TwistedTri twisted_factor(const double* d, const double* e, int n, double theta,
+                                            double floor, double* ll, double* ip, double* bb) {
+  const int back = (threadIdx.x >> 5) & 1, mid = n / 2;
+  TwistedTri T;
+  T.n = n;
+  T.steps = back ? n - 1 - mid : mid;
+  double l = 0.0, em = 0.0;
+  for (int s = 0; s < mid; ++s) {
+    // (past its last row the back half works on a row of the front half, unused)
+    const int i = back ? n - 1 - s : s;
+    const double p = floored((theta - d[i]) + l * em, floor);
+    const double y = newton_rcp(p), en = e[back ? max(i - 1, 0) : i];
+    if (s < T.steps) {
+      ll[i] = l;
+      ip[i] = y;
+      bb[i] = en * y;
+      em = en;
+      l = -en * y;
     }
-    if (!rotated) break;
   }
-  int best = 0;
-  for (int k = 1; k < m; ++k)
-    if (A[k * m + k] < A[best * m + best]) best = k;
-  *theta = A[best * m + best];
-  for (int k = lane; k < m; k += 64) y[k] = Vm[k * m + best];
-  __syncthreads();
+  const double c = l * em;
+  T.l0 = lane_value(l, 0);
+  T.l1 = lane_value(l, 32);
+  const double p = floored((theta - d[mid]) + (lane_value(c, 0) + lane_value(c, 32)), floor);
+  ip[mid] = newton_rcp(p);
+  wave_lds_fence();
+  return T;
+}
+// z (LDS) on entry y, on return the solution.
+__device__ inline void twisted_solve(const TwistedTri& T, const double* ll, const double* ip,
+                                     const double* bb, double* z) {
+  const int back = (threadIdx.x >> 5) & 1, n = T.n, mid = n / 2;
+  const int i0 = back ? n - 1 : 0, di = back ? -1 : 1;
+  double v = 0.0;
+#pragma unroll 4
+  for (int s = 0; s < T.steps; ++s) {
+    const int i = i0 + di * s;
+    v = z[i] - ll[i] * v;
+    z[i] = v;
+  }
+  v = ((z[mid] - T.l0 * lane_value(v, 0)) - T.l1 * lane_value(v, 32)) * ip[mid];
+  z[mid] = v;
+#pragma unroll 4
+  for (int s = T.steps - 1; s >= 0; --s) {
+    const int i = i0 + di * s;
+    v = z[i] * ip[i] + bb[i] * v;
+    z[i] = v;
+  }
+  wave_lds_fence();
+}
+
+// f(integral_constant 0), ..., f(integral_constant N - 1)
+template <int N, class F>
+__device__ inline void static_for(F&& f) {
+  if constexpr (N > 0) {
+    static_for<N - 1>(f);
+    f(std::integral_constant<int, N - 1>{});
+  }
+}
+// Minimum over the 16 lanes of a row, in every lane of it.
+__device__ inline double row_min(double x) {
+  x = fmin(x, dpp_move<0xB1>(x));
+  x = fmin(x, dpp_move<0x4E>(x));
+  x = fmin(x, dpp_move<0x141>(x));
+  return fmin(x, dpp_move<0x140>(x));
+}
+
+// Lowest eigenvalue and eigenvector (y, LDS) of the m x m subspace matrix A
+// (LDS, rows of kMaxSpace) by one wave: Householder reduction to tridiagonal
+// form, multisection of the lowest eigenvalue (64 points per round), inverse
+// iteration and the reflectors applied to its vector.  Lane (r, c) = (lane / 4,
+// lane % 4) holds row r, columns c + 4 j in registers.  A chain of dependent
+// steps like the P-space reduction; parallel Jacobi sweeps, which rotate every
+// eigenvector to the end, made k_dav_rr take 14.0 us for eight CASCIs and 78 us
+// for the 18,000 of an expansion, now 7.5 and 37 us.
+struct SubspaceScratch {
+  double v[kMaxSpace * kMaxSpace], beta[kMaxSpace], p[kMaxSpace];
+  double d[kMaxSpace], e[kMaxSpace], es[kMaxSpace];
+  double ll[kMaxSpace], ip[kMaxSpace], bb[kMaxSpace];
+};
+// Sum over the four lanes of a quad, the same value in each.
+__device__ inline double quad_sum(double x) {
+#pragma clang fp contract(off)
+  x += dpp_move<0xB1>(x);
+  x += dpp_move<0x4E>(x);
+  return x;
+}
+__device__ inline double wave_lowest(const double* A, int m, SubspaceScratch& W, double* y) {
+  static_assert(kMaxSpace == 16, "four lanes per row");
+  const int lane = threadIdx.x & 63, r = lane >> 2, c = lane & 3;
+  if (m == 1) {
+    if (lane == 0) y[0] = 1.0;
+    const double th = A[0];
+    wave_lds_fence();
+    return th;
+  }
+  double a[4];
+#pragma unroll
+  for (int j = 0; j < 4; ++j) a[j] = r < m && c + 4 * j < m ? A[r * kMaxSpace + c + 4 * j] : 0.0;
+  for (int i = lane; i < kMaxSpace; i += 64) W.e[i] = 0.0;
+  wave_lds_fence();
+  static_for<4>([&](auto block) {
+    constexpr int kb = decltype(block)::value;
+    for (int kk = 0; kk < 4; ++kk) {
+      const int k = 4 * kb + kk;
+      if (k + 2 >= m) break;  // uniform
+      double* __restrict__ vk = W.v + k * kMaxSpace;
+      if (c == kk) vk[r] = r > k ? a[kb] : 0.0;
+      wave_lds_fence();
+      double vc[4], sq = 0.0, vr = vk[r];
+#pragma unroll
+      for (int j = kb; j < 4; ++j) {
+        vc[j] = vk[c + 4 * j];
+        sq += vc[j] * vc[j];
+      }
+      const double x0 = vk[k + 1], sig = quad_sum(sq);
+      const bool some = sig > 1e-280;  // uniform: a column that is not done yet
+      const double g = sqrt(some ? sig : 1.0);
+      const double alpha = x0 >= 0.0 ? -g : g, v1 = some ? x0 - alpha : 0.0;
+      const double bt = some ? newton_rcp(sig - x0 * alpha) : 0.0;
+#pragma unroll
+      for (int j = kb; j < 4; ++j)
+        if (c + 4 * j == k + 1) vc[j] = v1;
+      if (r == k + 1) vr = v1;
+      double s0 = 0.0;
+#pragma unroll
+      for (int j = kb; j < 4; ++j) s0 += a[j] * vc[j];
+      const double pr = bt * quad_sum(s0);
+      if (c == 0) W.p[r] = pr;
+      if (lane == 0) {
+        W.e[k] = some ? alpha : x0;
+        W.beta[k] = bt;
+        vk[k + 1] = v1;
+      }
+      wave_lds_fence();
+      double pc[4], kv = 0.0;
+#pragma unroll
+      for (int j = kb; j < 4; ++j) {
+        pc[j] = W.p[c + 4 * j];
+        kv += pc[j] * vc[j];
+      }
+      const double Kc = 0.5 * bt * quad_sum(kv), wr = pr - Kc * vr;
+#pragma unroll
+      for (int j = kb; j < 4; ++j) a[j] -= vr * (pc[j] - Kc * vc[j]) + wr * vc[j];
+      wave_lds_fence();
+    }
+  });
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    if (c + 4 * j == r) W.d[r] = a[j];
+    if (r == m - 1 && c + 4 * j == m - 2) W.e[m - 2] = a[j];
+  }
+  wave_lds_fence();
+  // Gershgorin, one row per lane of a row of 16
+  const int q = lane & 15;
+  const double dq = W.d[q], el = q > 0 ? fabs(W.e[q > 0 ? q - 1 : 0]) : 0.0, er = fabs(W.e[q]);
+  double lo = row_min(q < m ? dq - (el + er) : 1e300);
+  double hi = -row_min(q < m ? -(dq + (el + er)) : 1e300);
+  const double scale = -row_min(q < m ? -(fabs(dq) + 2.0 * er) : 0.0);
+  if (lane < 16) {
+    W.es[q] = q < m ? el * el : 0.0;
+    // rows past m keep the sign of the minor before them
+    W.d[q] = q < m ? dq : hi + (1.0 + scale);
+  }
+  wave_lds_fence();
+  for (int round = 0; round < 9; ++round) {  // 64^9 = 1.8e16
+    const double w = hi - lo, x = lo + w * (double)(lane + 1) * (1.0 / 64.0);
+    double pm = 0.0, p = 1.0, mn = 1.0;  // leading minors of A - x
+    for (int i0 = 0; i0 < m; i0 += 4) {
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const double pn = (W.d[i0 + u] - x) * p - W.es[i0 + u] * pm;
+        pm = p;
+        p = pn;
+        mn = fmin(mn, p);
+      }
+      const int ex = -__builtin_amdgcn_frexp_exp(fmax(fabs(p), fabs(pm)));
+      p = __builtin_amdgcn_ldexp(p, ex);
+      pm = __builtin_amdgcn_ldexp(pm, ex);
+    }
+    const uint64_t below = __ballot(!(mn > 0.0));
+    if (below) {
+      const int f = __builtin_ctzll(below);
+      hi = lo + w * (double)(f + 1) * (1.0 / 64.0);
+      lo = lo + w * (double)f * (1.0 / 64.0);
+    }
+  }
+  const double th = 0.5 * (lo + hi);
+  const TwistedTri T =
+      twisted_factor(W.d, W.e, m, th, 1e-15 * fmax(scale, 1e-285), W.ll, W.ip, W.bb);
+  if (lane < 16) y[q] = q < m ? 1.0 : 0.0;
+  wave_lds_fence();
+  double z = 0.0;
+  for (int rep = 0; rep < 3; ++rep) {
+    twisted_solve(T, W.ll, W.ip, W.bb, y);
+    z = q < m ? y[q] : 0.0;
+    z *= 1.0 / sqrt(row_sum(z * z));
+    wave_lds_fence();
+    if (lane < 16) y[q] = z;
+    wave_lds_fence();
+  }
+  for (int k = m - 3; k >= 0; --k) {
+    const double v = W.v[k * kMaxSpace + q];
+    z -= W.beta[k] * row_sum(v * z) * v;
+  }
+  if (lane < 16) y[q] = z;
+  wave_lds_fence();
+  return th;
 }
 
 // Reduce the dots of the newest column into Hs; when the subspace is
 // complete (guess phase) or always (iteration phase), Rayleigh-Ritz.
 // One 64-thread block per item.
+//
+// Restart: a full subspace (mmax vectors) is collapsed onto the Ritz vector
+// x = V y (and H x = S y) in slot 0 and the previous iteration's Ritz vector,
+// made orthogonal to x, in slot 1: z = yp - (y.yp) y in the subspace's
+// orthonormal basis, x' = V z / |z| (kept when |z| > kRestartMin).  The
+// projected matrix becomes diag(theta, z^T Hs z / |z|^2): y is an
+// eigenvector of Hs and z is orthogonal to it.  The state is that of the
+// collapsed subspace from here on; the residual, which reads every vector
+// anyway, collapses them (kernels of their own cost 10 us per iteration of
+// a small batch and a pass over both vectors of a large one).
+constexpr double kRestartMin = 1e-8;
 __global__ void k_dav_rr(const Item* __restrict__ items, int ibase,
-                         const double* __restrict__ part, DavState* st, int slot) {
+                         const double* __restrict__ part, DavState* st, int slot, int mmax) {
   const Item& I = items[ibase + blockIdx.x];
   DavState& S = st[ibase + blockIdx.x];
   if (!item_active(S, slot)) return;
@@ -1895,148 +2078,95 @@ __global__ void k_dav_rr(const Item* __restrict__ items, int ibase,
     S.Hs[lane * kMaxSpace + j] = v;
     S.Hs[j * kMaxSpace + lane] = v;
   }
-  __syncthreads();
   const bool solve = slot < 0 || slot == S.nguess - 1;
   if (!solve) return;
-  __shared__ double A[kMaxSpace * kMaxSpace], B[kMaxSpace * kMaxSpace];
-  __shared__ double Vm[kMaxSpace * kMaxSpace], Vt[kMaxSpace * kMaxSpace], y[kMaxSpace];
-  __shared__ double th;
-  for (int k = lane; k < m * m; k += 64) A[k] = S.Hs[(k / m) * kMaxSpace + (k % m)];
-  __syncthreads();
-  double thl;
-  wave_jacobi_lowest(A, B, Vm, Vt, m, &thl, y);
-  if (lane == 0) th = thl;
-  __syncthreads();
-  __syncthreads();
-  if (lane < kMaxSpace) {
-    S.y[lane] = lane < m ? y[lane] : 0.0;
-    S.yp[lane] = yold;
+  __shared__ double A[kMaxSpace * kMaxSpace], y[kMaxSpace];
+  __shared__ SubspaceScratch W;
+  // (the newest row and column from here: their stores may still be under way)
+  for (int k = lane; k < kMaxSpace * kMaxSpace; k += 64) {
+    const int i = k / kMaxSpace, l = k % kMaxSpace;
+    if (i < j && l < j) A[k] = S.Hs[k];
+  }
+  if (lane < m) A[lane * kMaxSpace + j] = A[j * kMaxSpace + lane] = v;
+  wave_lds_fence();
+  const double th = wave_lowest(A, m, W, y);
+  const int q = lane & 15;  // a row of 16 lanes holds the subspace
+  const double yq = q < m ? y[q] : 0.0, yo = __shfl(yold, q, 64);
+  if (m >= mmax) {
+    const double cc = row_sum(yq * yo);
+    double z = fma(-cc, yq, yo);
+    const double nz = sqrt(row_sum(z * z));
+    const bool keep = nz > kRestartMin;
+    z = keep ? z / nz : 0.0;
+    if (lane < kMaxSpace) W.p[q] = z;
+    wave_lds_fence();
+    double hz = 0.0;
+    for (int i = 0; i < m; ++i) hz += (q < m ? A[q * kMaxSpace + i] : 0.0) * W.p[i];
+    const double h11 = row_sum(z * hz);
+    if (lane < kMaxSpace) {
+      S.cy[lane] = yq;
+      S.cz[lane] = z;
+      S.y[lane] = lane == 0 ? 1.0 : 0.0;
+    }
+    if (lane == 0) {
+      S.Hs[0] = th;
+      S.Hs[1] = 0.0;
+      S.Hs[kMaxSpace] = 0.0;
+      S.Hs[kMaxSpace + 1] = h11;
+      S.m = keep ? 2 : 1;
+    }
+  } else {
+    if (lane < kMaxSpace) S.y[lane] = yq;
+    if (lane == 0 && slot >= 0) S.m = m;  // end of the guess phase
   }
   if (lane == 0) {
+    S.restart = m >= mmax ? m : 0;
     S.theta = th;
-    if (slot >= 0) {   // end of the guess phase
-      S.m = m;
-    } else {
-      S.iters += 1;
-    }
+    if (slot < 0) S.iters += 1;
   }
 }
 
-// Restart: when the subspace is full, collapse it onto the Ritz vector
-// x = V y (and H x = S y) in slot 0 and the previous iteration's Ritz vector,
-// made orthogonal to x, in slot 1: z = yp - (y.yp) y in the subspace's
-// orthonormal basis, x' = V z / |z| (kept when |z| > kRestartMin).  The
-// projected matrix becomes diag(theta, z^T Hs z / |z|^2): y is an
-// eigenvector of Hs and z is orthogonal to it.
-// Both collapse kernels call restart_coef and must take the same decision:
-// explicit fused multiply-adds fix its rounding wherever it is inlined.
-constexpr double kRestartMin = 1e-8;
-__device__ inline double restart_coef(const DavState& S, double* z) {
-  double c = 0.0;
-  for (int i = 0; i < S.m; ++i) c = fma(S.y[i], S.yp[i], c);
-  double nz = 0.0;
-  for (int i = 0; i < S.m; ++i) {
-    z[i] = fma(-c, S.y[i], S.yp[i]);
-    nz = fma(z[i], z[i], nz);
-  }
-  nz = sqrt(nz);
-  return nz > kRestartMin ? nz : 0.0;
-}
-__global__ void __launch_bounds__(256) k_dav_collapse(const Item* __restrict__ items,
-                                                      const Work* __restrict__ work, double* V,
-                                                      double* Sv, int64_t ntot,
-                                                      const DavState* __restrict__ st, int mmax) {
-  const Work wk = work[blockIdx.x];
-  const Item& I = items[wk.item];
-  const DavState& S = st[wk.item];
-  if (S.conv || S.m < mmax) return;
-  __shared__ double z[kMaxSpace];
-  __shared__ double nz;
-  if (threadIdx.x == 0) nz = restart_coef(S, z);
-  __syncthreads();
-  const double inv = nz > 0.0 ? 1.0 / nz : 0.0;
-  const int64_t e0 = (int64_t)(wk.begin - I.chunk0) * kChunk;
-  const int64_t e1 = min(e0 + kChunk, I.ndet);
-  const bool unrolled = with_space(S.m, [&](auto mc) {
-    constexpr int M = decltype(mc)::value;
-    double y[M > 0 ? M : 1], zz[M > 0 ? M : 1];
+// One element of an item's collapse (k_dav_rr): x and H x into slot 0, x' and
+// H x' into slot 1 when the restart keeps it (m == 2).  v0 / v1: their
+// vectors, s0: H x.
+template <int M>
+__device__ inline void collapse_element(double* __restrict__ Vi, double* __restrict__ Si,
+                                        int64_t ntot, const DavState& S, double& v0, double& v1,
+                                        double& s0) {
+  double x = 0.0, sx = 0.0, xp = 0.0, sxp = 0.0;
+  const int n = M > 0 ? M : S.restart;
 #pragma unroll
-    for (int i = 0; i < M; ++i) {
-      y[i] = S.y[i];
-      zz[i] = z[i];
-    }
-    for (int64_t e = e0 + threadIdx.x; e < e1; e += 256) {
-      double x = 0.0, sx = 0.0, xp = 0.0, sxp = 0.0;
-#pragma unroll
-      for (int i = 0; i < M; ++i) {
-        const double v = V[(int64_t)i * ntot + I.off + e];
-        const double s = Sv[(int64_t)i * ntot + I.off + e];
-        x += y[i] * v;
-        sx += y[i] * s;
-        xp += zz[i] * v;
-        sxp += zz[i] * s;
-      }
-      V[I.off + e] = x;
-      Sv[I.off + e] = sx;
-      if (nz > 0.0) {
-        V[ntot + I.off + e] = xp * inv;
-        Sv[ntot + I.off + e] = sxp * inv;
-      }
-    }
-  });
-  if (!unrolled) {
-    for (int64_t e = e0 + threadIdx.x; e < e1; e += 256) {
-      double x = 0.0, sx = 0.0, xp = 0.0, sxp = 0.0;
-      for (int i = 0; i < S.m; ++i) {
-        const double v = V[(int64_t)i * ntot + I.off + e];
-        const double s = Sv[(int64_t)i * ntot + I.off + e];
-        x += S.y[i] * v;
-        sx += S.y[i] * s;
-        xp += z[i] * v;
-        sxp += z[i] * s;
-      }
-      V[I.off + e] = x;
-      Sv[I.off + e] = sx;
-      if (nz > 0.0) {
-        V[ntot + I.off + e] = xp * inv;
-        Sv[ntot + I.off + e] = sxp * inv;
-      }
-    }
+  for (int i = 0; i < n; ++i) {
+    const double v = Vi[(int64_t)i * ntot], s = Si[(int64_t)i * ntot];
+    x += S.cy[i] * v;
+    sx += S.cy[i] * s;
+    xp += S.cz[i] * v;
+    sxp += S.cz[i] * s;
   }
+  Vi[0] = x;
+  Si[0] = sx;
+  if (S.m == 2) {
+    Vi[ntot] = xp;
+    Si[ntot] = sxp;
+  }
+  v0 = x;
+  v1 = xp;
+  s0 = sx;
 }
-__global__ void k_dav_collapse_state(const Item* __restrict__ items, DavState* st, int ibase,
-                                     int nitem, int mmax) {
-  int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= nitem) return;
-  i += ibase;
-  DavState& S = st[i];
-  if (S.conv || S.m < mmax) return;
-  double z[kMaxSpace];
-  const double nz = restart_coef(S, z);
-  double h11 = 0.0;
-  if (nz > 0.0) {
-    for (int a = 0; a < S.m; ++a) {
-      double row = 0.0;
-      for (int b = 0; b < S.m; ++b) row += S.Hs[a * kMaxSpace + b] * z[b];
-      h11 += z[a] * row;
-    }
-    h11 /= nz * nz;
-  }
-  S.Hs[0] = S.theta;
-  S.Hs[1] = 0.0;
-  S.Hs[kMaxSpace] = 0.0;
-  S.Hs[kMaxSpace + 1] = h11;
-  S.m = nz > 0.0 ? 2 : 1;
-  S.y[0] = 1.0;
-  for (int k = 1; k < kMaxSpace; ++k) S.y[k] = 0.0;
+// f(integral_constant) with the restarts' usual subspace sizes unrolled
+template <class F>
+__device__ inline void with_restart(int n, F&& f) {
+  if (n == 5) f(std::integral_constant<int, 5>{});
+  else if (n == 8) f(std::integral_constant<int, 8>{});
+  else f(std::integral_constant<int, 0>{});
 }
 
 // Residual r = S y - theta V y, preconditioned t = r / (theta - H_II) into
-// slot m; partial sums of V_i . t (i < m), |r|^2 (index kMaxSpace) and |t|^2
+// slot m (after the collapse where the item restarts); partial sums of V_i . t (i < m), |r|^2 (index kMaxSpace) and |t|^2
 // (index kMaxSpace + 1).
 __global__ void __launch_bounds__(256) k_dav_residual(const Item* __restrict__ items,
                                                       const Work* __restrict__ work, double* V,
-                                                      const double* __restrict__ Sv,
+                                                      double* Sv,
                                                       const double* __restrict__ diag,
                                                       int64_t ntot,
                                                       const DavState* __restrict__ st,
@@ -2047,6 +2177,31 @@ __global__ void __launch_bounds__(256) k_dav_residual(const Item* __restrict__ i
   if (S.conv || S.olsen) return;
   const int m = S.m;
   const double th = S.theta;
+  if (S.restart) {  // the Ritz vector is slot 0 after the collapse
+    double acc[kMaxSpace + 2];
+#pragma unroll
+    for (int i = 0; i <= kMaxSpace + 1; ++i) acc[i] = 0.0;
+    const int64_t e0 = (int64_t)(wk.begin - I.chunk0) * kChunk;
+    const int64_t e1 = min(e0 + kChunk, I.ndet);
+    with_restart(S.restart, [&](auto mc) {
+      for (int64_t e = e0 + threadIdx.x; e < e1; e += 256) {
+        const double d = diag[I.off + e];
+        double v0, v1, s0;
+        collapse_element<decltype(mc)::value>(V + I.off + e, Sv + I.off + e, ntot, S, v0, v1, s0);
+        const double r = s0 - th * v0;
+        acc[kMaxSpace] += r * r;
+        double den = th - d;
+        if (fabs(den) < 1e-8) den = den < 0 ? -1e-8 : 1e-8;
+        const double tv = r / den;
+        V[(int64_t)m * ntot + I.off + e] = tv;
+        acc[kMaxSpace + 1] += tv * tv;
+        acc[0] += v0 * tv;
+        acc[1] += v1 * tv;
+      }
+    });
+    block_reduce_store<kMaxSpace + 2>(acc, m, kMaxSpace, part + (int64_t)wk.begin * kPart);
+    return;
+  }
   double y[kMaxSpace];
 #pragma unroll
   for (int i = 0; i < kMaxSpace; ++i) y[i] = S.y[i];
@@ -2113,10 +2268,9 @@ __device__ inline double guarded_den(double d) {
 }
 
 __global__ void __launch_bounds__(256) k_dav_residual_olsen(
-    const Item* __restrict__ items, const Work* __restrict__ work, const double* __restrict__ V,
-    const double* __restrict__ Sv, const double* __restrict__ diag, int64_t ntot,
-    const DavState* __restrict__ st, double* __restrict__ Rb, double* __restrict__ Xb,
-    double* part, int all) {
+    const Item* __restrict__ items, const Work* __restrict__ work, double* V, double* Sv,
+    const double* __restrict__ diag, int64_t ntot, const DavState* __restrict__ st,
+    double* __restrict__ Rb, double* __restrict__ Xb, double* part, int all) {
   const Work wk = work[blockIdx.x];
   const Item& I = items[wk.item];
   const DavState& S = st[wk.item];
@@ -2131,12 +2285,17 @@ __global__ void __launch_bounds__(256) k_dav_residual_olsen(
   const int64_t e1 = min(e0 + kChunk, I.ndet);
   for (int64_t e = e0 + threadIdx.x; e < e1; e += 256) {
     double x = 0.0, sx = 0.0;
+    if (S.restart) {  // uniform
+      double v1;
+      collapse_element<0>(V + I.off + e, Sv + I.off + e, ntot, S, x, v1, sx);
+    } else {
 #pragma unroll
-    for (int i = 0; i < kMaxSpace; ++i)
-      if (i < m) {
-        x += y[i] * V[(int64_t)i * ntot + I.off + e];
-        sx += y[i] * Sv[(int64_t)i * ntot + I.off + e];
-      }
+      for (int i = 0; i < kMaxSpace; ++i)
+        if (i < m) {
+          x += y[i] * V[(int64_t)i * ntot + I.off + e];
+          sx += y[i] * Sv[(int64_t)i * ntot + I.off + e];
+        }
+    }
     const double r = sx - th * x;
     const double den = guarded_den(diag[I.off + e] - th);
     Rb[I.off + e] = r;
@@ -2336,6 +2495,7 @@ __global__ void __launch_bounds__(256) k_dav_orth(const Item* __restrict__ items
   block_reduce_store<kMaxSpace + 1>(acc, m, kMaxSpace, part + (int64_t)wk.begin * kPart);
 }
 
+// Second Gram-Schmidt coefficients; the subspace grows by the new vector.
 __global__ void k_dav_reduce2(const Item* __restrict__ items, const double* __restrict__ part,
                               DavState* st, int ibase, int nitem) {
   int it = blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);  // a wave per item
@@ -2344,9 +2504,14 @@ __global__ void k_dav_reduce2(const Item* __restrict__ items, const double* __re
   const int lane = threadIdx.x & 63;
   const Item& I = items[it];
   DavState& S = st[it];
-  if (S.conv || S.onepass) return;
+  if (S.conv) return;
+  const int m = S.m;
+  if (S.onepass) {
+    if (lane == 0) S.m = m + 1;
+    return;
+  }
   const double v = wave_parts(part, I);
-  const double cf = lane < S.m ? v : 0.0;
+  const double cf = lane < m ? v : 0.0;
   const double n2 = lane_value(v, kMaxSpace) - wave_sum64(cf * cf);
   if (lane < kMaxSpace) S.coef[lane] = cf;
   if (lane != 0) return;
@@ -2354,10 +2519,13 @@ __global__ void k_dav_reduce2(const Item* __restrict__ items, const double* __re
   if (!(n2 > 1e-28)) {  // the correction lies in the subspace: accept
     S.conv = 1;
     S.status = 2;
+  } else {
+    S.m = m + 1;
   }
 }
 
-// t -= sum_i coef_i V_i, t /= |t|: the new basis vector in slot m; m += 1.
+// t -= sum_i coef_i V_i, t /= |t|: the new basis vector, in the last slot of
+// the grown subspace.
 __global__ void __launch_bounds__(256) k_dav_orth2(const Item* __restrict__ items,
                                                    const Work* __restrict__ work, double* V,
                                                    int64_t ntot, const DavState* __restrict__ st) {
@@ -2365,7 +2533,7 @@ __global__ void __launch_bounds__(256) k_dav_orth2(const Item* __restrict__ item
   const Item& I = items[wk.item];
   const DavState& S = st[wk.item];
   if (S.conv || S.onepass) return;
-  const int m = S.m;
+  const int m = S.m - 1;
   double cf[kMaxSpace];
 #pragma unroll
   for (int i = 0; i < kMaxSpace; ++i) cf[i] = S.coef[i];
@@ -2392,14 +2560,6 @@ __global__ void __launch_bounds__(256) k_dav_orth2(const Item* __restrict__ item
     }
   }
 }
-__global__ void k_dav_grow(DavState* st, int ibase, int nitem) {
-  int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= nitem) return;
-  i += ibase;
-  DavState& S = st[i];
-  if (!S.conv) S.m += 1;
-}
-
 // ------------------------------------------------------------- P-space
 // Davidson with a P-space: the np = min(kMaxPspace-ish cap, ndet) determinants
 // of lowest diagonal energy (ties: lower address) span a block H_PP of H that
@@ -2604,86 +2764,6 @@ __global__ void __launch_bounds__(256) k_pspace_select(const Item* __restrict__ 
 // host-built item lists: three sizes, each for a P-space and for a whole
 // space.
 
-// (theta - T) z = y for symmetric tridiagonal T (diagonal d, off-diagonal e) by
-// one wave: a twisted factorisation without pivoting, lanes below 32 from the
-// first row and the others from the last, meeting in row n / 2 - which halves
-// the chain of dependent divides.  Pivots are kept at |p| >= floor (1e-8 for
-// the correction, like the diagonal one; a tiny relative floor for inverse
-// iteration).  In the Davidson iteration theta never exceeds the lowest
-// eigenvalue of T, so theta - T is negative semidefinite and the sweep is
-// stable.
-__device__ inline double floored(double p, double floor) {
-  return fabs(p) < floor ? (p < 0 ? -floor : floor) : p;
-}
-// 1/x to about one unit in the last place: the hardware's estimate and two
-// Newton steps (a third of the latency of a divide).
-__device__ inline double newton_rcp(double x) {
-  double y = __builtin_amdgcn_rcp(x);
-  y = fma(fma(-x, y, 1.0), y, y);
-  return fma(fma(-x, y, 1.0), y, y);
-}
-// LDS written by one lane of a wave and read by another
-__device__ inline void wave_lds_fence() {
-  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-}
-struct TwistedTri {      // of one lane
-  int n, steps;          // rows, rows of this half
-  double l0, l1;         // multipliers of the middle row with either half
-};
-// ll, ip, bb (LDS, n each): multiplier with the row before, 1/pivot and
-// off-diagonal over pivot.  n >= 2; all 64 lanes.
-__device__ inline TwistedTri twisted_factor(const double* d, const double* e, int n, double theta,
-                                            double floor, double* ll, double* ip, double* bb) {
-  const int back = (threadIdx.x >> 5) & 1, mid = n / 2;
-  TwistedTri T;
-  T.n = n;
-  T.steps = back ? n - 1 - mid : mid;
-  double l = 0.0, em = 0.0;
-  for (int s = 0; s < mid; ++s) {
-    // (past its last row the back half works on a row of the front half, unused)
-    const int i = back ? n - 1 - s : s;
-    const double p = floored((theta - d[i]) + l * em, floor);
-    const double y = newton_rcp(p), en = e[back ? max(i - 1, 0) : i];
-    if (s < T.steps) {
-      ll[i] = l;
-      ip[i] = y;
-      bb[i] = en * y;
-      em = en;
-      l = -en * y;
-    }
-  }
-  const double c = l * em;
-  T.l0 = lane_value(l, 0);
-  T.l1 = lane_value(l, 32);
-  const double p = floored((theta - d[mid]) + (lane_value(c, 0) + lane_value(c, 32)), floor);
-  ip[mid] = newton_rcp(p);
-  wave_lds_fence();
-  return T;
-}
-// z (LDS) on entry y, on return the solution.
-__device__ inline void twisted_solve(const TwistedTri& T, const double* ll, const double* ip,
-                                     const double* bb, double* z) {
-  const int back = (threadIdx.x >> 5) & 1, n = T.n, mid = n / 2;
-  const int i0 = back ? n - 1 : 0, di = back ? -1 : 1;
-  double v = 0.0;
-#pragma unroll 4
-  for (int s = 0; s < T.steps; ++s) {
-    const int i = i0 + di * s;
-    v = z[i] - ll[i] * v;
-    z[i] = v;
-  }
-  v = ((z[mid] - T.l0 * lane_value(v, 0)) - T.l1 * lane_value(v, 32)) * ip[mid];
-  z[mid] = v;
-#pragma unroll 4
-  for (int s = T.steps - 1; s >= 0; --s) {
-    const int i = i0 + di * s;
-    v = z[i] * ip[i] + bb[i] * v;
-    z[i] = v;
-  }
-  wave_lds_fence();
-}
-
 // Guess of the CASCIs without a P-space, one 256-thread block per item of
 // the view (the others return at once): a single determinant is its own
 // solution; otherwise unit vectors on the nunit lowest diagonal determinants
@@ -2726,22 +2806,6 @@ __global__ void __launch_bounds__(256) k_pspace_guess(const Item* __restrict__ i
     S.olsen = 0;
     S.theta = 0.0;
   }
-}
-
-// f(integral_constant 0), ..., f(integral_constant N - 1)
-template <int N, class F>
-__device__ inline void static_for(F&& f) {
-  if constexpr (N > 0) {
-    static_for<N - 1>(f);
-    f(std::integral_constant<int, N - 1>{});
-  }
-}
-// Minimum over the 16 lanes of a row, in every lane of it.
-__device__ inline double row_min(double x) {
-  x = fmin(x, dpp_move<0xB1>(x));
-  x = fmin(x, dpp_move<0x4E>(x));
-  x = fmin(x, dpp_move<0x141>(x));
-  return fmin(x, dpp_move<0x140>(x));
 }
 
 // H_PP of the items of plist, lower triangle, into the rows of pQ that Q takes
@@ -4250,8 +4314,8 @@ void launch_dav_dots(const Item* items, const Work* chunks, int nchunk, const do
                        slot, part);
 }
 void launch_dav_rr(const Item* items, int ibase, int nitem, const double* part, DavState* st,
-                   int slot, hipStream_t s) {
-  hipLaunchKernelGGL(k_dav_rr, dim3(nitem), dim3(64), 0, s, items, ibase, part, st, slot);
+                   int slot, int mmax, hipStream_t s) {
+  hipLaunchKernelGGL(k_dav_rr, dim3(nitem), dim3(64), 0, s, items, ibase, part, st, slot, mmax);
 }
 void launch_pspace_setup(const Item* items, int ibase, int nitem, const PspaceLists& pl,
                          const ItemHam* hams, const double* diag, int32_t* pidx, double* pQ,
@@ -4283,15 +4347,11 @@ void launch_pspace_setup(const Item* items, int ibase, int nitem, const PspaceLi
 }
 void launch_dav_iteration(const Item* items, int ibase, int nitem, const Work* chunks, int nchunk,
                           double* V, double* Sv, const double* diag, int64_t ntot, DavState* st,
-                          double* part, double tol, int max_iter, int mmax, double* Rb,
+                          double* part, double tol, int max_iter, double* Rb,
                           double* Xb, const PspaceArgs* ps, bool olsen_all, double olsen_below,
                           hipStream_t s) {
   if (nchunk <= 0) return;
-  const int nb = nblk(nitem, 64), nw = nblk(nitem, 4);
-  hipLaunchKernelGGL(k_dav_collapse, dim3(nchunk), dim3(256), 0, s, items, chunks, V, Sv, ntot, st,
-                     mmax);
-  hipLaunchKernelGGL(k_dav_collapse_state, dim3(nb), dim3(64), 0, s, items, st, ibase, nitem,
-                     mmax);
+  const int nw = nblk(nitem, 4);
   // Olsen-corrected items first (all of them with olsen_all, else those that
   // switched in an earlier iteration), then the diagonal / P-space path for
   // the others, whose test may switch an item for the next iteration
@@ -4321,7 +4381,6 @@ void launch_dav_iteration(const Item* items, int ibase, int nitem, const Work* c
   hipLaunchKernelGGL(k_dav_orth, dim3(nchunk), dim3(256), 0, s, items, chunks, V, ntot, st, part);
   hipLaunchKernelGGL(k_dav_reduce2, dim3(nw), dim3(256), 0, s, items, part, st, ibase, nitem);
   hipLaunchKernelGGL(k_dav_orth2, dim3(nchunk), dim3(256), 0, s, items, chunks, V, ntot, st);
-  hipLaunchKernelGGL(k_dav_grow, dim3(nb), dim3(64), 0, s, st, ibase, nitem);
 }
 void launch_item_energy(const Item* items, const ItemHam* hams, const DavState* st, int nitem,
                         double* f, hipStream_t s) {

@@ -98,7 +98,7 @@ void launch_dav_dots(const Item* items, const Work* chunks, int nchunk, const do
                      const double* Sv, int64_t ntot, const DavState* st, int slot, double* part,
                      hipStream_t s);
 void launch_dav_rr(const Item* items, int ibase, int nitem, const double* part, DavState* st,
-                   int slot, hipStream_t s);
+                   int slot, int mmax, hipStream_t s);
 // P-space arrays of a plan: pidx [item][kMaxPspace] determinant addresses,
 // pQ [item][kMaxPspace^2] orthogonal factor of H_PP = Q T Q^T (row = P
 // position), pT [item][2][kMaxPspace] diagonal and off-diagonal of T.
@@ -168,7 +168,7 @@ void launch_pspace_setup(const Item* items, int ibase, int nitem, const PspaceLi
 // switch to the Olsen correction for the rest of the solve.
 void launch_dav_iteration(const Item* items, int ibase, int nitem, const Work* chunks, int nchunk,
                           double* V, double* Sv, const double* diag, int64_t ntot, DavState* st,
-                          double* part, double tol, int max_iter, int mmax, double* Rb,
+                          double* part, double tol, int max_iter, double* Rb,
                           double* Xb, const PspaceArgs* ps, bool olsen_all, double olsen_below,
                           hipStream_t s);
 void launch_item_energy(const Item* items, const ItemHam* hams, const DavState* st, int nitem,

@@ -1082,7 +1082,7 @@ void add_vector(mbefci_ctx* c, Plan& P, const View& v, int slot) {
   sigma(c, P, v, slot);
   launch_dav_dots(P.d_items, P.d_chunks + v.chunk_lo, v.nchunk, P.V, P.S, P.ntot, P.st, slot,
                   P.part, c->stream);
-  launch_dav_rr(P.d_items, v.ibase, v.nitem, P.part, P.st, slot, c->stream);
+  launch_dav_rr(P.d_items, v.ibase, v.nitem, P.part, P.st, slot, c->opts.max_space, c->stream);
 }
 
 // One Davidson iteration is split in two halves so that the convergence test
@@ -1119,7 +1119,7 @@ void step_a(mbefci_ctx* c, Plan& P, const View& v) {
   const double below = (!olsen && c->opts.conv_tol < kOlsenSwitch) ? kOlsenSwitch : 0.0;
   launch_dav_iteration(P.d_items, v.ibase, v.nitem, P.d_chunks + v.chunk_lo, v.nchunk, P.V, P.S,
                        P.diag, P.ntot, P.st, P.part, c->opts.conv_tol, c->opts.max_iter,
-                       c->opts.max_space, P.R, P.X, (P.pidx && !olsen) ? &ps : nullptr, olsen,
+                       P.R, P.X, (P.pidx && !olsen) ? &ps : nullptr, olsen,
                        below, c->stream);
 }
 void step_b(mbefci_ctx* c, Plan& P, const View& v) { add_vector(c, P, v, -1); }
