@@ -1906,147 +1906,90 @@ __device__ inline double row_min(double x) {
   return fmin(x, dpp_move<0x140>(x));
 }
 
-// Lowest eigenvalue and eigenvector (y, LDS) of the m x m subspace matrix A
-// (LDS, rows of kMaxSpace) by one wave: Householder reduction to tridiagonal
-// form, multisection of the lowest eigenvalue (64 points per round), inverse
-// iteration and the reflectors applied to its vector.  Lane (r, c) = (lane / 4,
-// lane % 4) holds row r, columns c + 4 j in registers.  A chain of dependent
-// steps like the P-space reduction; parallel Jacobi sweeps, which rotate every
-// eigenvector to the end, made k_dav_rr take 14.0 us for eight CASCIs and 78 us
-// for the 18,000 of an expansion, now 7.5 and 37 us.
-struct SubspaceScratch {
-  double v[kMaxSpace * kMaxSpace], beta[kMaxSpace], p[kMaxSpace];
-  double d[kMaxSpace], e[kMaxSpace], es[kMaxSpace];
-  double ll[kMaxSpace], ip[kMaxSpace], bb[kMaxSpace];
-};
-// Sum over the four lanes of a quad, the same value in each.
-__device__ inline double quad_sum(double x) {
-#pragma clang fp contract(off)
-  x += dpp_move<0xB1>(x);
-  x += dpp_move<0x4E>(x);
-  return x;
-}
-__device__ inline double wave_lowest(const double* A, int m, SubspaceScratch& W, double* y) {
-  static_assert(kMaxSpace == 16, "four lanes per row");
-  const int lane = threadIdx.x & 63, r = lane >> 2, c = lane & 3;
-  if (m == 1) {
-    if (lane == 0) y[0] = 1.0;
-    const double th = A[0];
-    wave_lds_fence();
-    return th;
+// Symmetric Jacobi eigen-solve of the m x m subspace matrix by one wave of
+// 64 lanes, parallel ordering: every round applies m/2 disjoint plane
+// rotations at once (round-robin pairing of the indices), m-1 rounds per
+// sweep.  A rotation is skipped when |a_pq| <= 1e-18 (|a_pp| + |a_qq|) and a
+// round without rotations costs only its test; the sweeps stop when a whole
+// sweep rotates nothing.  Returns the lowest eigenvalue and its eigenvector
+// (ties: lowest index).  Bound by the latency of a round's divides and square
+// roots (about 25 rounds at m = 5).
+__device__ void wave_jacobi_lowest(double* A, double* B, double* Vm, double* Vt, int m,
+                                   double* theta, double* y) {
+  const int lane = threadIdx.x & 63;
+  __shared__ double rc[kMaxSpace], rt[kMaxSpace];
+  __shared__ int partner[kMaxSpace];
+  const int N = m + (m & 1);  // even number of players (index m is a dummy when m is odd)
+  constexpr int EPL = kMaxSpace * kMaxSpace / 64;  // elements per lane
+  int row[EPL], column[EPL];
+#pragma unroll
+  for (int u = 0; u < EPL; ++u) {
+    const int e = lane + 64 * u;
+    row[u] = e / m;
+    column[u] = e % m;
+    if (e < m * m) Vm[e] = row[u] == column[u] ? 1.0 : 0.0;
   }
-  double a[4];
-#pragma unroll
-  for (int j = 0; j < 4; ++j) a[j] = r < m && c + 4 * j < m ? A[r * kMaxSpace + c + 4 * j] : 0.0;
-  for (int i = lane; i < kMaxSpace; i += 64) W.e[i] = 0.0;
   wave_lds_fence();
-  static_for<4>([&](auto block) {
-    constexpr int kb = decltype(block)::value;
-    for (int kk = 0; kk < 4; ++kk) {
-      const int k = 4 * kb + kk;
-      if (k + 2 >= m) break;  // uniform
-      double* __restrict__ vk = W.v + k * kMaxSpace;
-      if (c == kk) vk[r] = r > k ? a[kb] : 0.0;
-      wave_lds_fence();
-      double vc[4], sq = 0.0, vr = vk[r];
-#pragma unroll
-      for (int j = kb; j < 4; ++j) {
-        vc[j] = vk[c + 4 * j];
-        sq += vc[j] * vc[j];
+  auto wrap = [&](int x) { return x >= N - 1 ? x - (N - 1) : x; };
+  for (int sweep = 0; sweep < 40 && N > 1; ++sweep) {
+    bool rotated = false;  // uniform
+    for (int r = 0; r < N - 1; ++r) {
+      // round-robin pairs: position 0 holds index 0, positions 1..N-1 rotate
+      const int k = lane < N / 2 ? lane : 0;
+      const int a0 = k == 0 ? 0 : 1 + wrap(k - 1 + r), b0 = 1 + wrap(N - 2 - k + r);
+      const int p = a0 < b0 ? a0 : b0, q = a0 < b0 ? b0 : a0;
+      double apq = 0.0, app = 0.0, aqq = 0.0;
+      if (q < m) {
+        apq = A[p * m + q];
+        app = A[p * m + p];
+        aqq = A[q * m + q];
       }
-      const double x0 = vk[k + 1], sig = quad_sum(sq);
-      const bool some = sig > 1e-280;  // uniform: a column that is not done yet
-      const double g = sqrt(some ? sig : 1.0);
-      const double alpha = x0 >= 0.0 ? -g : g, v1 = some ? x0 - alpha : 0.0;
-      const double bt = some ? newton_rcp(sig - x0 * alpha) : 0.0;
-#pragma unroll
-      for (int j = kb; j < 4; ++j)
-        if (c + 4 * j == k + 1) vc[j] = v1;
-      if (r == k + 1) vr = v1;
-      double s0 = 0.0;
-#pragma unroll
-      for (int j = kb; j < 4; ++j) s0 += a[j] * vc[j];
-      const double pr = bt * quad_sum(s0);
-      if (c == 0) W.p[r] = pr;
-      if (lane == 0) {
-        W.e[k] = some ? alpha : x0;
-        W.beta[k] = bt;
-        vk[k + 1] = v1;
+      const bool rot = fabs(apq) > 1e-18 * (fabs(app) + fabs(aqq)) && apq != 0.0;
+      if (__ballot(rot) == 0) continue;
+      rotated = true;
+      if (lane < N / 2) {
+        double c = 1.0, t = 0.0;
+        if (rot) {
+          const double th = (aqq - app) / (2.0 * apq);
+          const double tt = (th >= 0 ? 1.0 : -1.0) / (fabs(th) + sqrt(th * th + 1.0));
+          c = 1.0 / sqrt(tt * tt + 1.0);
+          t = tt * c;
+        }
+        if (p < m) { partner[p] = rot ? q : p; rc[p] = c; rt[p] = rot ? -t : 0.0; }
+        if (q < m) { partner[q] = rot ? p : q; rc[q] = c; rt[q] = rot ? t : 0.0; }
       }
       wave_lds_fence();
-      double pc[4], kv = 0.0;
+      // B = A J, V = V J : column j <- c_j col_j + t_j col_partner(j)
 #pragma unroll
-      for (int j = kb; j < 4; ++j) {
-        pc[j] = W.p[c + 4 * j];
-        kv += pc[j] * vc[j];
+      for (int u = 0; u < EPL; ++u) {
+        const int e = lane + 64 * u, i = row[u], j = column[u];
+        if (e < m * m) {
+          const int pj = partner[j];
+          B[e] = rc[j] * A[e] + rt[j] * A[i * m + pj];
+          Vt[e] = rc[j] * Vm[e] + rt[j] * Vm[i * m + pj];
+        }
       }
-      const double Kc = 0.5 * bt * quad_sum(kv), wr = pr - Kc * vr;
+      wave_lds_fence();
+      // A = J^T B : row i <- c_i row_i + t_i row_partner(i)
 #pragma unroll
-      for (int j = kb; j < 4; ++j) a[j] -= vr * (pc[j] - Kc * vc[j]) + wr * vc[j];
+      for (int u = 0; u < EPL; ++u) {
+        const int e = lane + 64 * u, i = row[u], j = column[u];
+        if (e < m * m) {
+          const int pi = partner[i];
+          A[e] = rc[i] * B[e] + rt[i] * B[pi * m + j];
+          Vm[e] = Vt[e];
+        }
+      }
       wave_lds_fence();
     }
-  });
-#pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    if (c + 4 * j == r) W.d[r] = a[j];
-    if (r == m - 1 && c + 4 * j == m - 2) W.e[m - 2] = a[j];
+    if (!rotated) break;
   }
+  int best = 0;
+  for (int k = 1; k < m; ++k)
+    if (A[k * m + k] < A[best * m + best]) best = k;
+  *theta = A[best * m + best];
+  for (int k = lane; k < m; k += 64) y[k] = Vm[k * m + best];
   wave_lds_fence();
-  // Gershgorin, one row per lane of a row of 16
-  const int q = lane & 15;
-  const double dq = W.d[q], el = q > 0 ? fabs(W.e[q > 0 ? q - 1 : 0]) : 0.0, er = fabs(W.e[q]);
-  double lo = row_min(q < m ? dq - (el + er) : 1e300);
-  double hi = -row_min(q < m ? -(dq + (el + er)) : 1e300);
-  const double scale = -row_min(q < m ? -(fabs(dq) + 2.0 * er) : 0.0);
-  if (lane < 16) {
-    W.es[q] = q < m ? el * el : 0.0;
-    // rows past m keep the sign of the minor before them
-    W.d[q] = q < m ? dq : hi + (1.0 + scale);
-  }
-  wave_lds_fence();
-  for (int round = 0; round < 9; ++round) {  // 64^9 = 1.8e16
-    const double w = hi - lo, x = lo + w * (double)(lane + 1) * (1.0 / 64.0);
-    double pm = 0.0, p = 1.0, mn = 1.0;  // leading minors of A - x
-    for (int i0 = 0; i0 < m; i0 += 4) {
-#pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const double pn = (W.d[i0 + u] - x) * p - W.es[i0 + u] * pm;
-        pm = p;
-        p = pn;
-        mn = fmin(mn, p);
-      }
-      const int ex = -__builtin_amdgcn_frexp_exp(fmax(fabs(p), fabs(pm)));
-      p = __builtin_amdgcn_ldexp(p, ex);
-      pm = __builtin_amdgcn_ldexp(pm, ex);
-    }
-    const uint64_t below = __ballot(!(mn > 0.0));
-    if (below) {
-      const int f = __builtin_ctzll(below);
-      hi = lo + w * (double)(f + 1) * (1.0 / 64.0);
-      lo = lo + w * (double)f * (1.0 / 64.0);
-    }
-  }
-  const double th = 0.5 * (lo + hi);
-  const TwistedTri T =
-      twisted_factor(W.d, W.e, m, th, 1e-15 * fmax(scale, 1e-285), W.ll, W.ip, W.bb);
-  if (lane < 16) y[q] = q < m ? 1.0 : 0.0;
-  wave_lds_fence();
-  double z = 0.0;
-  for (int rep = 0; rep < 3; ++rep) {
-    twisted_solve(T, W.ll, W.ip, W.bb, y);
-    z = q < m ? y[q] : 0.0;
-    z *= 1.0 / sqrt(row_sum(z * z));
-    wave_lds_fence();
-    if (lane < 16) y[q] = z;
-    wave_lds_fence();
-  }
-  for (int k = m - 3; k >= 0; --k) {
-    const double v = W.v[k * kMaxSpace + q];
-    z -= W.beta[k] * row_sum(v * z) * v;
-  }
-  if (lane < 16) y[q] = z;
-  wave_lds_fence();
-  return th;
 }
 
 // Reduce the dots of the newest column into Hs; when the subspace is
@@ -2080,16 +2023,21 @@ __global__ void k_dav_rr(const Item* __restrict__ items, int ibase,
   }
   const bool solve = slot < 0 || slot == S.nguess - 1;
   if (!solve) return;
-  __shared__ double A[kMaxSpace * kMaxSpace], y[kMaxSpace];
-  __shared__ SubspaceScratch W;
+  __shared__ double A[kMaxSpace * kMaxSpace], B[kMaxSpace * kMaxSpace];
+  __shared__ double Vm[kMaxSpace * kMaxSpace], Vt[kMaxSpace * kMaxSpace], y[kMaxSpace];
+  __shared__ double zs[kMaxSpace];
   // (the newest row and column from here: their stores may still be under way)
-  for (int k = lane; k < kMaxSpace * kMaxSpace; k += 64) {
-    const int i = k / kMaxSpace, l = k % kMaxSpace;
-    if (i < j && l < j) A[k] = S.Hs[k];
+  auto hs = [&](int i, int l, double newest) {
+    return i < j && l < j ? S.Hs[i * kMaxSpace + l] : newest;
+  };
+  for (int k0 = 0; k0 < m * m; k0 += 64) {  // every lane: the newest comes from other lanes
+    const int k = k0 + lane, i = k / m, l = k % m;
+    const double nv = __shfl(v, i == j ? l : i, 64);
+    if (k < m * m) A[k] = hs(i, l, nv);
   }
-  if (lane < m) A[lane * kMaxSpace + j] = A[j * kMaxSpace + lane] = v;
   wave_lds_fence();
-  const double th = wave_lowest(A, m, W, y);
+  double th;
+  wave_jacobi_lowest(A, B, Vm, Vt, m, &th, y);
   const int q = lane & 15;  // a row of 16 lanes holds the subspace
   const double yq = q < m ? y[q] : 0.0, yo = __shfl(yold, q, 64);
   if (m >= mmax) {
@@ -2098,10 +2046,14 @@ __global__ void k_dav_rr(const Item* __restrict__ items, int ibase,
     const double nz = sqrt(row_sum(z * z));
     const bool keep = nz > kRestartMin;
     z = keep ? z / nz : 0.0;
-    if (lane < kMaxSpace) W.p[q] = z;
+    if (lane < kMaxSpace) zs[q] = z;
     wave_lds_fence();
+    // (the store of the newest row and column by this wave comes before)
     double hz = 0.0;
-    for (int i = 0; i < m; ++i) hz += (q < m ? A[q * kMaxSpace + i] : 0.0) * W.p[i];
+    for (int i = 0; i < m; ++i) {
+      const double nv = __shfl(v, q == j ? i : q, 64);
+      hz += (q < m ? hs(q, i, nv) : 0.0) * zs[i];
+    }
     const double h11 = row_sum(z * hz);
     if (lane < kMaxSpace) {
       S.cy[lane] = yq;
