@@ -3300,21 +3300,33 @@ __global__ void __launch_bounds__(kCorrectThreads) k_pspace_correct(
 // gamma+ is column NP of Gamma+ and Gamma+_{NP,NP} = |c|^2.  Each workgroup
 // accumulates the upper 16x16 blocks over its tiles in registers and writes
 // one partial; k_rdm_reduce sums the partials in a fixed order.
-template <int NACT, int TN>
-__global__ void __launch_bounds__(256) k_rdm_syrk(const Item* __restrict__ items,
-                                                  const Work* __restrict__ work,
-                                                  const double* __restrict__ civ,
-                                                  double* __restrict__ part) {
+//
+// Bound by the build's loads and the LDS reads of the products, so the size of
+// a workgroup is that which gives a SIMD four waves to alternate between: from
+// 13 orbitals its LDS leaves one per CU, below two or three.  The next tile's
+// entries, c values and c row load under this tile's products.  Measured:
+// CAS(14,14) 14.2 ms with 256 threads and every load waited for in the build,
+// 5.98 with 512, 4.94 with 1024; Hubbard-16 (10 orbitals) 1.83 ms, 1.56 with
+// 256, 1.40 with 512; eight CAS(8,8)s 57, 44 and 33 us.
+constexpr int rdm_threads(int nact) { return nact >= 13 ? 1024 : nact >= 8 ? 512 : 256; }
+template <int NACT, int TN, int NT = rdm_threads(NACT)>
+__global__ void __launch_bounds__(NT) k_rdm_syrk(const Item* __restrict__ items,
+                                                 const Work* __restrict__ work,
+                                                 const double* __restrict__ civ,
+                                                 double* __restrict__ part) {
   constexpr int NP = NACT * (NACT + 1) / 2;
   constexpr int KPAD = (NP + 15) / 16 * 16;
   constexpr int NRB = KPAD / 16;
   constexpr int NBLK = NRB * (NRB + 1) / 2;   // upper 16x16 blocks
-  constexpr int BPW = (NBLK + 3) / 4;         // blocks per wave
-  constexpr int NSUB = 256 / TN;
+  constexpr int NW = NT / 64;
+  constexpr int BPW = (NBLK + NW - 1) / NW;   // blocks per wave
+  constexpr int NSUB = NT / TN;
   constexpr int NPER = (NP + NSUB - 1) / NSUB;
   constexpr int LDT = TN + 1;
   constexpr int CMAX = (int)binom_c(NACT, NACT / 2);
+  constexpr int CPT = (CMAX + NT - 1) / NT;
   static_assert(NP < KPAD, "the c row needs a padding row");
+  static_assert(TN == 64, "a wave per D+ row");
   __shared__ double Ds[KPAD * LDT];
   __shared__ int32_t Tb[NP * TN];
   __shared__ double Cr[CMAX];
@@ -3327,64 +3339,77 @@ __global__ void __launch_bounds__(256) k_rdm_syrk(const Item* __restrict__ items
   const int32_t* __restrict__ pB = I.pairB;
   const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
   const int col = t % TN;
-  const int sub = (TN >= 64) ? __builtin_amdgcn_readfirstlane(t / TN) : t / TN;
+  const int sub = __builtin_amdgcn_readfirstlane(t / TN);
   const int blk = wk.begin / Na;
   const int Kb0 = blk * TN;
   const int Kb = Kb0 + col;
   const double keep = Kb < Nb ? 1.0 : 0.0;
   const int Kbc = Kb < Nb ? Kb : Nb - 1;
-  for (int x = t; x < NP * TN; x += 256) {
+  const double* __restrict__ ca = c + Kbc;
+  for (int x = t; x < NP * TN; x += NT) {
     const int ab = x / TN, cc = x - ab * TN;
     const int kb = Kb0 + cc < Nb ? Kb0 + cc : Nb - 1;
     Tb[x] = ldg(pB + ab * Nb + kb);
   }
-  for (int x = (NP + 1) * LDT + t; x < KPAD * LDT; x += 256) Ds[x] = 0.0;
+  for (int x = (NP + 1) * LDT + t; x < KPAD * LDT; x += NT) Ds[x] = 0.0;
   // this wave's output blocks (rb <= cb) in a fixed enumeration
   int brb[BPW], bcb[BPW];
   double4_t acc[BPW];
 #pragma unroll
   for (int u = 0; u < BPW; ++u) {
-    int id = wave + 4 * u, rb = 0;
+    int id = wave + NW * u, rb = 0;
     while (id >= NRB - rb && rb < NRB) { id -= NRB - rb; ++rb; }
     brb[u] = rb;
     bcb[u] = rb + id;
     acc[u] = (double4_t){0.0, 0.0, 0.0, 0.0};
   }
+  int32_t ea[NPER];
+  double ga[NPER], cr[CPT];
+  auto load = [&](int ka) {  // (unconditional loads: a branch would wait for them)
+    const int32_t* __restrict__ pa = pA + ka * NP;
+#pragma unroll
+    for (int i = 0; i < NPER; ++i) ea[i] = ldc(pa + min(sub + NSUB * i, NP - 1));
+#pragma unroll
+    for (int i = 0; i < NPER; ++i) ga[i] = ldg(ca + (ea[i] ? (ea[i] >> 1) - 1 : 0) * Nb);
+#pragma unroll
+    for (int j = 0; j < CPT; ++j) cr[j] = ldg(c + ka * Nb + min(t + NT * j, Nb - 1));
+  };
+  load(wk.begin - blk * Na);
   for (int tile = wk.begin; tile < wk.end; ++tile) {
-    const int Ka = tile - blk * Na;
-    for (int x = t; x < Nb; x += 256) Cr[x] = ldg(c + Ka * Nb + x);
+#pragma unroll
+    for (int j = 0; j < CPT; ++j)
+      if (t + NT * j < Nb) Cr[t + NT * j] = cr[j];
     __syncthreads();
-    const int32_t* __restrict__ pa = pA + Ka * NP;
-    const double* __restrict__ ca = c + Kbc;
 #pragma unroll
     for (int i = 0; i < NPER; ++i) {
       const int ab = sub + NSUB * i;
       if (ab < NP) {
-        const int32_t ea = ldc(pa + ab);
         const int32_t eb = Tb[ab * TN + col];
-        const int ja = ea ? (ea >> 1) - 1 : 0, jb = eb ? (eb >> 1) - 1 : 0;
-        const double fa = ea ? ((ea & 1) ? -keep : keep) : 0.0;
+        const int jb = eb ? (eb >> 1) - 1 : 0;
+        const double fa = ea[i] ? ((ea[i] & 1) ? -keep : keep) : 0.0;
         const double fb = eb ? ((eb & 1) ? -keep : keep) : 0.0;
-        Ds[ab * LDT + col] = fa * ldg(ca + ja * Nb) + fb * Cr[jb];
+        Ds[ab * LDT + col] = fa * ga[i] + fb * Cr[jb];
       }
     }
     if (sub == 0) Ds[NP * LDT + col] = keep * Cr[Kbc];
     __syncthreads();
+    load(min(tile + 1, wk.end - 1) - blk * Na);
 #pragma unroll
     for (int u = 0; u < BPW; ++u) {
-      if (wave + 4 * u >= NBLK) continue;
+      if (wave + NW * u >= NBLK) continue;
       const double* ar = Ds + (brb[u] * 16 + (lane & 15)) * LDT + (lane >> 4);
       const double* br = Ds + (bcb[u] * 16 + (lane & 15)) * LDT + (lane >> 4);
 #pragma unroll
       for (int k = 0; k < TN; k += 4)
         acc[u] = __builtin_amdgcn_mfma_f64_16x16x4f64(ar[k], br[k], acc[u], 0, 0, 0);
     }
-    __syncthreads();
+    // no barrier here: the next tile's Cr stores follow this tile's second
+    // barrier, its D+ stores the next first one
   }
   double* out = part + (int64_t)blockIdx.x * KPAD * KPAD;
 #pragma unroll
   for (int u = 0; u < BPW; ++u) {
-    if (wave + 4 * u >= NBLK) continue;
+    if (wave + NW * u >= NBLK) continue;
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
       const int r = brb[u] * 16 + (lane >> 4) + 4 * v, cc = bcb[u] * 16 + (lane & 15);
@@ -4393,7 +4418,8 @@ namespace mbefci {
 template <int NACT, int TN>
 static void rdm_syrk_t(const Item* items, const Work* work, int nwork, const double* civ,
                        double* part, hipStream_t s) {
-  hipLaunchKernelGGL((k_rdm_syrk<NACT, TN>), dim3(nwork), dim3(256), 0, s, items, work, civ, part);
+  hipLaunchKernelGGL((k_rdm_syrk<NACT, TN>), dim3(nwork), dim3(rdm_threads(NACT)), 0, s, items,
+                     work, civ, part);
 }
 bool launch_rdm_syrk(int n, int tn, const Item* items, const Work* work, int nwork,
                      const double* civ, double* part, hipStream_t s) {
