@@ -2545,7 +2545,8 @@ __device__ void select_lowest(const KeyAt& key_at, int64_t n, int np, uint64_t* 
   __shared__ uint32_t pre_lo;
   __shared__ int64_t need;
   __shared__ uint32_t ncol;
-  if (t == 0) { pre_hi = 0; pre_lo = 0; need = np; ncol = 0; }
+  __shared__ int done;
+  if (t == 0) { pre_hi = 0; pre_lo = 0; need = np; ncol = 0; done = 0; }
   __syncthreads();
   if (np < n) {
     for (int dg = 0; dg < 12; ++dg) {
@@ -2589,8 +2590,14 @@ __device__ void select_lowest(const KeyAt& key_at, int64_t n, int np, uint64_t* 
         need = k - below;
         if (dg < 8) pre_hi |= (uint64_t)t << (56 - 8 * dg);
         else pre_lo |= (uint32_t)t << (24 - 8 * (dg - 8));
+        if (need == (int64_t)h) {  // every key with this prefix is wanted
+          done = 1;
+          if (dg < 8) pre_hi |= (dg < 7 ? (1ull << (56 - 8 * dg)) - 1 : 0);
+          pre_lo |= dg < 8 ? ~0u : dg < 11 ? (1u << (24 - 8 * (dg - 8))) - 1 : 0;
+        }
       }
       __syncthreads();
+      if (done) break;  // uniform
     }
   } else if (t == 0) {
     pre_hi = ~0ull;
@@ -2618,8 +2625,8 @@ __device__ __forceinline__ int select_count(int64_t nd, int pmax) {
   return nd <= kMaxPspace ? (int)nd : (pmax > 8 ? pmax : 8);
 }
 
-// First phase for CASCIs of more than kSelectChunk determinants: one block per
-// chunk of kSelectChunk addresses writes the chunk's np lowest keys to the
+// First phase for CASCIs of more than one chunk: one block per chunk of
+// select_chunk addresses writes the chunk's np lowest keys to the
 // item's candidate slots (chunk c of an item whose slots start at s:
 // slot s + c, kMaxPspace keys each; unused keys are the sentinel ~0, which is
 // never selected since the item has at least np real keys).  Work: item,
@@ -2635,8 +2642,8 @@ __global__ void __launch_bounds__(256) k_pspace_select_chunk(const Item* __restr
   if (wk.item < ibase || wk.item >= ibase + nitem) return;
   const Item& I = items[wk.item];
   const int np = select_count(I.ndet, pmax);
-  const int64_t lo = (int64_t)wk.begin * kSelectChunk;
-  const int64_t hi = min(I.ndet, lo + kSelectChunk);
+  const int64_t size = select_chunk(I.ndet), lo = (int64_t)wk.begin * size;
+  const int64_t hi = min(I.ndet, lo + size);
   const double* __restrict__ d = diag + I.off;
   __shared__ uint64_t khi[kMaxPspace];
   __shared__ uint32_t klo[kMaxPspace];
@@ -2674,7 +2681,7 @@ __global__ void __launch_bounds__(256) k_pspace_select(const Item* __restrict__ 
   __shared__ uint32_t klo[kMaxPspace];
   const int slot = cand_slot ? cand_slot[it] : -1;
   if (slot >= 0) {
-    const int64_t nchunk = (nd + kSelectChunk - 1) / kSelectChunk;
+    const int64_t size = select_chunk(nd), nchunk = (nd + size - 1) / size;
     const uint64_t* __restrict__ ch = cand_hi + (int64_t)slot * kMaxPspace;
     const uint32_t* __restrict__ cl = cand_lo + (int64_t)slot * kMaxPspace;
     auto key_at = [&](int64_t i, uint64_t& kh, uint32_t& kl) {

@@ -110,10 +110,16 @@ struct PspaceArgs {
   const int32_t* list[3];
   int n[3];
 };
-// chunked P-space selection of large CASCIs: per chunk of kSelectChunk
+// chunked P-space selection of large CASCIs: per chunk of select_chunk
 // determinants a work unit (item, chunk, first candidate slot of the item),
 // per item its first slot or -1, and the candidate keys (kMaxPspace per slot)
-constexpr int64_t kSelectChunk = 16384;
+// A chunk is one block's search, several passes over it; the chunks' candidates
+// (kMaxPspace each) are one block's again.  Small chunks for CASCIs whose
+// candidates stay few: eight CAS(9,9)s of 15,876 determinants take 32 us
+// in chunks of 2,048, 189 us in one; at CAS(14,14) candidates would be the work.
+__host__ __device__ inline int64_t select_chunk(int64_t nd) {
+  return nd <= ((int64_t)1 << 17) ? 2048 : 16384;
+}
 // Row stride of G (doubles): the beta-string count rounded up to 16, so
 // that every row of G starts on a 128-byte line, when that adds at most
 // 1/16 to the row (252 -> 256, 3432 -> 3440); short rows, where padding

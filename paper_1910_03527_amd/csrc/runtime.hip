@@ -159,7 +159,7 @@ struct Plan {
   // kept for the views' sub-ranges and while the uploads may be in flight
   std::vector<int32_t> pcls_h[kPspaceClasses];
   int32_t* pcls[kPspaceClasses] = {};
-  // chunked selection of the P-space of CASCIs above kSelectChunk
+  // chunked selection of the P-space of CASCIs above one chunk
   // determinants (host copies kept while the uploads may be in flight)
   std::vector<Work> psel_works;
   std::vector<int32_t> psel_slots;
@@ -931,8 +931,9 @@ void finalize_plan(mbefci_ctx* c, Plan& P, int nguess_slots) {
     int32_t nslot = 0;
     for (int i = 0; i < P.nitem; ++i) {
       const int64_t nd = P.items[i].ndet;
-      if (nd <= kSelectChunk) continue;
-      const int nch = (int)((nd + kSelectChunk - 1) / kSelectChunk);
+      const int64_t size = select_chunk(nd);
+      if (nd <= size) continue;
+      const int nch = (int)((nd + size - 1) / size);
       P.psel_slots[i] = nslot;
       for (int k = 0; k < nch; ++k) P.psel_works.push_back(Work{i, k, nslot, 0});
       nslot += nch;
