@@ -673,7 +673,10 @@ __global__ void k_string_links(int n, int ne, int64_t N, uint32_t* alpha, uint32
 // and Hb's symmetry and C's layout give every operand whole 128-byte lines:
 // in the second sum lane l takes four consecutive C[Ia][Jb] and the k order
 // is permuted to match.  Bound by the FP64 matrix pipe (2 (Na + Nb) flops per
-// determinant, operands from L2).
+// determinant, operands from L2): 0.26 ms for Hubbard-16, 50 TFLOP/s.
+// Where a plan has few tiles (1 x 1 then) a wave is one chain of loads, so
+// three chunks are in flight: CAS(10,10) 31 -> 22 us, eight CAS(9,9)s 18.5 ->
+// 15.3 us against one.
 typedef double double2u_t __attribute__((ext_vector_type(2), aligned(8)));
 typedef double double2_t __attribute__((ext_vector_type(2)));
 template <int RB, int CB>
@@ -709,7 +712,8 @@ __global__ void __launch_bounds__(256, 2) k_sigma_same_spin(
     for (int q = 0; q < CB; ++q)
 #pragma unroll
       for (int v = 0; v < 4; ++v) acc[r][q][v] = 0.0;
-  double A[2][RB][4], B[2][CB][4];
+  constexpr int DEPTH = RB * CB == 1 ? 4 : 2;  // chunks in flight
+  double A[DEPTH][RB][4], B[DEPTH][CB][4];
   auto load1 = [&](int k0, double (&a)[RB][4], double (&b)[CB][4]) {
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
@@ -757,15 +761,41 @@ __global__ void __launch_bounds__(256, 2) k_sigma_same_spin(
       }
   };
   const int n1 = pa / 16, n2 = pb / 16;
-  load1(0, A[0], B[0]);
-  for (int k = 0; k < n1 + n2; k += 2) {
+  if constexpr (DEPTH > 2) {
+    // either sum's chunk by the same loads, never under a branch (the compiler
+    // would wait for every load in flight where the paths meet)
+    auto load = [&](int k, double (&a)[RB][4], double (&b)[CB][4]) {
+      const bool one = k < n1;  // uniform
+      const int k0 = 16 * (one ? k : min(k, n1 + n2 - 1) - n1);
+      const double* __restrict__ pa_ = one ? Ha : c;
+      const double* __restrict__ pb_ = one ? c : Hb;
 #pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      if (k + h < n1 + n2) {
-        const int nx = k + h + 1;
-        if (nx < n1) load1(16 * nx, A[1 - h], B[1 - h]);
-        else if (nx < n1 + n2) load2(16 * (nx - n1), A[1 - h], B[1 - h]);
-        multiply(A[h], B[h]);
+      for (int j = 0; j < 4; ++j) {
+        const int j1 = k0 + 4 * j + lk, j2 = k0 + 4 * lk + j;
+        a[0][j] = ldg(pa_ + (one ? j1 * pa + ia[0] : ia[0] * Nb + min(j2, Nb - 1)));
+        b[0][j] = ldg(pb_ + (one ? min(j1, Na - 1) * Nb : j2 * pb) + jb[0]);
+      }
+    };
+#pragma unroll
+    for (int d = 0; d + 1 < DEPTH; ++d) load(d, A[d], B[d]);
+    for (int k = 0; k < n1 + n2; k += DEPTH) {
+#pragma unroll
+      for (int h = 0; h < DEPTH; ++h) {
+        load(k + h + DEPTH - 1, A[(h + DEPTH - 1) % DEPTH], B[(h + DEPTH - 1) % DEPTH]);
+        if (k + h < n1 + n2) multiply(A[h], B[h]);
+      }
+    }
+  } else {
+    load1(0, A[0], B[0]);
+    for (int k = 0; k < n1 + n2; k += 2) {
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        if (k + h < n1 + n2) {
+          const int nx = k + h + 1;
+          if (nx < n1) load1(16 * nx, A[1 - h], B[1 - h]);
+          else if (nx < n1 + n2) load2(16 * (nx - n1), A[1 - h], B[1 - h]);
+          multiply(A[h], B[h]);
+        }
       }
     }
   }
