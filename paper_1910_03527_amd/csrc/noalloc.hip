@@ -127,11 +127,16 @@ __global__ void k_noalloc_prepare(Item item, Item* items, const double* h1, cons
     hptr[0] = h1;
     gptr[0] = eri;
     ecore[0] = e_core;
-    DavState s{};
-    s.m = 1;
-    s.nguess = 1;
-    st[0] = s;
     block[0] = Work{0, 0, 1, 0};
+  }
+  // a solver state of one vector; zeroed by the whole block (by one thread it
+  // took 55 us of a 151 us call at CAS(8,8))
+  static_assert(sizeof(DavState) % 8 == 0, "whole words");
+  for (int i = t; i < (int)(sizeof(DavState) / 8); i += blockDim.x) ((uint64_t*)st)[i] = 0;
+  __syncthreads();
+  if (t == 0) {
+    st[0].m = 1;
+    st[0].nguess = 1;
   }
   const int Na = item.Na, Nb = item.Nb;
   if (nsame > 0) {
@@ -249,8 +254,12 @@ int noalloc_sigma(int device, int n, int na, int nb, const double* h1, const dou
     launch_pair_table(n, na, Na, (int32_t*)at(L.pairA), (int32_t*)at(L.pairAT), s);
     launch_pair_table(n, nb, Nb, (int32_t*)at(L.pairB), (int32_t*)at(L.pairBT), s);
   } else if (I.ndet > 1) {
-    launch_string_links(n, na, Na, (uint32_t*)at(L.klink), nullptr, s);
-    launch_string_links(n, nb, Nb, nullptr, (uint32_t*)at(L.glink), s);
+    if (na == nb) {  // the same strings: both tables from one pass over them
+      launch_string_links(n, na, Na, (uint32_t*)at(L.klink), (uint32_t*)at(L.glink), s);
+    } else {
+      launch_string_links(n, na, Na, (uint32_t*)at(L.klink), nullptr, s);
+      launch_string_links(n, nb, Nb, nullptr, (uint32_t*)at(L.glink), s);
+    }
   }
   launch_casci_setup(n, hptr, gptr, ecore, items, 1, hams, W, s);
   if (I.ndet > 1) {
