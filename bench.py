@@ -43,7 +43,9 @@ def kernel_source_sha(kernel_name):
     csrc = os.path.join(here, "paper_1910_03527_amd", "csrc")
     fn = "k_" + kernel_name.split("<")[0]
     m = re.match(r"sigma_dgemm<n=(\d+),", kernel_name)
-    if m and int(m.group(1)) > 10:  # the contraction that keeps every pair row of G
+    if kernel_name.startswith("sigma_dgemm_flat<"):  # one wave per alpha string
+        fn = "k_sigma_dgemm"
+    if m and int(m.group(1)) > 10:  # the contraction of every pair into G
         fn = "k_sigma_dgemm_pairrows"
     with open(os.path.join(csrc, "kernels.hip")) as fh:
         text = fh.read()
@@ -147,8 +149,8 @@ def _roofline(kt, workload):
 
 
 def _sigma_build(kt, workload, copy_gbps):
-    """sigma-sweep totals: algorithmic bytes (c read, G written and read back,
-    sigma written) and flops over the summed kernel times, against the
+    """sigma-sweep totals: algorithmic bytes (c read, sigma written; above 10
+    orbitals G written and read back too) and flops over the summed kernel times, against the
     published HBM peak and the copy rate measured in the same run; the counted
     L2-fabric bytes beside them, which include last-level-cache hits and can
     exceed what HBM delivers."""
