@@ -3713,10 +3713,25 @@ __device__ inline void tri_index(int64_t x, int* i, int* j) {
 }
 
 // dE/dh_pq = sum_it w_it gamma_full(p, q), for p >= q, written to (p, q)
-// and (q, p).  One wave per element: lane l sums the candidate items l,
-// l + 64, ... (in ascending item order), then the lanes' sums meet in
-// wave_sum64 (a fixed order, so the result is bitwise reproducible).
-__global__ void __launch_bounds__(64) k_grad_h(const Item* __restrict__ items, int nitem,
+// and (q, p).  One block of T threads per element: thread l sums the candidate
+// items l, l + T, ... (in ascending item order), then the threads' sums meet in
+// block_sum (a fixed order, so the result is bitwise reproducible).  A
+// candidate is a chain of loads and there are few elements, so T is large:
+// Hubbard-12 (78 elements, 2,510 CASCIs) 98 us with 64, 22 with 512.
+constexpr int kGradHThreads = 512;
+// Sum over the block, in thread 0.
+template <int T>
+__device__ inline double block_sum(double v) {
+  __shared__ double part[T / 64];
+  v = wave_sum64(v);
+  if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = v;
+  __syncthreads();
+  double s = part[0];
+#pragma unroll
+  for (int i = 1; i < T / 64; ++i) s += part[i];
+  return s;
+}
+__global__ void __launch_bounds__(kGradHThreads) k_grad_h(const Item* __restrict__ items, int nitem,
                                                const int32_t* __restrict__ act, uint64_t occmask,
                                                int M, const double* __restrict__ w,
                                                const double* __restrict__ rdmp,
@@ -3729,7 +3744,7 @@ __global__ void __launch_bounds__(64) k_grad_h(const Item* __restrict__ items, i
   int nv;
   const int32_t* __restrict__ cand = grad_candidates(e, nitem, L, &nv);
   double acc = 0.0;
-  for (int k = lane; k < nv; k += 64) {
+  for (int k = lane; k < nv; k += kGradHThreads) {
     const int it = cand[k];
     if (e & ~L.live[it]) continue;
     const double wt = w[it];
@@ -3743,7 +3758,7 @@ __global__ void __launch_bounds__(64) k_grad_h(const Item* __restrict__ items, i
     else if (cp >= 0 && cq >= 0) val = act_gamma(rdmp + roff[it], I.kpad, I.npair, cp, cq);
     acc += wt * val;
   }
-  acc = wave_sum64(acc);
+  acc = block_sum<kGradHThreads>(acc);
   if (lane == 0) {
     out[p * M + q] = acc;
     out[q * M + p] = acc;
@@ -3752,20 +3767,23 @@ __global__ void __launch_bounds__(64) k_grad_h(const Item* __restrict__ items, i
 
 // dE/d(pq|rs) = sum_it w_it 1/2 Sym8(Gamma_full)_pqrs.  The value has the
 // 8-fold symmetry of the integrals, so it is formed once per orbit (p >= q,
-// r >= s, pair pq >= pair rs) and written to all eight positions; one wave
-// per orbit as in k_grad_h (four per 256-thread block).  An element with an
+// r >= s, pair pq >= pair rs) and written to all eight positions; W waves per
+// orbit (4 / W orbits per 256-thread block): one where the orbits fill the
+// device, four where they don't (Hubbard-12, 3,081 orbits: 249 us with one,
+// 140 with four).  An element with an
 // orbital outside every CASCI's live set, or with more expansion orbitals
 // than any tuple holds, finds an empty or non-matching candidate list.
+template <int W>
 __global__ void __launch_bounds__(256) k_grad_g(const Item* __restrict__ items, int nitem,
                                                 const int32_t* __restrict__ act, uint64_t occmask,
                                                 int M, const double* __restrict__ w,
                                                 const double* __restrict__ rdmp,
                                                 const int64_t* __restrict__ roff, GradLists L,
                                                 double* out) {
-  const int64_t x = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-  const int lane = threadIdx.x & 63;
+  const int64_t x = (int64_t)blockIdx.x * (4 / W) + threadIdx.x / (64 * W);
+  const int lane = threadIdx.x % (64 * W);
   const int64_t np = (int64_t)M * (M + 1) / 2;
-  if (x >= np * (np + 1) / 2) return;  // whole waves
+  if (x >= np * (np + 1) / 2) return;  // whole waves; the whole block for W = 4
   int P, Q, p, q, r, s;
   tri_index(x, &P, &Q);
   tri_index(P, &p, &q);
@@ -3775,7 +3793,7 @@ __global__ void __launch_bounds__(256) k_grad_g(const Item* __restrict__ items, 
   int nv;
   const int32_t* __restrict__ cand = grad_candidates(e, nitem, L, &nv);
   double acc = 0.0;
-  for (int k = lane; k < nv; k += 64) {
+  for (int k = lane; k < nv; k += 64 * W) {
     const int it = cand[k];
     if (e & ~L.live[it]) continue;
     const double wt = w[it];
@@ -3789,7 +3807,9 @@ __global__ void __launch_bounds__(256) k_grad_g(const Item* __restrict__ items, 
     const int cs = orb_class(a, I.n, single, occmask, s);
     acc += wt * 0.5 * sym_gamma2(p, q, r, s, cp, cq, cr, cs, rdmp + roff[it], I.kpad, I.npair);
   }
-  acc = wave_sum64(acc);
+  static_assert(W == 1 || W == 4, "an orbit per wave or per block");
+  if constexpr (W == 1) acc = wave_sum64(acc);
+  else acc = block_sum<256>(acc);
   if (lane < 8) {
     // lane l writes the permutation (bit 0: swap p q, bit 1: swap r s, bit 2: swap the pairs)
     int a = p, b = q, c = r, d = s;
@@ -3843,7 +3863,9 @@ __global__ void k_casci_rdm_out(const Item* __restrict__ items, int it,
 // f(T) = E_core(T) + theta_T ; eps_T = f(T) - E_ref ;
 // Delta eps_T = sum over non-empty U in T of (-1)^{|T|-|U|} eps_U, which is the
 // solution of the recursion of Eq. 2 (Moebius inversion of
-// eps_T = sum_{non-empty U in T} Delta eps_U).
+// eps_T = sum_{non-empty U in T} Delta eps_U).  16 lanes per tuple, subsets dealt
+// over them: a thread walking all 2^n of them left the device idle (2,510 tuples
+// of order up to 6: 274 -> 34 us).
 __global__ void k_item_energy(const Item* __restrict__ items, const ItemHam* __restrict__ hams,
                               const DavState* __restrict__ st, int nitem, double* f) {
   int i = blockIdx.x * blockDim.x + threadIdx.x;
@@ -3858,7 +3880,7 @@ __global__ void k_mbe_increments(MbeSpaces sp, const BucketDev* __restrict__ buc
                                  const int64_t* __restrict__ order_off,
                                  const int32_t* __restrict__ xpos_o,
                                  const int32_t* __restrict__ xpos_v, int nX) {
-  int it = blockIdx.x * blockDim.x + threadIdx.x;
+  const int it = blockIdx.x * (blockDim.x / 16) + (threadIdx.x >> 4), lane = threadIdx.x & 15;
   if (it >= nitem || it == 0) return;   // item 0 is the reference CASCI
   const int32_t* tp = tuple_pos + (int64_t)it * (2 * max_order + 2);
   const int no = tp[0], nv = tp[1], n = no + nv;
@@ -3866,7 +3888,7 @@ __global__ void k_mbe_increments(MbeSpaces sp, const BucketDev* __restrict__ buc
   // bucket base index per (order, nocc)
   double acc = 0.0;
   const unsigned full = (1u << n) - 1u;
-  for (unsigned sub = 1; sub <= full; ++sub) {
+  for (unsigned sub = 1 + lane; sub <= full; sub += 16) {
     int co[kMaxActive], cv[kMaxActive];
     int ko = 0, kv = 0;
     for (int b = 0; b < n; ++b)
@@ -3883,6 +3905,8 @@ __global__ void k_mbe_increments(MbeSpaces sp, const BucketDev* __restrict__ buc
     const double e = f[idx] - eref;
     acc += ((n - ord) & 1) ? -e : e;
   }
+  acc = row_sum(acc);
+  if (lane != 0) return;
   inc[it] = acc;
   if (inc_lex) {
     // lexicographic rank of T among the order-n tuples of the sorted X
@@ -4406,7 +4430,7 @@ void launch_mbe_combine(const MbeSpaces* sp, const BucketDev* buckets, int nbuck
                         double* inc, double* inc_lex, double* f_lex, const int64_t* order_off,
                         const int32_t* xpos_o, const int32_t* xpos_v, int nX, double* e_order,
                         hipStream_t s) {
-  hipLaunchKernelGGL(k_mbe_increments, dim3(nblk(nitem, 64)), dim3(64), 0, s, *sp, buckets,
+  hipLaunchKernelGGL(k_mbe_increments, dim3(nblk(nitem, 16)), dim3(256), 0, s, *sp, buckets,
                      nbucket, tuple_pos, max_order, f, nitem, inc, inc_lex, f_lex, order_off,
                      xpos_o, xpos_v, nX);
   if (max_order > 0)
@@ -4500,10 +4524,16 @@ void launch_grad(const Item* items, int nitem, const int32_t* act, uint64_t occm
   hipLaunchKernelGGL(k_grad_pair_fill, dim3(M, M), dim3(64), 0, s, live, nitem, poff, plist);
   const GradLists L{live, list, count, plist, poff, pcount};
   const int64_t np = (int64_t)M * (M + 1) / 2;  // p >= q
-  hipLaunchKernelGGL(k_grad_h, dim3((int)np), dim3(64), 0, s, items, nitem, act, occmask, M, w,
-                     rdmp, roff, L, dh);
-  hipLaunchKernelGGL(k_grad_g, dim3(nblk(np * (np + 1) / 2, 4)), dim3(256), 0, s, items, nitem,
-                     act, occmask, M, w, rdmp, roff, L, dg);
+  hipLaunchKernelGGL(k_grad_h, dim3((int)np), dim3(kGradHThreads), 0, s, items, nitem, act,
+                     occmask, M, w, rdmp, roff, L, dh);
+  // 8 waves per SIMD x 1024 SIMDs: with fewer orbits a wave each leaves slots
+  const int64_t orbits = np * (np + 1) / 2;
+  if (orbits < 8192)
+    hipLaunchKernelGGL(k_grad_g<4>, dim3((int)orbits), dim3(256), 0, s, items, nitem, act, occmask,
+                       M, w, rdmp, roff, L, dg);
+  else
+    hipLaunchKernelGGL(k_grad_g<1>, dim3(nblk(orbits, 4)), dim3(256), 0, s, items, nitem, act,
+                       occmask, M, w, rdmp, roff, L, dg);
 }
 void launch_casci_rdm_out(const Item* items, int it, int n, const double* rdmp,
                           const int64_t* roff, double* rdm1, double* rdm2, hipStream_t s) {
