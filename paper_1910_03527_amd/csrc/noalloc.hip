@@ -53,6 +53,10 @@ struct Layout {
   int ntiles, nsegs, nsame;
 };
 
+// whether sigma is formed from string operators (0 and 1 orbitals have one
+// determinant, and no shape of theirs is defined for 0)
+bool string_path(int n) { return n >= 2 && n <= kStringMax; }
+
 Layout layout(int n, int na, int nb, int64_t Na, int64_t Nb, int La, int Lb) {
   Layout L{};
   size_t off = 0;
@@ -63,7 +67,7 @@ Layout layout(int n, int na, int nb, int64_t Na, int64_t Nb, int La, int Lb) {
   };
   const int64_t npair = (int64_t)n * (n + 1) / 2;
   const int64_t kpad = (npair + 15) / 16 * 16;
-  const bool strings = n <= kStringMax;
+  const bool strings = string_path(n);
   const int64_t nblk = (Nb + kNoallocTile - 1) / kNoallocTile;
   const int64_t nsg = Na * ((Nb + 63) / 64);
   if (strings) {  // one step of alpha strings per unit, 16 x 16 same-spin tiles
@@ -219,7 +223,7 @@ int noalloc_sigma(int device, int n, int na, int nb, const double* h1, const dou
   I.chunk0 = 0;
   I.nchunk = 0;
   I.shape = 0;
-  const bool strings = n <= kStringMax;
+  const bool strings = string_path(n);
   I.strA = (const uint64_t*)at(L.strA);
   I.strB = (const uint64_t*)at(L.strB);
   if (strings) {
