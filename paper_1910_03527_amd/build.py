@@ -16,7 +16,7 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libmbefci.so")
 SOURCES = ["kernels.hip", "runtime.hip", "noalloc.hip"]
-HEADERS = ["common.h", "launch.h"]
+HEADERS = ["common.h", "launch.h", "schedule.h"]
 
 # Packed FP32 instructions stay disabled for every device compile.
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",

@@ -26,6 +26,7 @@
 #include "../../include/mbefci.h"
 #include "common.h"
 #include "launch.h"
+#include "schedule.h"
 
 using namespace mbefci;
 
@@ -93,7 +94,7 @@ struct SymTab {
 // One kernel-shape group of a plan: items with the same active size n share
 // the sigma contraction kernel (its pair dimension is a template parameter).
 struct Group {
-  int n = 0, tn = 64, tiles_per_wg = 16;
+  int n = 0, tn = 64, tiles_per_wg = 0;  // 0: chosen by build_tiles
   std::vector<Work> tiles;
   std::vector<int> item_lo, item_hi;  // per item of the plan: its tile range (or empty)
   Work* d_tiles = nullptr;
@@ -536,10 +537,11 @@ int tile_for(mbefci_ctx* c, int n) {
   if (it != c->tuned.end()) return it->second.first;
   return n >= 10 ? 32 : 64;  // measured defaults when nothing is tuned
 }
+// tiles per workgroup: the tuned number, 0 for the plan's own choice (build_tiles)
 int tpw_for(mbefci_ctx* c, int n) {
   auto it = c->tuned.find(n);
   if (c->opts.tile == 0 && it != c->tuned.end()) return it->second.second;
-  return 16;
+  return 0;
 }
 
 // tune cache: one line per active size, "n tile tiles_per_wg"
@@ -567,21 +569,22 @@ void save_tune_cache(mbefci_ctx* c) {
 }
 
 // --------------------------------------------------------------- planning
-// Sigma-contraction work units of group gi: tiles (one alpha string x tn beta
-// strings) numbered column-major, tile = block * Na + Ka; a unit covers
-// tiles_per_wg alpha strings of one beta block and never crosses a block.
-// Up to kStringMax orbitals a unit is a range of alpha strings, tiles_per_wg
-// steps of the strings a workgroup takes at a time; fewer steps where the
-// group would give less than kStringUnits units (four per CU).
-constexpr int64_t kStringUnits = 1024;
-void build_string_units(Plan& P, int gi) {
-  Group& g = P.groups[gi];
+// Steps of group gi's alpha strings, string_spw of them at a time.
+int64_t string_steps(const Plan& P, int gi, int tn) {
   int64_t strings = 0;
   for (int i = 0; i < P.nitem; ++i)
     if (P.item_group[i] == gi) strings += P.items[i].Na;
+  return strings / string_spw(P.groups[gi].n, tn);
+}
+// Sigma-contraction work units of group gi.  Above kStringMax orbitals a tile
+// is one alpha string x tn beta strings, numbered column-major, tile = block *
+// Na + Ka; a unit covers consecutive alpha strings of one beta block and never
+// crosses a block.  Up to kStringMax orbitals a unit is a range of alpha
+// strings.  Lengths: schedule.h.
+void build_string_units(Plan& P, int gi) {
+  Group& g = P.groups[gi];
   const int spw = string_spw(g.n, g.tn);
-  const int64_t most = strings / (spw * kStringUnits);
-  const int len = spw * (int)std::max<int64_t>(1, std::min<int64_t>(g.tiles_per_wg, most));
+  const int len = spw * string_unit_steps(g.tiles_per_wg, string_steps(P, gi, g.tn));
   for (int i = 0; i < P.nitem; ++i) {
     if (P.item_group[i] != gi) continue;
     g.item_lo[i] = (int)g.tiles.size();
@@ -594,15 +597,13 @@ void build_tiles(Plan& P, int gi) {
   Group& g = P.groups[gi];
   g.tiles.clear();
   if (g.n <= kStringMax) return build_string_units(P, gi);
-  // A CU holds three or four workgroups at 11-12 orbitals: below twice that
-  // many units a short last wave costs more than a unit's set-up, so small
-  // groups take shorter ones (12 orbitals, 792 x 495 strings: 792 units of 16
-  // tiles 198 us, 1,584 of 8 185 us, 3,168 of 4 188 us).
-  int64_t tiles = 0;
-  for (int i = 0; i < P.nitem; ++i)
-    if (P.item_group[i] == gi)
-      tiles += (int64_t)P.items[i].Na * ((P.items[i].Nb + g.tn - 1) / g.tn);
-  const int len = tiles < 2048 * 8 ? std::min(g.tiles_per_wg, 8) : g.tiles_per_wg;
+  const int len = pair_unit_tiles(g.tiles_per_wg, [&](int l) {
+    int64_t units = 0;
+    for (int i = 0; i < P.nitem; ++i)
+      if (P.item_group[i] == gi)
+        units += (int64_t)((P.items[i].Na + l - 1) / l) * ((P.items[i].Nb + g.tn - 1) / g.tn);
+    return units;
+  });
   for (int i = 0; i < P.nitem; ++i) {
     if (P.item_group[i] != gi) continue;
     const Item& I = P.items[i];
