@@ -107,7 +107,11 @@ typedef struct {
   int64_t max_workspace; /* workspace cap in bytes, 0 = no cap                       */
   const char* tune_cache;/* autotuner cache file (read/written) or NULL: one line per
                             active size n, "n tile tiles_per_workgroup" (tile
-                            -32 or -64: one wave per alpha string)            */
+                            -32 or -64: one wave per alpha string).  Up to 10
+                            orbitals tiles_per_workgroup is the most: a plan
+                            with few alpha strings takes shorter units, and a
+                            negative number -k was timed on a plan that allowed
+                            k at most (larger plans are timed anew)           */
 } mbefci_opts;
 
 typedef struct {

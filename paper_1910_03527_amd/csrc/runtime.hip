@@ -213,7 +213,8 @@ struct mbefci_ctx {
   void* alloc_user = nullptr;
   std::unique_ptr<Plan> plan;
   // autotuned sigma-contraction schedule per active size n: (tile width,
-  // tiles per workgroup); loaded from / saved to opts.tune_cache when set
+  // tiles per workgroup as schedule_kept gives them); loaded from / saved to
+  // opts.tune_cache when set
   std::map<int, std::pair<int, int>> tuned;
   bool cache_loaded = false;
   double ms_tune = 0.0;
@@ -540,11 +541,12 @@ int tile_for(mbefci_ctx* c, int n) {
 // tiles per workgroup: the tuned number, 0 for the plan's own choice (build_tiles)
 int tpw_for(mbefci_ctx* c, int n) {
   auto it = c->tuned.find(n);
-  if (c->opts.tile == 0 && it != c->tuned.end()) return it->second.second;
+  if (c->opts.tile == 0 && it != c->tuned.end()) return schedule_steps(it->second.second);
   return 0;
 }
 
-// tune cache: one line per active size, "n tile tiles_per_wg"
+// tune cache: one line per active size, "n tile tiles_per_wg" (the last as
+// schedule_kept gives it)
 void load_tune_cache(mbefci_ctx* c) {
   if (c->cache_loaded || !c->opts.tune_cache) return;
   c->cache_loaded = true;
@@ -554,7 +556,7 @@ void load_tune_cache(mbefci_ctx* c) {
   char line[128];
   while (std::fgets(line, sizeof(line), f))
     if (std::sscanf(line, "%d %d %d", &n, &tn, &tpw) == 3 && tile_supported(n, tn) &&
-        tpw >= 1 && tpw <= 256)
+        ((tpw >= 1 && tpw <= 256) || (n <= kStringMax && tpw < 0 && tpw > -32)))
       c->tuned[n] = {tn, tpw};
   std::fclose(f);
 }
@@ -563,7 +565,8 @@ void save_tune_cache(mbefci_ctx* c) {
   FILE* f = std::fopen(c->opts.tune_cache, "w");
   if (!f) return;
   std::fprintf(f, "# n tile tiles_per_workgroup (sigma contraction schedule, gfx950; a negative\n"
-                 "# tile is that many consecutive determinants per flattened tile)\n");
+                 "# tile: one wave per alpha string; a negative third number -k: the plan\n"
+                 "# allowed k at most, larger plans are timed anew)\n");
   for (auto& kv : c->tuned) std::fprintf(f, "%d %d %d\n", kv.first, kv.second.first, kv.second.second);
   std::fclose(f);
 }
@@ -1143,11 +1146,16 @@ int count_active(mbefci_ctx* c, Plan& P, const View& v) {
   return h;
 }
 
+// The longest unit that group gi's plan lets a schedule have.
+int unit_limit(const Plan& P, int gi, int tn) {
+  return P.groups[gi].n <= kStringMax ? string_unit_limit(string_steps(P, gi, tn)) : INT32_MAX;
+}
+
 // Autotuner: for every active size n of the plan that has no tuned schedule
-// yet, time the contraction kernel over the group's whole work list for each
-// candidate (tile width, tiles per workgroup) on the live plan (guess vectors
-// in slot 0; the kernels' cost does not depend on the values) and keep the
-// fastest.  Results persist in the context and, with opts.tune_cache, in a
+// yet (or none that covers a plan of its size, schedule.h), time the
+// contraction kernel over the group's whole work list for each candidate (tile
+// width, tiles per workgroup) on the live plan (guess vectors in slot 0; the
+// kernels' cost does not depend on the values) and keep the fastest.  Results persist in the context and, with opts.tune_cache, in a
 // file.  Runs once per plan, before the iteration graph is captured.
 void autotune(mbefci_ctx* c, Plan& P) {
   if (c->opts.tile != 0 || P.tuned) return;
@@ -1161,10 +1169,12 @@ void autotune(mbefci_ctx* c, Plan& P) {
   HIPCHK(hipEventCreate(&e1));
   for (size_t gi = 0; gi < P.groups.size(); ++gi) {
     Group& g = P.groups[gi];
-    if (c->tuned.count(g.n)) {
-      if (g.tn != c->tuned[g.n].first || g.tiles_per_wg != c->tuned[g.n].second) {
-        g.tn = c->tuned[g.n].first;
-        g.tiles_per_wg = c->tuned[g.n].second;
+    const auto kept = c->tuned.find(g.n);
+    if (kept != c->tuned.end() &&
+        schedule_covers(kept->second.second, unit_limit(P, (int)gi, kept->second.first))) {
+      if (g.tn != kept->second.first || g.tiles_per_wg != tpw_for(c, g.n)) {
+        g.tn = kept->second.first;
+        g.tiles_per_wg = tpw_for(c, g.n);
         changed = true;
       }
       continue;
@@ -1173,7 +1183,9 @@ void autotune(mbefci_ctx* c, Plan& P) {
     std::pair<int, int> pick{g.tn, g.tiles_per_wg};
     for (int tn : {32, 64, 128, -32, -64}) {
       if (!tile_supported(g.n, tn)) continue;
+      const int limit = unit_limit(P, (int)gi, tn);
       for (int tpw : {4, 8, 16, 32}) {
+        if (tpw > 4 && tpw / 2 >= limit) break;  // the work list just timed
         g.tn = tn;
         g.tiles_per_wg = tpw;
         build_tiles(P, (int)gi);
@@ -1198,9 +1210,9 @@ void autotune(mbefci_ctx* c, Plan& P) {
         }
       }
     }
-    c->tuned[g.n] = pick;
+    c->tuned[g.n] = {pick.first, schedule_kept(pick.second, unit_limit(P, (int)gi, pick.first))};
     g.tn = pick.first;
-    g.tiles_per_wg = pick.second;
+    g.tiles_per_wg = tpw_for(c, g.n);
     changed = true;
   }
   HIPCHK(hipEventDestroy(e0));

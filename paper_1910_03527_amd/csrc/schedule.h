@@ -18,6 +18,19 @@ inline int string_unit_steps(int tuned, int64_t steps) {
   return std::min(tuned > 0 ? tuned : 16, string_unit_limit(steps));
 }
 
+// The tuner times 4, 8, 16 and 32 steps per unit as far as the plan's limit
+// tells them apart, and keeps one schedule per active size for every later
+// plan.  A best length at a limit below 32 says nothing of longer ones: it is
+// kept as -limit, and a plan with a higher limit (and more than the one length
+// to choose from) is timed anew.
+inline int schedule_kept(int best, int limit) {
+  return limit < 32 && best >= limit ? -limit : best;
+}
+inline bool schedule_covers(int kept, int limit) {
+  return kept > 0 || limit <= std::max(4, -kept);
+}
+inline int schedule_steps(int kept) { return kept > 0 ? kept : std::max(16, -kept); }
+
 // Above kStringMax orbitals a unit is a number of tiles: the tuned one, or (0)
 // 16, or 8 where the busiest CU then takes fewer tiles in all.  Units are
 // dealt to the CUs, and the last, partly filled turn costs as much as a full

@@ -43,3 +43,41 @@ def test_noalloc_sigma_of_no_and_one_orbital(n, na, nb):
         assert float(out[0]) == 2.0 * (0.25 + 0.75 * (na + nb) + 0.5 * na * nb)
     finally:
         ctx.close()
+
+
+def test_small_plan_leaves_the_units_of_larger_ones_open(tmp_path):
+    """One CASCI has one length of work unit: the tuner keeps its tile width and
+    times a batch of the same size anew; the energies are the same bit for bit
+    (identical problems, and the order of every sum is fixed)."""
+    from paper_1910_03527_amd import Context
+    cache = tmp_path / "tune.txt"
+    h, g = W.synthetic(8, 31)
+    hd, gd = _dev(h), _dev(g)
+
+    def entry():
+        return [int(x) for x in cache.read_text().splitlines()[-1].split()]
+
+    c = Context(0, tune_cache=str(cache))
+    try:
+        _log("tune one CAS(8,8)")
+        e1 = c.casci([hd], [gd], 4, 4)[0]
+        n, _, steps = entry()
+        assert (n, steps) == (8, -1)  # 70 strings: one step per unit
+        ms = c.last_stats["ms_tune"]
+        c.casci([hd], [gd], 4, 4)
+        assert c.last_stats["ms_tune"] - ms < 1.0  # kept
+        _log("tune 400 CAS(8,8)s")
+        e = c.casci([hd] * 400, [gd] * 400, 4, 4)
+        n, _, steps = entry()
+        assert n == 8 and (steps >= 4 or steps <= -5)
+        assert all(x == e1 for x in e)
+    finally:
+        c.close()
+    # read back and kept by the same plan
+    _log("reread")
+    c = Context(0, tune_cache=str(cache))
+    try:
+        assert all(x == e1 for x in c.casci([hd] * 400, [gd] * 400, 4, 4))
+        assert entry() == [n, entry()[1], steps]
+    finally:
+        c.close()

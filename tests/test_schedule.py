@@ -16,7 +16,14 @@ DRIVER = r"""
 using namespace mbefci;
 int main(int argc, char** argv) {
   const int tuned = std::atoi(argv[2]);
-  if (argv[1][0] == 's') {  // steps of up to 10 orbitals
+  if (argv[1][0] == 'k') {  // tuner: kept steps of a best length under a limit
+    const int limit = std::atoi(argv[3]), kept = schedule_kept(tuned, limit);
+    std::printf("%d", kept);
+  } else if (argv[1][0] == 'c') {
+    std::printf("%d", (int)schedule_covers(tuned, std::atoi(argv[3])));
+  } else if (argv[1][0] == 'u') {  // units of a plan of `limit` under a kept number
+    std::printf("%d", string_unit_steps(schedule_steps(tuned), 1024ll * std::atoll(argv[3])));
+  } else if (argv[1][0] == 's') {  // steps of up to 10 orbitals
     std::printf("%d", string_unit_steps(tuned, std::atoll(argv[3])));
   } else {                  // tiles above: CASCIs, Na, beta blocks
     const long long n = std::atoll(argv[3]), na = std::atoll(argv[4]), nblk = std::atoll(argv[5]);
@@ -54,3 +61,19 @@ def test_steps_per_unit_leave_four_units_per_cu(rule, tuned):
         assert 1 <= got <= most
         assert got == 1 or steps // got >= 1024
         assert got == most or steps // (got + 1) < 1024
+
+
+@pytest.mark.parametrize("limit", [1, 3, 4, 6, 16, 20, 31, 32, 100])
+def test_a_kept_schedule_gives_its_own_plan_the_timed_unit(rule, limit):
+    """Whatever length was best, the plan it was timed on (and any other of
+    that limit) takes it again without being timed, and a plan of a higher limit
+    is timed unless the length was below the limit."""
+    for best in (4, 8, 16, 32):
+        if best > 4 and best // 2 >= limit:
+            continue  # not a candidate of its own
+        kept = rule("k", best, limit)
+        assert rule("c", kept, limit) == 1
+        assert rule("u", kept, limit) == min(best, limit)
+        assert (kept < 0) == (best >= limit and limit < 32)
+        if kept < 0:
+            assert rule("c", kept, max(limit, 4) + 1) == 0
