@@ -104,7 +104,11 @@ typedef struct {
                             (an order with more tuples, or more than 2^25
                             determinants, is solved in several batches);
                             0 = 65536 (default 0)                            */
-  int64_t max_workspace; /* workspace cap in bytes, 0 = no cap                       */
+  int64_t max_workspace; /* workspace cap in bytes, 0 = no cap.  Where it has no room for the
+                            string Hamiltonians of all CASCIs of up to 10
+                            orbitals, sigma sweeps form them in passes, within
+                            what the pair matrices and one pass of G would take
+                            (at least one CASCI's, up to 0.7 MB)              */
   const char* tune_cache;/* autotuner cache file (read/written) or NULL: one line per
                             active size n, "n tile tiles_per_workgroup" (tile
                             -32 or -64: one wave per alpha string).  Up to 10

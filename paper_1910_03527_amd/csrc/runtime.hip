@@ -102,7 +102,8 @@ struct Group {
 
 // One pass of a sigma sweep: a contiguous item range whose G blocks are
 // written by the contraction kernels and read back by the gather before the
-// next pass reuses the same G memory.
+// next pass reuses the same G memory (and that of its sigma operands, where a
+// plan forms them pass by pass).
 struct Pass {
   int item_lo = 0, item_hi = 0;
   std::vector<int> tile_lo, tile_hi;  // per group
@@ -139,9 +140,14 @@ struct Plan {
   Work* d_same = nullptr;
   bool same_small = false;    // 16 x 16 tiles instead of 32 x 64
   int64_t operand_most = 0;   // largest sigma_operand_size
+  // most doubles of sigma operands held at once, and whether they are formed
+  // pass by pass in every sweep because all of them are more (operand_budget)
+  int64_t operand_cap = INT64_MAX;
+  bool operand_passes = false;
   int nitem = 0, nchunk = 0, nblock = 0, nseg = 0;
   int gather_lds = 0;  // LDS reserved per gather workgroup (an occupancy cap), gather_lds_bytes
   int64_t ntot = 0, gtot = 0, wtot = 0;
+  int64_t wres = 0;  // start of the sigma operands in W, after the pair matrices
   int nsingle = 0;
   int64_t ndet_total = 0;
   // device
@@ -212,6 +218,7 @@ struct mbefci_ctx {
   void (*release_fn)(void*, void*) = nullptr;
   void* alloc_user = nullptr;
   std::unique_ptr<Plan> plan;
+  bool gw_spare = false;  // a plan is being laid out: G and W are an earlier one's
   // autotuned sigma-contraction schedule per active size n: (tile width,
   // tiles per workgroup as schedule_kept gives them); loaded from / saved to
   // opts.tune_cache when set
@@ -261,9 +268,16 @@ T* arena(mbefci_ctx* c, const std::string& name, size_t count, bool* grown = nul
   DevBuf& b = c->bufs[name];
   if (b.bytes < bytes) {
     release_buf(c, b);
-    size_t total = 0;
-    for (auto& kv : c->bufs) total += kv.second.bytes;
-    if (c->opts.max_workspace > 0 && (int64_t)(total + bytes) > c->opts.max_workspace)
+    auto over = [&] {
+      size_t total = 0;
+      for (auto& kv : c->bufs) total += kv.second.bytes;
+      return c->opts.max_workspace > 0 && (int64_t)(total + bytes) > c->opts.max_workspace;
+    };
+    if (c->gw_spare && over()) {
+      release_buf(c, c->bufs["G"]);
+      release_buf(c, c->bufs["W"]);
+    }
+    if (over())
       throw Error(MBEFCI_ENOMEM, "workspace cap exceeded by arena '" + name + "'");
     if (c->alloc_fn) {
       b.p = c->alloc_fn(bytes, c->alloc_user);
@@ -619,14 +633,80 @@ void build_tiles(Plan& P, int gi) {
   }
 }
 
+int64_t pass_bytes(mbefci_ctx* c) {
+  return c->opts.sigma_pass_mb > 0 ? (int64_t)c->opts.sigma_pass_mb << 20 : INT64_MAX;
+}
+int64_t operand_size(const Item& I) {
+  return sigma_operand_size(I.n, I.Na, I.Nb, I.na == I.nb);
+}
+bool has_operands(const Item& I) { return I.ndet > 1 && !I.sym && I.n <= kStringMax; }
+int64_t line_up(int64_t x) { return (x + 15) & ~(int64_t)15; }  // a 128-byte line
+
+// Sigma operands under a workspace cap.  A plan holds those of all its CASCIs
+// where the cap has room for them and for what later calls on the plan take
+// (operand_room).  Else it holds at most operand_budget doubles of them and
+// forms them pass by pass in every sweep: no more than the contraction of
+// every pair would take for the same CASCIs - their matrices W and one pass of
+// G - less the lists that only the string operators need, so that a batch
+// which fits a cap in one form fits it in the other; at least the largest
+// CASCI's (682 KB).  Two dense string Hamiltonians are more than that where
+// one spin's strings are few (252 x 1 strings: 682 against 123 KB) or
+// sigma_pass_mb keeps G small.  Hubbard-16's expansion in passes of 64 MiB: 47
+// ms with its operands formed in every sweep (0.26 of a sweep's 1.6 ms), 39 with
+// all of them held.
+int64_t operand_budget(mbefci_ctx* c, const Plan& P, int64_t psel_bytes) {
+  const int64_t cap = pass_bytes(c);
+  int64_t w = 0, most = 0, strings = 0, gpass[2] = {0, 0}, gmax[2] = {0, 0};
+  for (const Item& I : P.items) {
+    if (I.ndet <= 1 || I.sym) continue;
+    const bool op = has_operands(I);
+    if (op) {
+      w += (int64_t)I.kpad * I.kpad;
+      most = std::max(most, operand_size(I));
+      strings += I.Na;
+    }
+    for (int k = 0; k < 2; ++k) {  // G of every CASCI, G of those without operands
+      if (k == 1 && op) continue;
+      const int64_t rows = op ? I.npair - I.n : I.npair;
+      const int64_t gb = rows * I.Na * g_stride(I.Nb);
+      if (gpass[k] > 0 && (line_up(gpass[k]) + gb) * 8 > cap) gpass[k] = 0;
+      gpass[k] = line_up(gpass[k]) + gb;
+      gmax[k] = std::max(gmax[k], gpass[k]);
+    }
+  }
+  const int64_t lists = psel_bytes + sizeof(Work) * ((int64_t)P.same.size() + 2 * strings) +
+                        64 * (int64_t)P.nitem + 2048;
+  return std::max(most, w + std::max<int64_t>(gmax[0] - gmax[1], 0) - lists / 8);
+}
+// Whether `doubles` of G and W fit the cap beside the allocated arenas and what
+// later calls may add: the RDM partials, the gradient's lists, the tuner's and
+// the timer's copies (a bound per item) and the buffers of the peak probe.
+bool operand_room(mbefci_ctx* c, const Plan& P, int64_t doubles) {
+  int64_t used = 8 * doubles + ((int64_t)600 << 20);
+  for (const auto& kv : c->bufs)
+    if (kv.first != "G" && kv.first != "W") used += (int64_t)kv.second.bytes;
+  for (const Item& I : P.items) {
+    const int64_t strips = (int64_t)I.Na * ((I.Nb + 63) / 64);
+    used += (std::min<int64_t>(strips, 520) + 1) * (8 * (int64_t)I.kpad * I.kpad + 32) +
+            32 * (strips + I.Na) + 16384;
+  }
+  return used <= c->opts.max_workspace;
+}
+
 // Sigma passes (contiguous item ranges whose G blocks stay below
-// sigma_pass_mb): sets every item's pass-relative G offset and the pass work
-// ranges; returns the largest pass's G size (doubles).
+// sigma_pass_mb, and whose sigma operands stay within the plan's budget where
+// they are formed pass by pass): sets every item's pass-relative G offset, the
+// offset of its sigma operands and the pass work ranges; returns the largest
+// pass's G size (doubles).
 int64_t build_passes(mbefci_ctx* c, Plan& P) {
   {
-    const int64_t cap = c->opts.sigma_pass_mb > 0 ? (int64_t)c->opts.sigma_pass_mb << 20 : INT64_MAX;
+    const int64_t cap = pass_bytes(c);
+    int64_t operands = 0;
+    for (const Item& I : P.items)
+      if (has_operands(I)) operands = line_up(operands) + operand_size(I);
+    P.operand_passes = operands > P.operand_cap;
     P.passes.clear();
-    int64_t gpass = 0, gmax = 0;
+    int64_t gpass = 0, gmax = 0, wpass = 0, wmax = 0;
     Pass cur;
     cur.tile_lo.assign(P.groups.size(), INT32_MAX);
     cur.tile_hi.assign(P.groups.size(), 0);
@@ -639,6 +719,7 @@ int64_t build_passes(mbefci_ctx* c, Plan& P) {
       if (cur.seg_lo == INT32_MAX) cur.seg_lo = cur.seg_hi = 0;
       P.passes.push_back(cur);
       gmax = std::max(gmax, gpass);
+      if (P.operand_passes) wpass = 0;
       cur = Pass();
       cur.item_lo = end;
       cur.tile_lo.assign(P.groups.size(), INT32_MAX);
@@ -651,10 +732,19 @@ int64_t build_passes(mbefci_ctx* c, Plan& P) {
       Item& I = P.items[i];
       if (I.ndet <= 1 || I.sym) continue;
       const int64_t gb = I.n <= kStringMax ? 0 : (int64_t)I.npair * I.Na * g_stride(I.Nb);
-      if (gpass > 0 && (((gpass + 15) & ~(int64_t)15) + gb) * 8 > cap) close(i);
-      gpass = (gpass + 15) & ~(int64_t)15;  // a 128-byte line
+      const int64_t op = has_operands(I) ? operand_size(I) : 0;
+      if ((gpass > 0 && (line_up(gpass) + gb) * 8 > cap) ||
+          (P.operand_passes && wpass > 0 && line_up(wpass) + op > P.operand_cap))
+        close(i);
+      gpass = line_up(gpass);
       I.goff = gpass;
       gpass += gb;
+      if (op > 0) {
+        wpass = line_up(wpass);
+        I.woff = P.wres + wpass;
+        wpass += op;
+        wmax = std::max(wmax, wpass);
+      }
       const int g = P.item_group[i];
       cur.tile_lo[g] = std::min(cur.tile_lo[g], P.groups[g].item_lo[i]);
       cur.tile_hi[g] = std::max(cur.tile_hi[g], P.groups[g].item_hi[i]);
@@ -664,6 +754,7 @@ int64_t build_passes(mbefci_ctx* c, Plan& P) {
       }
     }
     close(P.nitem);
+    P.wtot = P.wres + wmax;
     return gmax;
   }
 }
@@ -752,16 +843,16 @@ void build_same_units(Plan& P) {
   int64_t large = 0;
   for (int i = 0; i < P.nitem; ++i) {
     const Item& I = P.items[i];
-    if (I.ndet <= 1 || I.sym || I.n > kStringMax) continue;
+    if (!has_operands(I)) continue;
     large += (int64_t)tiles(I.Na, 32) * tiles(I.Nb, 64);
-    P.operand_most = std::max(P.operand_most, sigma_operand_size(I.n, I.Na, I.Nb, I.na == I.nb));
+    P.operand_most = std::max(P.operand_most, operand_size(I));
   }
   P.same_small = large < 2048;
   const int wa = P.same_small ? 16 : 32, wb = P.same_small ? 16 : 64;
   for (int i = 0; i < P.nitem; ++i) {
     const Item& I = P.items[i];
     P.same_lo[i] = (int)P.same.size();
-    if (I.ndet > 1 && !I.sym && I.n <= kStringMax)
+    if (has_operands(I))
       for (int a = 0; a < tiles(I.Na, wa); ++a)
         for (int b = 0; b < tiles(I.Nb, wb); ++b) P.same.push_back(Work{i, a, b, 0});
     P.same_hi[i] = (int)P.same.size();
@@ -774,7 +865,8 @@ void build_same_units(Plan& P) {
 // of at most kMaxPspace determinants exactly) under both corrections; its
 // correction on the P block is used with the diagonal correction only.
 
-void finalize_plan(mbefci_ctx* c, Plan& P, int nguess_slots) {
+// bounded: what the call allocates after this plan has a bound (operand_room).
+void finalize_plan(mbefci_ctx* c, Plan& P, int nguess_slots, bool bounded = true) {
   const int mmax = c->opts.max_space;
   P.nitem = (int)P.items.size();
   int64_t off = 0, woff = 0;
@@ -849,11 +941,12 @@ void finalize_plan(mbefci_ctx* c, Plan& P, int nguess_slots) {
     P.ndet_total += I.ndet;
     if (I.ndet > 1) {
       I.goff = 0;  // set by build_passes and build_sym_work
-      woff = (woff + 15) & ~(int64_t)15;  // a 128-byte line
-      I.woff = woff;
-      woff += sy || I.n > kStringMax
-                  ? (int64_t)I.kpad * I.kpad
-                  : sigma_operand_size(I.n, I.Na, I.Nb, I.na == I.nb);
+      I.woff = 0;  // operands: set by build_passes
+      if (!has_operands(I)) {
+        woff = line_up(woff);
+        I.woff = woff;
+        woff += (int64_t)I.kpad * I.kpad;
+      }
     } else {
       I.goff = 0;
       I.woff = 0;
@@ -891,12 +984,13 @@ void finalize_plan(mbefci_ctx* c, Plan& P, int nguess_slots) {
     }
   }
   for (size_t gi = 0; gi < P.groups.size(); ++gi) build_tiles(P, (int)gi);
-  int64_t goff = build_passes(c, P);
-  build_sym_work(P, goff);
   build_same_units(P);
+  int64_t psel_keys = 0;  // candidates of the chunked P-space selection
+  for (const Item& I : P.items)
+    if (I.ndet > select_chunk(I.ndet))
+      psel_keys += (I.ndet + select_chunk(I.ndet) - 1) / select_chunk(I.ndet) * kMaxPspace;
+  P.wres = line_up(woff);
   P.ntot = std::max<int64_t>(off, 64);
-  P.gtot = goff;
-  P.wtot = woff;
   P.nchunk = (int)P.chunks.size();
   P.nblock = (int)P.blocks.size();
   P.nseg = (int)P.segs.size();
@@ -916,6 +1010,7 @@ void finalize_plan(mbefci_ctx* c, Plan& P, int nguess_slots) {
   }
 
   bool grown = false;
+  c->gw_spare = true;  // no plan uses them until they are laid out anew below
   P.d_items = arena<Item>(c, "items", P.nitem, &grown);
   P.d_chunks = arena<Work>(c, "chunks", P.nchunk, &grown);
   P.d_blocks = arena<Work>(c, "blocks", P.nblock, &grown);
@@ -962,8 +1057,6 @@ void finalize_plan(mbefci_ctx* c, Plan& P, int nguess_slots) {
   // to it near convergence)
   P.R = arena<double>(c, "resid", P.ntot, &grown);
   P.X = arena<double>(c, "ritz", P.ntot, &grown);
-  P.G = arena<double>(c, "G", std::max<int64_t>(P.gtot, 1), &grown);
-  P.W = arena<double>(c, "W", std::max<int64_t>(P.wtot, 1), &grown);
   P.part = arena<double>(c, "part", (size_t)std::max(P.nchunk, 1) * kPartStride, &grown);
   P.f = arena<double>(c, "f", P.nitem + 2, &grown);
   P.inc = arena<double>(c, "inc", P.nitem, &grown);
@@ -973,6 +1066,27 @@ void finalize_plan(mbefci_ctx* c, Plan& P, int nguess_slots) {
   for (size_t g = 0; g < P.groups.size(); ++g)
     P.groups[g].d_tiles =
         arena<Work>(c, "tiles" + std::to_string(g), P.groups[g].tiles.size(), &grown);
+  P.d_same = arena<Work>(c, "same", std::max<size_t>(P.same.size(), 1), &grown);
+  P.operand_cap = INT64_MAX;
+  int64_t goff = build_passes(c, P);
+  if (c->opts.max_workspace > 0 && !(bounded && operand_room(c, P, goff + P.wtot))) {
+    P.operand_cap = operand_budget(c, P, 13 * psel_keys);
+    goff = build_passes(c, P);
+  }
+  build_sym_work(P, goff);
+  P.gtot = goff;
+  if (c->opts.max_workspace > 0) {  // an earlier plan's larger ones give way
+    const int64_t need[2] = {std::max<int64_t>(8 * P.gtot, 256), std::max<int64_t>(8 * P.wtot, 256)};
+    DevBuf* gw[2] = {&c->bufs["G"], &c->bufs["W"]};
+    int64_t total = 0;
+    for (const auto& kv : c->bufs) total += (int64_t)kv.second.bytes;
+    for (int k = 0; k < 2; ++k) total += std::max<int64_t>(need[k] - (int64_t)gw[k]->bytes, 0);
+    for (int k = 0; k < 2; ++k)
+      if (total > c->opts.max_workspace && (int64_t)gw[k]->bytes > need[k]) release_buf(c, *gw[k]);
+  }
+  c->gw_spare = false;
+  P.G = arena<double>(c, "G", std::max<int64_t>(P.gtot, 1), &grown);
+  P.W = arena<double>(c, "W", std::max<int64_t>(P.wtot, 1), &grown);
   for (size_t g = 0; g < P.sym_groups.size(); ++g) {
     P.sym_groups[g].d_tiles = arena<Work>(c, "symtiles" + std::to_string(g),
                                           std::max<size_t>(P.sym_groups[g].tiles.size(), 1), &grown);
@@ -986,7 +1100,6 @@ void finalize_plan(mbefci_ctx* c, Plan& P, int nguess_slots) {
   upload(c, P.d_chunks, P.chunks);
   upload(c, P.d_blocks, P.blocks);
   upload(c, P.d_segs, P.segs);
-  P.d_same = arena<Work>(c, "same", std::max<size_t>(P.same.size(), 1), &grown);
   upload(c, P.d_same, P.same);
   for (auto& g : P.groups) upload(c, g.d_tiles, g.tiles);
   (void)nguess_slots;
@@ -1009,7 +1122,8 @@ View single(const Plan& P, int i) {
 // One launch of the sigma sweep: kind 0 = contraction of group `group`,
 // kind 1 = gather, kind 2 = blocked contraction of sym group `group`, kind 3 =
 // blocked gather, kind 4 = same-spin part (before the group's kernel, which
-// adds to it); work-list range [lo, lo + cnt).
+// adds to it), kind 5 = sigma operands of the items; work-list range
+// [lo, lo + cnt).
 struct SigmaLaunch {
   int kind, group, lo, cnt;
 };
@@ -1036,6 +1150,7 @@ std::vector<SigmaLaunch> sigma_launches(const Plan& P, const View& v) {
     const int g = P.item_group[v.item];
     if (g < 0) return out;
     const bool strings = P.groups[g].n <= kStringMax;
+    if (strings && P.operand_passes) out.push_back({5, -1, v.item, 1});
     if (strings)
       out.push_back({4, -1, P.same_lo[v.item], P.same_hi[v.item] - P.same_lo[v.item]});
     out.push_back({0, g, P.groups[g].item_lo[v.item],
@@ -1044,9 +1159,16 @@ std::vector<SigmaLaunch> sigma_launches(const Plan& P, const View& v) {
     return out;
   }
   if (P.has_sym) sym_launches(P, -1, out);
-  if (!P.same.empty()) out.push_back({4, -1, 0, (int)P.same.size()});
+  if (!P.same.empty() && !P.operand_passes) out.push_back({4, -1, 0, (int)P.same.size()});
   for (const Pass& ps : P.passes) {
     bool any = false;
+    if (P.operand_passes && ps.item_hi > ps.item_lo) {
+      const int lo = P.same_lo[ps.item_lo], hi = P.same_hi[ps.item_hi - 1];
+      if (hi > lo) {
+        out.push_back({5, -1, ps.item_lo, ps.item_hi - ps.item_lo});
+        out.push_back({4, -1, lo, hi - lo});
+      }
+    }
     for (size_t g = 0; g < P.groups.size(); ++g)
       if (ps.tile_hi[g] > ps.tile_lo[g]) {
         out.push_back({0, (int)g, ps.tile_lo[g], ps.tile_hi[g] - ps.tile_lo[g]});
@@ -1075,6 +1197,8 @@ void sigma_launch(mbefci_ctx* c, Plan& P, const SigmaLaunch& L, int slot) {
   } else if (L.kind == 4) {
     launch_sigma_same_spin(P.d_items, P.d_same + L.lo, L.cnt, P.same_small, P.W, P.V, P.ntot, P.S,
                            P.st, slot, c->stream);
+  } else if (L.kind == 5) {
+    launch_sigma_operands(P.d_items + L.lo, L.cnt, P.operand_most, P.hams, P.W, c->stream);
   } else {
     launch_sigma_sym_gather(P.d_items, P.d_sym_blocks + L.lo, L.cnt, P.G, P.S, P.ntot, P.st, slot,
                             c->stream);
@@ -1082,8 +1206,9 @@ void sigma_launch(mbefci_ctx* c, Plan& P, const SigmaLaunch& L, int slot) {
 }
 
 // The sigma operands of the CASCIs of up to kStringMax orbitals, from their
-// folded Hamiltonians.
+// folded Hamiltonians (unless every sweep forms them).
 void build_operands(mbefci_ctx* c, Plan& P) {
+  if (P.operand_passes) return;
   launch_sigma_operands(P.d_items, P.nitem, P.operand_most, P.hams, P.W, c->stream);
   HIPCHK(hipGetLastError());
 }
@@ -2389,7 +2514,7 @@ int mbefci_mbe_screened(mbefci_ctx* c, const mbefci_problem* pb, const mbefci_sc
             P.item_symtab.push_back(&sym_tab(c, I.n, I.na, I.nb, os, 0));
           }
         }
-        finalize_plan(c, P, c->opts.nguess);
+        finalize_plan(c, P, c->opts.nguess, false);  // the orders' lists are unknown
         uint64_t* d_masks = arena<uint64_t>(c, "scr_items", masks.size());
         upload(c, d_masks, masks);
         launch_mbe_setup_list(&P.sp, d_masks, P.d_items, P.nitem, pb->h1, pb->eri, pb->e_const,
@@ -2701,6 +2826,13 @@ int mbefci_time_kernels(mbefci_ctx* c, int32_t reps, mbefci_kernel_time* out, in
                             (I.na == I.nb ? 0.0 : (double)I.Nb * I.Nb));
           }
         name = "sigma_same_spin";
+      } else if (L.kind == 5) {
+        for (int i = L.lo; i < L.lo + L.cnt; ++i)
+          if (has_operands(P.items[i])) {
+            nd += (double)P.items[i].ndet;
+            bytes += 8.0 * operand_size(P.items[i]);
+          }
+        name = "sigma_operands";
       } else {
         for (int w = L.lo; w < L.lo + L.cnt; ++w)
           if (P.sym_blocks[w].begin == 0) {
