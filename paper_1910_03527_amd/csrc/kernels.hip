@@ -2869,8 +2869,8 @@ __global__ void __launch_bounds__(256, EXACT ? 2 : 1) k_pspace_eigen(
   static_assert(PMAX <= PM && PMAX <= NT, "a thread per P row");
   __shared__ double refl[EXACT ? PMAX * (PMAX - 1) / 2 : 1], beta[EXACT ? PMAX : 1];
   __shared__ double pv[2][PMAX], xo[2][PMAX], dd[PMAX], ee[PMAX], es[PMAX], zz[PMAX];
-  __shared__ double ll[PMAX], ip[PMAX], bb[PMAX], lo_hi[2];
-  __shared__ int neg[NT];
+  __shared__ double ll[PMAX], ip[PMAX], bb[PMAX];
+  __shared__ int first[2][NT / 64];
   const int it = plist[blockIdx.x];
   const Item& I = items[it];
   DavState& S = st[it];
@@ -3026,14 +3026,9 @@ __global__ void __launch_bounds__(256, EXACT ? 2 : 1) k_pspace_eigen(
     ghi = fmin(ghi, -(dd[i] + (el + er)));
     gsc = fmin(gsc, -(fabs(dd[i]) + 2.0 * er));
   }
-  glo = row_min(glo);  // (DPP: with every lane active)
+  glo = row_min(glo);  // (DPP: with every lane active); the same in every row
   ghi = -row_min(ghi);
   const double scale = -row_min(gsc);
-  __syncthreads();
-  if (t == 0) {
-    lo_hi[0] = glo;
-    lo_hi[1] = ghi;
-  }
   if (t < PMAX) {
     es[t] = t > 0 && t < n ? ee[t - 1] * ee[t - 1] : 0.0;
     // rows past n keep the sign of the minor before them
@@ -3042,8 +3037,8 @@ __global__ void __launch_bounds__(256, EXACT ? 2 : 1) k_pspace_eigen(
   __syncthreads();
   // 7 rounds of 256 points narrow the interval by 256^7 >= 1.8e16, to the
   // rounding level of the spectrum
+  double lo = glo, hi = ghi;  // the same in every thread
   for (int round = 0; round < 7; ++round) {
-    const double lo = lo_hi[0], hi = lo_hi[1];
     const double x = lo + (hi - lo) * (double)(t + 1) / (double)NT;
     // an eigenvalue at or below x: a leading minor of T - x that is not
     // positive.  The minors' own recurrence has one multiply-add on its chain
@@ -3061,18 +3056,24 @@ __global__ void __launch_bounds__(256, EXACT ? 2 : 1) k_pspace_eigen(
       p = __builtin_amdgcn_ldexp(p, ex);
       pm = __builtin_amdgcn_ldexp(pm, ex);
     }
-    const int below = !(mn > 0.0);
-    // the first point with an eigenvalue at or below it (the answer at the
-    // previous point is the previous thread's)
-    neg[t] = below;
+    // the lowest point with an eigenvalue at or below it ends the interval, the
+    // point before it begins it.  One choice for the block: that the test is
+    // monotone in x under rounding is not known, and neighbouring points are
+    // an ulp apart in the last round.
+    const unsigned long long below = __ballot(!(mn > 0.0));
+    int* fw = first[round & 1];
+    if ((t & 63) == 0) fw[t >> 6] = below ? t + __builtin_ctzll(below) : NT;
     __syncthreads();
-    if (below && (t == 0 || neg[t - 1] == 0)) {
-      lo_hi[0] = lo + (hi - lo) * (double)t / (double)NT;
-      lo_hi[1] = x;
+    int f = fw[0];
+#pragma unroll
+    for (int w = 1; w < NT / 64; ++w) f = min(f, fw[w]);
+    if (f < NT) {
+      const double l = lo;
+      lo = l + (hi - l) * (double)f / (double)NT;
+      hi = l + (hi - l) * (double)(f + 1) / (double)NT;
     }
-    __syncthreads();
   }
-  const double lam0 = 0.5 * (lo_hi[0] + lo_hi[1]);
+  const double lam0 = 0.5 * (lo + hi);
   // ---- eigenvector of T for lam0 by one wave: inverse iteration,
   // (lam0 - T) z = z, with pivots floored at 1e-15 of the spectrum's scale
   if (t < 64) {
