@@ -3075,10 +3075,12 @@ __global__ void __launch_bounds__(256, EXACT ? 2 : 1) k_pspace_eigen(
   }
   const double lam0 = 0.5 * (lo + hi);
   // ---- eigenvector of T for lam0 by one wave: inverse iteration,
-  // (lam0 - T) z = z, with pivots floored at 1e-15 of the spectrum's scale
+  // (lam0 - T) z = z, with pivots floored at 1e-15 of the spectrum's scale (at
+  // least 1e-115: their reciprocals' squares, summed below, have to be finite
+  // where T vanishes)
   if (t < 64) {
     const TwistedTri T =
-        twisted_factor(dd, ee, n, lam0, 1e-15 * fmax(scale, 1e-285), ll, ip, bb);
+        twisted_factor(dd, ee, n, lam0, 1e-15 * fmax(scale, 1e-100), ll, ip, bb);
     for (int i = t; i < n; i += 64) zz[i] = 1.0;
     wave_lds_fence();
     for (int rep = 0; rep < 3; ++rep) {

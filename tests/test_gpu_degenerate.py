@@ -57,3 +57,22 @@ def test_equal_casci_of_a_batch_are_bitwise_equal(n, na, nb, t):
         assert e[0] <= exact + 1e-8
     if t <= 1e-3:  # the lowest multiplet: within 4 t^2 / U of zero per bond
         assert abs(e[0]) <= 4 * n * t * t + 1e-8
+
+
+@pytest.mark.parametrize("n,na,nb,u", [(2, 1, 1, 0.0), (4, 2, 2, 0.0), (8, 4, 4, 0.0), (9, 4, 4, 0.0),
+                                       (7, 3, 3, 4.0), (9, 4, 4, 4.0), (9, 2, 5, 4.0)])
+def test_vanishing_pspace_block(n, na, nb, u):
+    """No hopping: the P-space holds only determinants without a doubly occupied
+    site, a block of zeros (for u = 0 the whole Hamiltonian vanishes).  The
+    lowest energy is 0, exactly: every term of sigma on such a vector is."""
+    from paper_1910_03527_amd import Context
+    _log("vanishing block", n, na, nb, u)
+    h, g = _atomic(n, u)
+    c = Context(0)
+    try:
+        e = c.casci([_dev(h)], [_dev(g)], na, nb)[0]
+        c.set_opts(precond=1)
+        e1 = c.casci([_dev(h)], [_dev(g)], na, nb)[0]
+    finally:
+        c.close()
+    assert abs(e) <= 1e-12 and abs(e1) <= 1e-12, (e, e1)
