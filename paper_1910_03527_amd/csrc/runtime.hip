@@ -550,7 +550,7 @@ int tile_for(mbefci_ctx* c, int n) {
   load_tune_cache(c);
   auto it = c->tuned.find(n);
   if (it != c->tuned.end()) return it->second.first;
-  return n >= 10 ? 32 : 64;  // measured defaults when nothing is tuned
+  return default_tile(n);
 }
 // tiles per workgroup: the tuned number, 0 for the plan's own choice (build_tiles)
 int tpw_for(mbefci_ctx* c, int n) {

@@ -7,6 +7,14 @@ namespace mbefci {
 
 constexpr int kCus = 256;
 
+// Tile width where nothing is tuned (calls of one sigma, one CASCI per launch
+// sequence).  10 orbitals, contraction in us with 32, 64 and 128: one CASCI of
+// 252 x 252 strings 15.2, 11.4, 11.5, of 45 x 252 12.4, 9.6, 9.6, 24 of 252 x
+// 252 159, 129, 150 (two waves per string hold eight column blocks each and
+// leave one wave per SIMD).  9 orbitals, 126 x 126: one 8.5 and 7.8, 24 34.8 and
+// 35.6 with 32 and 64; 8 orbitals, 70 x 70: one 6.8 and 6.6, 300 83 and 114.
+inline int default_tile(int n) { return n > 10 ? 32 : 64; }
+
 // Up to kStringMax orbitals a unit is a number of steps, each of the alpha
 // strings that a workgroup takes at a time (string_spw).  The most steps that
 // leave a plan with `steps` of them in all four units per CU.

@@ -16,7 +16,9 @@ DRIVER = r"""
 using namespace mbefci;
 int main(int argc, char** argv) {
   const int tuned = std::atoi(argv[2]);
-  if (argv[1][0] == 'k') {  // tuner: kept steps of a best length under a limit
+  if (argv[1][0] == 'd') {
+    std::printf("%d", default_tile(tuned));
+  } else if (argv[1][0] == 'k') {  // tuner: kept steps of a best length under a limit
     const int limit = std::atoi(argv[3]), kept = schedule_kept(tuned, limit);
     std::printf("%d", kept);
   } else if (argv[1][0] == 'c') {
@@ -77,3 +79,9 @@ def test_a_kept_schedule_gives_its_own_plan_the_timed_unit(rule, limit):
         assert (kept < 0) == (best >= limit and limit < 32)
         if kept < 0:
             assert rule("c", kept, max(limit, 4) + 1) == 0
+
+
+@pytest.mark.parametrize("n", range(2, 15))
+def test_default_tile(rule, n):
+    """Four waves on an alpha string up to 10 orbitals, 32 columns above."""
+    assert rule("d", n) == (64 if n <= 10 else 32)
