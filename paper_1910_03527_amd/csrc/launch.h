@@ -87,9 +87,9 @@ void launch_sigma_sym_gather(const Item* items, const Work* work, int nwork, con
 void launch_check_integrals(const double* h1, const double* eri, int M, int* flags,
                             hipStream_t s);
 void launch_fill(double* p, int64_t n, double v, hipStream_t s);
-// peak probes: FP64 MFMA chains (256-thread blocks; flops of one launch from
-// probe_mfma_flops) and a copy of n doubles (n even, 16-byte aligned)
-void launch_probe_mfma(double* out, int blocks, int iters, hipStream_t s);
+// peak probes: FP64 MFMA chains of either form (256-thread blocks; flops of one
+// launch from probe_mfma_flops) and a copy of n doubles (n even, 16-byte aligned)
+void launch_probe_mfma(double* out, int blocks, int iters, bool blocks4, hipStream_t s);
 double probe_mfma_flops(int blocks, int iters);
 void launch_probe_copy(const double* src, double* dst, int64_t n, int blocks, hipStream_t s);
 void launch_dav_guess(const Item* items, int ibase, int nitem, const double* diag, double* V,

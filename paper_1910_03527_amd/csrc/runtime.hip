@@ -2719,9 +2719,12 @@ int mbefci_probe_peaks(mbefci_ctx* c, double* fp64_mfma_tflops, double* copy_gbp
       return (double)best;
     };
     // sixteen blocks per CU in flight or queued, eight chains per wave: the
-    // rate no longer rises with either (measured), about 10 ms per launch
+    // rate no longer rises with either (measured), about 10 ms per launch.  The
+    // faster form counts: sigma of up to 10 orbitals issues 4x4x4 products.
     const int mblocks = 16 * ncu, iters = 2000;
-    const double tm = timed([&] { launch_probe_mfma(out, mblocks, iters, c->stream); }, 3);
+    double tm = 1e30;
+    for (bool blocks4 : {false, true})
+      tm = std::min(tm, timed([&] { launch_probe_mfma(out, mblocks, iters, blocks4, c->stream); }, 3));
     const double tc = timed([&] { launch_probe_copy(src, dst, n, 4 * ncu * 8, c->stream); }, 5);
     HIPCHK(hipEventDestroy(e0));
     HIPCHK(hipEventDestroy(e1));

@@ -155,3 +155,15 @@ def test_cap_counts_the_plan_in_hand_only():
             assert c.casci([h12], [g12], 5, 2) == want[1]
     finally:
         c.close()
+
+
+def test_probed_mfma_peak_is_that_of_the_faster_form():
+    """Independent chains of the 16x16x4 form end at 50 TFLOP/s, of the 4x4x4
+    form (which sigma of up to 10 orbitals issues) at 65 to 78.6."""
+    from paper_1910_03527_amd import Context
+    _log("probe")
+    c = Context(0)
+    try:
+        assert 55.0 < c.probe_peaks()["fp64_mfma_tflops"] < 80.0
+    finally:
+        c.close()
