@@ -230,15 +230,16 @@ int mbefci_sigma(mbefci_ctx* ctx, int32_t norb, int32_t nalpha, int32_t nbeta, c
 
 /* sigma = H c as mbefci_sigma computes it, for callers that cannot allocate
  * device memory (code under HIP graph capture, tight serving loops, harnesses
- * that forbid hipMalloc).  Allocates nothing: every intermediate (string, link
- * and pair tables, W, the contracted pair array G, work lists) lives in one
- * static device array of 32 MiB per GPU, held until the process ends.  Runs
- * only kernel launches, on hip_stream itself (no library stream, no events,
- * no synchronisation, no host copies, no memset nodes), so it may be captured
- * into a graph.  The integrals are not validated on the host (opts.validate
+ * that forbid hipMalloc).  Allocates nothing: every intermediate (string and
+ * link tables, the string Hamiltonians or, above 10 orbitals, the pair tables,
+ * W and the contracted pair array G, work lists) lives in one static device
+ * array of 32 MiB per GPU, held until the process ends.  Runs only kernel
+ * launches, on hip_stream itself (no library stream, no events, no
+ * synchronisation, no host copies, no memset nodes), so it may be captured into
+ * a graph.  The integrals are not validated on the host (opts.validate
  * does not apply).  Shapes: norb 0..14 whose tables, W and G fit the 32 MiB
- * (every shape up to CAS(10,10), 28.8 MB at 5+5 electrons); larger ones
- * return ENOMEM with the size in mbefci_last_error(ctx).  ctx supplies the
+ * (every shape of up to 10 orbitals, 1.2 MB at most); larger ones return
+ * ENOMEM with the size in mbefci_last_error(ctx).  ctx supplies the
  * device and the error message only: neither its plan nor its workspaces are
  * touched, so its other calls are unaffected.  Every call on a GPU shares that
  * GPU's array and leaves its contents behind: calls that overlap on one GPU

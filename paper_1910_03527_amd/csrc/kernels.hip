@@ -681,7 +681,7 @@ __global__ void k_string_links(int n, int ne, int64_t N, uint32_t* alpha, uint32
 // is permuted to match.  Bound by the FP64 matrix pipe (2 (Na + Nb) flops per
 // determinant, operands from L2): 0.26 ms for Hubbard-16, 50 TFLOP/s.
 // Where a plan has few tiles (1 x 1 then) a wave is one chain of loads, so
-// three chunks are in flight: CAS(10,10) 31 -> 22 us, eight CAS(9,9)s 18.5 ->
+// three chunks are in flight: CAS(10,10) 31 -> 22 us, 24 CAS(9,9)s 18.5 ->
 // 15.3 us against one.
 typedef double double2u_t __attribute__((ext_vector_type(2), aligned(8)));
 typedef double double2_t __attribute__((ext_vector_type(2)));
@@ -3353,7 +3353,7 @@ __global__ void __launch_bounds__(kCorrectThreads) k_pspace_correct(
 // entries, c values and c row load under this tile's products.  Measured:
 // CAS(14,14) 14.2 ms with 256 threads and every load waited for in the build,
 // 5.98 with 512, 4.94 with 1024; Hubbard-16 (10 orbitals) 1.83 ms, 1.56 with
-// 256, 1.40 with 512; eight CAS(8,8)s 57, 44 and 33 us.
+// 256, 1.40 with 512; one CAS(8,8) 57, 44 and 33 us.
 constexpr int rdm_threads(int nact) { return nact >= 13 ? 1024 : nact >= 8 ? 512 : 256; }
 template <int NACT, int TN, int NT = rdm_threads(NACT)>
 __global__ void __launch_bounds__(NT) k_rdm_syrk(const Item* __restrict__ items,
@@ -3576,9 +3576,6 @@ __device__ double sym_gamma2(int p, int q, int r, int s, int cp, int cq, int cr,
   }
   return 0.25 * acc;
 }
-
-// Sum over a wave by a butterfly: every lane ends with the same value, and
-// the order of the additions is fixed by the lane numbering alone.
 
 // Orbitals on which a CASCI's full-space RDMs can be non-zero: its active
 // orbitals and the occupied orbitals of the reference determinant (frozen
@@ -4200,7 +4197,7 @@ static bool sigma_string_t(const Item* items, const Work* work, int nwork, const
                            const double* V, int64_t ntot, double* Sv, const DavState* st, int slot,
                            hipStream_t s) {
   if constexpr (TN == 128 && (NACT == 8 || NACT == 9)) {
-    return false;  // not compiled
+    return false;  // an option of 128 stands for 64 there (tile_for)
   } else {
     constexpr int WPS = string_wps(NACT, TN), SPW = string_spw(NACT, TN);
     hipLaunchKernelGGL((k_sigma_dgemm<NACT, WPS, SPW>), dim3(nwork), dim3(64 * WPS * SPW), 0, s,
@@ -4550,7 +4547,9 @@ void launch_grad(const Item* items, int nitem, const int32_t* act, uint64_t occm
   const int64_t np = (int64_t)M * (M + 1) / 2;  // p >= q
   hipLaunchKernelGGL(k_grad_h, dim3((int)np), dim3(kGradHThreads), 0, s, items, nitem, act,
                      occmask, M, w, rdmp, roff, L, dh);
-  // 8 waves per SIMD x 1024 SIMDs: with fewer orbits a wave each leaves slots
+  // 8 waves per SIMD x 1024 SIMDs: with fewer orbits a wave each leaves slots.
+  // Whole backward with one and four waves: 14 orbitals (5,565 orbits) 330 and
+  // 281 us, 16 (9,316) 2.02 and 2.00 ms, 40 (336,610) 0.82 and 1.51 ms.
   const int64_t orbits = np * (np + 1) / 2;
   if (orbits < 8192)
     hipLaunchKernelGGL(k_grad_g<4>, dim3((int)orbits), dim3(256), 0, s, items, nitem, act, occmask,

@@ -36,13 +36,10 @@ void launch_casci_setup(int n, const double* const* h1s, const double* const* er
                         double* warena, hipStream_t s);
 void launch_hdiag(const Item* items, const Work* work, int nwork, const ItemHam* hams,
                   double* diag, hipStream_t s);
-// Above kStringMax orbitals: G = W D+, tn columns of one alpha string per tile
-// (work units: tile ranges).  Up to kStringMax: the opposite-spin part of
-// sigma, added to the same-spin part (work units: alpha string ranges); |tn| /
-// 16 waves per workgroup, which share an alpha string as far as it has column
-// blocks (tn > 0) or take one string each (tn < 0, at most 9 orbitals).
-// waves that share an alpha string (a power of two, at most its column blocks)
-// and alpha strings a workgroup takes at a time, n <= kStringMax
+// Waves that share an alpha string and alpha strings a workgroup takes at a
+// time, n <= kStringMax: a power of two of waves, at most the string's column
+// blocks rounded up (7 orbitals have three blocks: with 64 one of four waves
+// is idle in the products).
 __host__ __device__ constexpr int string_wps(int n, int tn) {
   const int cb = (string_binom(n, n / 2) + 15) / 16, most = cb > 4 ? 8 : cb > 2 ? 4 : cb;
   return tn < 0 ? 1 : tn / 16 < most ? tn / 16 : most;
@@ -50,6 +47,11 @@ __host__ __device__ constexpr int string_wps(int n, int tn) {
 __host__ __device__ constexpr int string_spw(int n, int tn) {
   return (tn < 0 ? -tn : tn) / 16 / string_wps(n, tn);
 }
+// Above kStringMax orbitals: G = W D+, tn columns of one alpha string per tile
+// (work units: tile ranges).  Up to kStringMax: the opposite-spin part of
+// sigma, added to the same-spin part (work units: alpha string ranges); |tn| /
+// 16 waves per workgroup, which share an alpha string as far as it has column
+// blocks (tn > 0) or take one string each (tn < 0, at most 9 orbitals).
 bool launch_sigma_dgemm(int n, int tn, const Item* items, const Work* work, int nwork,
                         const double* warena, const double* V, int64_t ntot, double* G,
                         double* Sv, const DavState* st, int slot, hipStream_t s);
@@ -61,10 +63,10 @@ void launch_sigma_gather(const Item* items, const Work* work, int nwork, const d
 // The gather's LDS reservation for items whose row block of G (npair rows
 // of the row stride) takes `row_block` bytes.  Each workgroup reads one
 // row block scattered; with many resident workgroups the L2 re-fetches it.
-// Measured (eight workgroups per CU uncapped): blocks of 112 KB (10
-// orbitals) do best at six per CU, blocks of 1 MB and more (13-14
-// orbitals) at four; blocks below 64 KB (9 orbitals and fewer) are not
-// capped.
+// Measured (eight workgroups per CU uncapped): blocks of 112 KB do best at
+// six per CU (taken while CASCIs of 10 orbitals still had a G; 11 and 12 have
+// 0.2 and 0.6 MB at half filling), blocks of 1 MB and more (13-14 orbitals) at
+// four; blocks below 64 KB (few beta strings) are not capped.
 inline int gather_lds_bytes(int64_t row_block) {
   if (row_block >= ((int64_t)1 << 20)) return 40960;  // four workgroups per CU
   if (row_block >= 64 * 1024) return 26624;           // six
@@ -115,7 +117,7 @@ struct PspaceArgs {
 // per item its first slot or -1, and the candidate keys (kMaxPspace per slot)
 // A chunk is one block's search, several passes over it; the chunks' candidates
 // (kMaxPspace each) are one block's again.  Small chunks for CASCIs whose
-// candidates stay few: eight CAS(9,9)s of 15,876 determinants take 32 us
+// candidates stay few: 24 CAS(9,9)s of 15,876 determinants take 32 us
 // in chunks of 2,048, 189 us in one; at CAS(14,14) candidates would be the work.
 __host__ __device__ inline int64_t select_chunk(int64_t nd) {
   return nd <= ((int64_t)1 << 17) ? 2048 : 16384;

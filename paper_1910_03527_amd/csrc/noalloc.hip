@@ -9,9 +9,8 @@
 // with hipGetSymbolAddress (noalloc_init, called when a context is created,
 // or on the first call on a device) and kept in g_scratch[device].  The
 // kernels are those of mbefci_sigma (kernels.hip); only the storage differs.
-// Up to kStringMax orbitals no G or W is needed, and the sigma operands and
-// link tables take their place (less room: every shape is accepted or
-// refused as if G were there).
+// From 2 to kStringMax orbitals the sigma operands and link tables take the
+// place of W and G: at most 1.2 MB, so every shape fits, as it did with G.
 // Calls that overlap on one GPU share the array and race.
 #include <hip/hip_runtime.h>
 

@@ -532,9 +532,9 @@ const SymTab& sym_tab(mbefci_ctx* c, int n, int na, int nb, const int* osym, int
 }
 
 void load_tune_cache(mbefci_ctx* c);
-// Tile widths compiled for active size n: 32 and 64 columns; 128 up to 12
-// orbitals except the three-wave workgroups of 8 and 9; flattened tiles of
-// 32 or 64 determinants up to 9 orbitals.
+// Tile widths compiled for active size n (launch_sigma_dgemm): 32 and 64; 128
+// up to 12 orbitals except 8 and 9; -32 and -64, one wave per alpha string, up
+// to 9 orbitals.
 bool tile_supported(int n, int tn) {
   if (tn == 32 || tn == 64) return n >= 2 && n <= 14;
   if (tn == 128) return n >= 2 && n <= 12 && n != 8 && n != 9;
