@@ -1858,7 +1858,9 @@ __device__ inline double floored(double p, double floor) {
   return fabs(p) < floor ? (p < 0 ? -floor : floor) : p;
 }
 // 1/x to about one unit in the last place: the hardware's estimate and two
-// Newton steps (a third of the latency of a divide).
+// Newton steps (a third of the latency of a divide).  It enters reflectors,
+// guesses and corrections only; energies and vectors are Rayleigh-Ritz pairs of
+// the sigma vectors.
 __device__ inline double newton_rcp(double x) {
   double y = __builtin_amdgcn_rcp(x);
   y = fma(fma(-x, y, 1.0), y, y);
