@@ -686,8 +686,8 @@ bool operand_room(mbefci_ctx* c, const Plan& P, int64_t doubles) {
   for (const auto& kv : c->bufs)
     if (kv.first != "G" && kv.first != "W") used += (int64_t)kv.second.bytes;
   for (const Item& I : P.items) {
-    const int64_t strips = (int64_t)I.Na * ((I.Nb + 63) / 64);
-    used += (std::min<int64_t>(strips, 520) + 1) * (8 * (int64_t)I.kpad * I.kpad + 32) +
+    const int64_t blocks = (I.Nb + 63) / 64, strips = I.Na * blocks;
+    used += (std::min<int64_t>(strips, 512 + blocks) + 1) * (8 * (int64_t)I.kpad * I.kpad + 32) +
             32 * (strips + I.Na) + 16384;
   }
   return used <= c->opts.max_workspace;
